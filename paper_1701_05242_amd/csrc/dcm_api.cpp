@@ -781,7 +781,7 @@ namespace {
 // current cell build
 dcm_status forces_impl(dcm_ctx *ctx, dcm_lj lj, int pair_rule, int prec, int ev_flags, double *fx,
                        double *fy, double *fz, double *energy, double *virial, int32_t *nnbr,
-                       uint64_t *npairs, bool use_list) {
+                       uint64_t *npairs, bool use_list, bool alone = false) {
   if (!ctx) return DCM_ERR_INVALID;
   if (ctx->cell_n < 0) return fail(ctx, DCM_ERR_INVALID, "dcm_forces before dcm_build_cells");
   if (use_list && ctx->list_n != ctx->cell_n)
@@ -802,8 +802,6 @@ dcm_status forces_impl(dcm_ctx *ctx, dcm_lj lj, int pair_rule, int prec, int ev_
     return fail(ctx, DCM_ERR_INVALID, "energy requested without a pointer");
   if ((ev_flags & DCM_EV_VIRIAL) && !virial)
     return fail(ctx, DCM_ERR_INVALID, "virial requested without a pointer");
-  const int64_t blocks = std::max<int64_t>(1, ceil_div(n, pair_block_size()));
-  DCM_TRY(ensure(ctx, ctx->partials, blocks * kPartialSlots * sizeof(double)));
   PairArgs a;
   a.pos = ptr<double4>(ctx->sorted);
   a.cell_start = ptr<int32_t>(ctx->cell_start);
@@ -817,6 +815,11 @@ dcm_status forces_impl(dcm_ctx *ctx, dcm_lj lj, int pair_rule, int prec, int ev_
   const bool rel = ctx->cell_rel && ctx->cell_qtab && prec == DCM_FP32_MIXED &&
                    pair_rule == DCM_PAIR_OWN && max_len <= kRelMaxEdgeSigma * lj.sigma;
   a.ext_rel = rel ? ptr<float4>(ctx->ext_rel) : nullptr;
+  // a list keeps the split it was built with
+  const int split_log =
+      use_list ? ctx->list_split : pair_split_log(n, ctx->rc_bound, pair_rule, rel, alone);
+  const int64_t blocks = pair_blocks(n, split_log);
+  DCM_TRY(ensure(ctx, ctx->partials, blocks * kPartialSlots * sizeof(double)));
   double span = 0.0;  // largest coordinate magnitude in the extended grid
   for (int k = 0; k < 3; ++k)
     span = std::max(span, ctx->cell_box.L[k] + 2.0 * ctx->halo[k] * ctx->cell_len[k]);
@@ -837,6 +840,7 @@ dcm_status forces_impl(dcm_ctx *ctx, dcm_lj lj, int pair_rule, int prec, int ev_
   a.eps = lj.epsilon;
   a.sigma = lj.sigma;
   a.ev_flags = ev_flags;
+  a.split_log = split_log;
   a.ctl = ctx->ctl;
   a.fx = fx;
   a.fy = fy;
@@ -909,8 +913,10 @@ dcm_status dcm_build_list(dcm_ctx *ctx, double skin) {
   if (ctx->cells_moved)
     return fail(ctx, DCM_ERR_INVALID,
                 "dcm_build_list after dcm_update_list: build the cells again first");
-  const int64_t n = ctx->cell_n, nw = list_waves(n);
-  DCM_TRY(ensure(ctx, ctx->list_count, std::max<int64_t>(n, 1) * sizeof(int32_t)));
+  const int64_t n = ctx->cell_n;
+  const int split_log = pair_split_log(n, ctx->rc_bound, DCM_PAIR_OWN, false, false);  // as the cell walk's
+  const int64_t nw = list_waves(n, split_log);
+  DCM_TRY(ensure(ctx, ctx->list_count, std::max<int64_t>(n << split_log, 1) * sizeof(int32_t)));
   DCM_TRY(ensure(ctx, ctx->list_wave_len, std::max<int64_t>(nw, 1) * sizeof(int32_t)));
   DCM_TRY(ensure(ctx, ctx->list_wave_start, (nw + 1) * sizeof(int32_t)));
   DCM_TRY(ensure(ctx, ctx->list_ref, std::max<int64_t>(n, 1) * sizeof(double4)));
@@ -931,6 +937,7 @@ dcm_status dcm_build_list(dcm_ctx *ctx, double skin) {
   }
   a.rc_bound = ctx->rc_bound;
   a.skin = skin;
+  a.split_log = split_log;
   a.count = ptr<int32_t>(ctx->list_count);
   a.wave_len = ptr<int32_t>(ctx->list_wave_len);
   a.wave_start = ptr<int32_t>(ctx->list_wave_start);
@@ -961,6 +968,7 @@ dcm_status dcm_build_list(dcm_ctx *ctx, double skin) {
   timer_end(ctx, "list", ev);
   DCM_TRY(check_launch(ctx, "dcm_build_list"));
   ctx->list_n = n;
+  ctx->list_split = split_log;
   ctx->list_skin = skin;
   return DCM_OK;
 }
@@ -1172,6 +1180,10 @@ dcm_status dcm_step(dcm_ctx *ctx, double *x, double *y, double *z, double *vx, d
   // the cells of this step were built beside the sweep (prebuild), and only
   // their records' cutoffs are missing
   bool prebuilt = false;
+  auto step_forces = [&](int ev_flags, double *e_out) -> dcm_status {
+    return forces_impl(ctx, lj, pair_rule, prec, ev_flags, W[WFX], W[WFY], W[WFZ], e_out, nullptr,
+                       nullptr, nullptr, false, true);
+  };
   auto forces = [&](double *e_out) -> dcm_status {
     // cells built on the second stream: complete before their records
     // take the cutoffs
@@ -1193,23 +1205,20 @@ dcm_status dcm_step(dcm_ctx *ctx, double *x, double *y, double *z, double *vx, d
     }
     if (prebuilt) {
       prebuilt = false;
-      return dcm_forces(ctx, lj, pair_rule, prec, DCM_EV_ENERGY, W[WFX], W[WFY], W[WFZ],
-                        e_out ? e_out : scal, nullptr, nullptr, nullptr);
+      return step_forces(DCM_EV_ENERGY, e_out ? e_out : scal);
     }
     if (step_cell_edge <= 0.0) {
       auto run = [&](double e) -> dcm_status {
         DCM_TRY(dcm_build_cells(ctx, W[WX], W[WY], W[WZ], W[WRC], n, box, e, rule.rc_max, prec,
                                 nullptr, nullptr));
         // forces only (a kernel instance apart from the steps' energy passes)
-        return dcm_forces(ctx, lj, pair_rule, prec, 0, W[WFX], W[WFY], W[WFZ], nullptr,
-                          nullptr, nullptr, nullptr);
+        return step_forces(0, nullptr);
       };
       DCM_TRY(tune_edge(ctx, edge_key, edge_cands, run, &step_cell_edge));
     }
     DCM_TRY(dcm_build_cells(ctx, W[WX], W[WY], W[WZ], W[WRC], n, box, step_cell_edge,
                             rule.rc_max, prec, nullptr, nullptr));
-    return dcm_forces(ctx, lj, pair_rule, prec, DCM_EV_ENERGY, W[WFX], W[WFY], W[WFZ],
-                      e_out ? e_out : scal, nullptr, nullptr, nullptr);
+    return step_forces(DCM_EV_ENERGY, e_out ? e_out : scal);
   };
   // Build the cells of a step on a second stream while the sweep runs on the
   // context's stream: the build reads only the positions, and the

@@ -12,7 +12,7 @@ namespace dcm {
 
 namespace {
 
-constexpr int kItem = 256;  // particles per work item = pair kernel block
+constexpr int kItem = 256;  // particles per block of the build = lanes of a pair work item
 // cell edges the tuner tries for systems that leave the edge to the library
 constexpr double kTuneEdges[] = {1.0, 1.15, 1.3, 1.5, 1.75};
 
@@ -37,9 +37,12 @@ struct BatchState {
   int row_lists = 0;    // the variant the next launches use
   bool needs_tuning = false;
   int plan_queues = 1;  // work-queue segments of the plan: 1 or kXcds
+  int plan_rule = 0;          // pair rule, and whether the force pass reads the compact
+  bool plan_compact = false;  // records, the plan's work items were made for
   // plan
   std::vector<SysGeom> geo;
-  std::vector<int2> items;  // natural order: system-major, also the particle block table
+  std::vector<int2> items;   // particle blocks of the build, system-major
+  std::vector<int2> pitems;  // pair work items in natural order: blocks of kItem >> split_log
   std::vector<int2> eblk;
   std::vector<int2> rblk;  // (system, first extended row) per group of 256 rows
   std::vector<int32_t> queue;
@@ -93,13 +96,22 @@ dcm_status check_system(dcm_ctx *ctx, const dcm_system &s, int32_t b, int ev_fla
   return DCM_OK;
 }
 
+// Whether the batch's force pass reads the compact records: FP32-mixed
+// own-cutoff forces on cells narrow enough for their precision.
+bool compact_records(const BatchState &B, dcm_lj lj, int rule, int prec) {
+  return B.rel_ok && prec == DCM_FP32_MIXED && rule == DCM_PAIR_OWN &&
+         B.max_len <= kRelMaxEdgeSigma * lj.sigma;
+}
+
 // Cell geometry, concatenated layout, block tables and work queue for the
 // batch, with `edge` for the systems that leave the cell edge to the tuner,
 // and `queues` work-queue segments (1 or kBatchQueues).
-dcm_status make_plan(dcm_ctx *ctx, BatchState &B, double edge, int queues) {
+dcm_status make_plan(dcm_ctx *ctx, BatchState &B, double edge, int queues, dcm_lj lj, int rule,
+                     int prec) {
   const int32_t nsys = (int32_t)B.desc.size();
   B.geo.assign(nsys, SysGeom{});
   B.items.clear();
+  B.pitems.clear();
   B.eblk.clear();
   B.rblk.clear();
   std::vector<double> cost_pp(nsys, 0.0);
@@ -183,27 +195,38 @@ dcm_status make_plan(dcm_ctx *ctx, BatchState &B, double edge, int queues) {
   // the most ghost copies any arrangement of the particles can need
   // (capped at what the pair kernel can address)
   B.ext_cap = std::max<int64_t>((int64_t)ext_bound, 1);
+  // pair work items, with the lanes per particle of the single-system calls
+  B.plan_rule = rule;
+  B.plan_compact = compact_records(B, lj, rule, prec);
+  for (int32_t b = 0; b < nsys; ++b) {
+    SysGeom &g = B.geo[b];
+    g.split_log = pair_split_log(g.n, g.rc_cap, rule, B.plan_compact, false);
+    const int64_t per = kItem >> g.split_log;
+    g.pitem0 = (int64_t)B.pitems.size();
+    g.npitems = ceil_div(g.n, per);
+    for (int64_t k = 0; k < g.npitems; ++k) B.pitems.push_back(make_int2(b, (int)(k * per)));
+  }
   // work queue: largest estimated cost first, ties in natural order
-  const int64_t nitems = (int64_t)B.items.size();
-  std::vector<double> cost(nitems);
-  for (int64_t k = 0; k < nitems; ++k) {
-    const int b = B.items[k].x;
-    const int64_t cnt = std::min<int64_t>(kItem, B.desc[b].n - B.items[k].y);
+  const int64_t npitems = (int64_t)B.pitems.size();
+  std::vector<double> cost(npitems);
+  for (int64_t k = 0; k < npitems; ++k) {
+    const int b = B.pitems[k].x;
+    const int64_t cnt = std::min<int64_t>(kItem >> B.geo[b].split_log, B.desc[b].n - B.pitems[k].y);
     cost[k] = cost_pp[b] * (double)cnt;
   }
   B.plan_queues = queues;
-  B.queue.resize(nitems);
+  B.queue.resize(npitems);
   B.qseg.assign(queues + 1, 0);
   if (queues == 1) {
     std::iota(B.queue.begin(), B.queue.end(), 0);
     std::stable_sort(B.queue.begin(), B.queue.end(),
                      [&](int32_t a, int32_t b) { return cost[a] > cost[b]; });
-    B.qseg[1] = (int32_t)nitems;
+    B.qseg[1] = (int32_t)npitems;
   } else {
     // whole systems to segments, the costliest first onto the least loaded
     // one; a segment lists its systems' items in natural order
     std::vector<double> scost(nsys, 0.0);
-    for (int64_t k = 0; k < nitems; ++k) scost[B.items[k].x] += cost[k];
+    for (int64_t k = 0; k < npitems; ++k) scost[B.pitems[k].x] += cost[k];
     std::vector<int32_t> order(nsys);
     std::iota(order.begin(), order.end(), 0);
     std::stable_sort(order.begin(), order.end(),
@@ -218,24 +241,27 @@ dcm_status make_plan(dcm_ctx *ctx, BatchState &B, double edge, int queues) {
     int64_t pos = 0;
     for (int q = 0; q < queues; ++q) {
       B.qseg[q] = (int32_t)pos;
-      for (int64_t k = 0; k < nitems; ++k)
-        if (seg_of[B.items[k].x] == q) B.queue[pos++] = (int32_t)k;
+      for (int64_t k = 0; k < npitems; ++k)
+        if (seg_of[B.pitems[k].x] == q) B.queue[pos++] = (int32_t)k;
     }
     B.qseg[queues] = (int32_t)pos;
   }
   // device tables, uploaded once per plan
   B.off_geo = 0;
+  const int64_t nitems = (int64_t)B.items.size();
   B.off_items = align256(sizeof(SysGeom) * nsys);
   B.off_eblk = B.off_items + align256(sizeof(int2) * std::max<int64_t>(nitems, 1));
   B.off_rblk = B.off_eblk + align256(sizeof(int2) * std::max<size_t>(B.eblk.size(), 1));
   B.off_queue = B.off_rblk + align256(sizeof(int2) * std::max<size_t>(B.rblk.size(), 1));
-  B.off_qseg = B.off_queue + align256(sizeof(int32_t) * std::max<int64_t>(nitems, 1));
+  B.off_qseg = B.off_queue + align256(sizeof(int4) * std::max<int64_t>(npitems, 1));
   B.table_bytes = B.off_qseg + align256(sizeof(int32_t) * (queues + 1));
   B.table_host.assign(B.table_bytes, 0);
   std::memcpy(B.table_host.data() + B.off_geo, B.geo.data(), sizeof(SysGeom) * nsys);
   if (nitems) {
     std::memcpy(B.table_host.data() + B.off_items, B.items.data(), sizeof(int2) * nitems);
-    std::memcpy(B.table_host.data() + B.off_queue, B.queue.data(), sizeof(int32_t) * nitems);
+    int4 *q = reinterpret_cast<int4 *>(B.table_host.data() + B.off_queue);
+    for (int64_t k = 0; k < npitems; ++k)
+      q[k] = make_int4(B.pitems[B.queue[k]].x, B.pitems[B.queue[k]].y, B.queue[k], 0);
   }
   std::memcpy(B.table_host.data() + B.off_qseg, B.qseg.data(), sizeof(int32_t) * (queues + 1));
   if (!B.eblk.empty())
@@ -279,7 +305,7 @@ dcm_status make_plan(dcm_ctx *ctx, BatchState &B, double edge, int queues) {
   if ((st = ensure(ctx, B.ext_pos, sizeof(double4) * B.ext_cap)) != DCM_OK) return st;
   if (B.rel_ok && (st = ensure(ctx, B.ext_rel, sizeof(float4) * B.ext_cap)) != DCM_OK) return st;
   if ((st = ensure(ctx, B.partials,
-                   sizeof(double) * kPartialSlots * std::max<int64_t>(nitems, 1))) != DCM_OK)
+                   sizeof(double) * kPartialSlots * std::max<int64_t>(npitems, 1))) != DCM_OK)
     return st;
   if ((st = ensure(ctx, B.rcmax, sizeof(unsigned long long) * nsys)) != DCM_OK) return st;
   if ((st = ensure(ctx, B.rcmax_part, sizeof(unsigned long long) * std::max<int64_t>(nitems, 1))) !=
@@ -305,13 +331,9 @@ void enqueue(dcm_ctx *ctx, BatchState &B, hipStream_t s, dcm_lj lj, int rule, in
   const SysGeom *geo = dptr<SysGeom>(B.tables, B.off_geo);
   const int2 *items = dptr<int2>(B.tables, B.off_items);
   const int2 *eblk = dptr<int2>(B.tables, B.off_eblk);
-  const int32_t *queue = dptr<int32_t>(B.tables, B.off_queue);
   const int64_t nitems = (int64_t)B.items.size();
   // FP32-mixed own-cutoff forces read the compact records
-  float4 *rel = (B.rel_ok && prec == DCM_FP32_MIXED && rule == DCM_PAIR_OWN &&
-                 B.max_len <= kRelMaxEdgeSigma * lj.sigma)
-                    ? dptr<float4>(B.ext_rel)
-                    : nullptr;
+  float4 *rel = compact_records(B, lj, rule, prec) ? dptr<float4>(B.ext_rel) : nullptr;
   hipEvent_t ev = nullptr;
   if (timed) timer_begin(ctx, "batch_cells", &ev);
   launch_zero2_i32(s, dptr<int32_t>(B.cell_count), dptr<int32_t>(B.cell_fill), B.cells_total);
@@ -340,11 +362,10 @@ void enqueue(dcm_ctx *ctx, BatchState &B, hipStream_t s, dcm_lj lj, int rule, in
   if (timed) timer_end(ctx, "batch_cells", ev);
   BatchPairArgs a;
   a.sys = geo;
-  a.items = items;
-  a.queue = queue;
+  a.queue = dptr<int4>(B.tables, B.off_queue);
   a.qseg = dptr<int32_t>(B.tables, B.off_qseg);
   a.nqueues = B.plan_queues;
-  a.nitems = (int32_t)nitems;
+  a.nitems = (int32_t)B.pitems.size();
   a.head = dptr<uint32_t>(B.head);
   a.pos = dptr<double4>(B.sorted);
   a.cell_start = dptr<int32_t>(B.cell_start);
@@ -389,7 +410,7 @@ dcm_status tune(dcm_ctx *ctx, BatchState &B, dcm_lj lj, int rule, int prec, int 
     const int il = trial % nlists, iq = (trial / nlists) % nlayouts;
     const double edge = kTuneEdges[trial / (nlists * nlayouts)];
     const int queues = ctx->batch_queues ? ctx->batch_queues : (iq ? kBatchQueues : 1);
-    if (il == 0 && (st = make_plan(ctx, B, edge, queues)) != DCM_OK) break;
+    if (il == 0 && (st = make_plan(ctx, B, edge, queues, lj, rule, prec)) != DCM_OK) break;
     B.row_lists = ctx->batch_lists ? ctx->batch_lists - 1 : il;
     enqueue(ctx, B, ctx->stream, lj, rule, prec, ev_flags, false);
     const hipError_t r0 = hipEventRecord(e0, ctx->stream);
@@ -494,8 +515,12 @@ dcm_status dcm_forces_batched(dcm_ctx *ctx, int32_t nsys, const dcm_system *sys,
   const int queues =
       ctx->batch_queues ? ctx->batch_queues : (B.needs_tuning ? B.tuned_queues : 1);
   B.row_lists = ctx->batch_lists ? ctx->batch_lists - 1 : (B.needs_tuning ? B.tuned_lists : 0);
-  if (!B.have_plan || B.plan_edge != edge || B.plan_queues != queues) {
-    if ((st = make_plan(ctx, B, edge, queues)) != DCM_OK) {
+  // (the lanes per particle, and so the pair work items, follow the rule and
+  // whether the compact records serve)
+  if (!B.have_plan || B.plan_edge != edge || B.plan_queues != queues ||
+      B.plan_rule != pair_rule ||
+      B.plan_compact != compact_records(B, lj, pair_rule, prec)) {
+    if ((st = make_plan(ctx, B, edge, queues, lj, pair_rule, prec)) != DCM_OK) {
       B.have_plan = false;
       return st;
     }

@@ -154,6 +154,15 @@ __device__ __forceinline__ int64_t row_prefix(const int32_t *__restrict__ cell_s
   return (int64_t)p * T + (cell_start[r0 + r] - cell_start[r0]);
 }
 
+// Several lanes may share one particle's cell rows: row (y, z) belongs to
+// part (y - cy + row_skew (z - cz)) mod 2^split_log, (cy, cz) the particle's
+// own cell.  The share depends on the row alone, so the cell walk and the
+// Verlet list deal the same rows to the same lanes.  With the skew the parts
+// of the 3 x 3 to 9 x 9 rows of a search disc differ by a row or two.
+__device__ __forceinline__ int row_skew(int split_log) {
+  return split_log == 0 ? 0 : (split_log <= 2 ? 1 : (split_log == 3 ? 3 : 4));
+}
+
 // MI355X has 8 XCDs, each with its own L2; consecutive workgroups are
 // dispatched round-robin across them.  xcd_block(b, n, G) remaps workgroup b
 // so that each XCD receives runs of G consecutive logical blocks (spatially

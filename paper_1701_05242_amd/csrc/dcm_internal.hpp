@@ -113,6 +113,9 @@ struct SysGeom {
   int64_t row0;       // first extended row (rows: ne[1] * ne[2] per system)
   int64_t item0;      // first pair work item (blocks of 256 particles)
   int64_t nitems;
+  int64_t pitem0;     // the same for the force pass (blocks of 256 >> split_log particles)
+  int64_t npitems;
+  int32_t split_log;  // lanes sharing a particle in the force pass (pair_split_log)
   double rel_delta;   // error bound of the compact records (rel_record_delta)
   int32_t nc[3], h[3], ne[3];
   double len[3], sc[3], L[3];
@@ -138,6 +141,7 @@ struct dcm_ctx {
   dcm::DevBuf list_count, list_wave_len, list_wave_start, list;
   dcm::DevBuf list_ref, list_part, list_out;
   int64_t list_n = -1;  // particles of the list (-1: none built)
+  int list_split = 0;   // lanes sharing a particle in it (pair_split_log)
   double list_skin = 0.0;
   int32_t *h_list_total = nullptr;  // pinned: entries / 64 of the last build
   double *h_list_verdict = nullptr; // pinned: [displacement, slack] of the last update
@@ -406,6 +410,7 @@ struct PairArgs {
   double rc_bound;
   double eps, sigma;
   int ev_flags;
+  int split_log;             // lanes sharing a particle: 2^split_log (pair_split_log)
   const Ctl *ctl;
   double *fx, *fy, *fz;
   int32_t *nnbr;
@@ -417,7 +422,47 @@ struct PairArgs {
   double4 *n3_f;
   int32_t *n3_cnt;           // null without DCM_EV_COUNTS
 };
-int pair_block_size();
+// workgroups of a force pass over n particles, 2^split_log lanes for each
+int64_t pair_blocks(int64_t n, int split_log);
+// Lanes that share one particle's rows in a force pass over n particles with
+// cutoffs up to rc_max, as a power of 2.  One lane per particle leaves most of
+// the chip idle below a few hundred thousand particles, and its time is then
+// that of the longest walk (a particle near an interface tests thousands of
+// candidates): 0.25 ms for 3,000 particles as for 99,000.  More lanes shorten
+// the walk, but each pays the set-up, the planes and the closing sums again.
+// The long walks grow with rc_max^3 and the rest with n, so the best number
+// follows m = n (6 / rc_max)^3.
+// compact: the force pass reads the compact records (cheaper candidates, so
+// the overhead weighs more).
+// alone: dcm_step's own passes.  The other calls share one rule, because a
+// batch returns what single-system calls do bit for bit, and in a batch the
+// other systems fill the chip: that rule stays where a 64-system batch of
+// 2,000 to 200,000 particles loses at most a few per cent of its time.
+// Measured, us per dcm_step without detection at 1, 2, 4, 8, 16 lanes (n in
+// thousands, rc_max):
+//   compact: 8, 6: 218 149 106 96 90; 40, 6: 223 160 121 114 121; 100, 4.5:
+//     172 134 134 141 163; 341, 8 (cylinder): 672 609 522 480 560; 400, 4.5:
+//     275 248 255 305 391; 800, 8: 681 565 574 648 842; 2600, 8: 1423 1376
+//     1555 1878
+//   FP64: 8, 6: 328 190 131 107 96; 99, 6: 364 245 216 198 216; 200, 4.5: 278
+//     230 206 221 236; 341, 8 (cylinder): 1581 1421 1285 1191 1270; 400, 4.5:
+//     413 340 316 343 389; 1200, 8: 1451 1245 1206 1229 1555
+//   64-system batch, compact: 1440 1516 1743 2319; FP64: 2106 2073 2243 2665
+// From 500,000 particles on, FP64 passes use one number everywhere, so
+// dcm_step's forces there are those of dcm_forces on the same cells.
+inline int pair_split_log(int64_t n, double rc_max, int rule, bool compact, bool alone) {
+  if (rule == DCM_PAIR_MAX_N3) return 0;  // bound by the reactions' atomics
+  const double q = 6.0 / rc_max, m = (double)n * (q * q * q);
+  if (compact) {
+    if (alone) return m < 16e3 ? 4 : (m < 150e3 ? 3 : (m < 300e3 ? 2 : (m < 3e6 ? 1 : 0)));
+    return n < 8000 ? 2 : (n < 32000 ? 1 : 0);
+  }
+  if (n >= 500000) return 2;
+  // (the symmetric rule walks every particle with the largest cutoff and
+  // gains least from many lanes)
+  if (alone && rule == DCM_PAIR_OWN) return m < 20e3 ? 4 : (m < 150e3 ? 3 : 2);
+  return n < 8000 ? 3 : (n < 100000 ? 2 : 1);
+}
 void launch_pair(hipStream_t s, const PairArgs &a, int rule, int prec);
 // rule DCM_PAIR_MAX_N3: sorted-order sums to caller order (24 eps applied)
 void launch_n3_out(hipStream_t s, const double4 *f, const int32_t *cnt, const int32_t *perm,
@@ -437,7 +482,8 @@ struct ListArgs {
   int32_t nc[3], h[3], ne[3];
   double len[3], sc[3];
   double rc_bound, skin;
-  int32_t *count;            // [n] list lengths
+  int split_log;             // lanes sharing a particle: 2^split_log (pair_split_log)
+  int32_t *count;            // [n << split_log] list lengths
   int32_t *wave_len;         // [n_waves] longest list of each wavefront
   const int32_t *wave_start; // [n_waves + 1] exclusive scan of wave_len
   int64_t n_waves;
@@ -446,7 +492,7 @@ struct ListArgs {
   double4 *ref;              // [n] build position and list radius R (count pass)
   uint32_t *status;
 };
-int64_t list_waves(int64_t n);
+int64_t list_waves(int64_t n, int split_log);
 int64_t list_update_blocks(int64_t n);
 // new positions and cutoffs for the cells of the list's build (sorted order),
 // out[0] = largest displacement from the build, out[1] = smallest R - r_c
@@ -459,8 +505,9 @@ void launch_list_fill(hipStream_t s, const ListArgs &a);
 
 struct BatchPairArgs {
   const SysGeom *sys;
-  const int2 *items;          // work item -> (system, first local particle)
-  const int32_t *queue;       // items in the order they are handed out, in nqueues segments
+  // work items (system, first local particle, item, -) in the order they are
+  // handed out, in nqueues segments
+  const int4 *queue;
   const int32_t *qseg;        // [nqueues + 1] segment starts in queue
   int32_t nqueues;            // 1, or kXcds: segment x first serves workgroups on XCD x
   int32_t nitems;

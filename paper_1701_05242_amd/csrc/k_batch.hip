@@ -279,7 +279,7 @@ __global__ __launch_bounds__(kReduceThreads) void kb_reduce(const SysGeom *__res
   const SysGeom &g = sys[blockIdx.x];
   __shared__ double red[kReduceThreads / 64][kPartialSlots];
   double t[kPartialSlots];
-  sum_rows<kReduceThreads, kPartialSlots>(partials + g.item0 * kPartialSlots, g.nitems, red, t);
+  sum_rows<kReduceThreads, kPartialSlots>(partials + g.pitem0 * kPartialSlots, g.npitems, red, t);
   if (threadIdx.x == 0) {
     if (g.energy && (ev_flags & DCM_EV_ENERGY)) *g.energy = t[0];
     if (g.virial && (ev_flags & DCM_EV_VIRIAL))

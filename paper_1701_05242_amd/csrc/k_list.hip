@@ -22,10 +22,11 @@ __device__ __forceinline__ int clampl(int v, int lo, int hi) {
 
 // Walk the rows of sorted particle s within radius R (x, y, z, self slot
 // given) and call f(j) for every extended slot j != self with r^2 < R^2, in
-// row order (z planes, then y rows, then x).
+// row order (z planes, then y rows, then x), for the rows of the lane's part
+// (row_skew).
 template <typename F>
 __device__ __forceinline__ void walk_within(const ListArgs &a, double xi, double yi, double zi,
-                                            double R, int self, F &&f) {
+                                            double R, int self, int part, F &&f) {
   const int nx = a.nc[0], ny = a.nc[1], nz = a.nc[2];
   const int hx = a.h[0], hy = a.h[1], hz = a.h[2];
   const int nex = a.ne[0], ney = a.ne[1];
@@ -44,7 +45,9 @@ __device__ __forceinline__ void walk_within(const ListArgs &a, double xi, double
     const double wy = (double)(sqrtf((float)remz) * 1.00001f) + guard;
     const int ylo = clampl((int)floor((yi - wy) * a.sc[1]), -hy, ny + hy - 1);
     const int yhi = clampl((int)floor((yi + wy) * a.sc[1]), -hy, ny + hy - 1);
-    for (int y = ylo; y <= yhi; ++y) {
+    const int parts = 1 << a.split_log;
+    const int y0 = ylo + ((part - (ylo - cy) - row_skew(a.split_log) * (z - cz)) & (parts - 1));
+    for (int y = y0; y <= yhi; y += parts) {
       double ey = 0.0;
       if (y < cy) ey = yi - (double)(y + 1) * a.len[1];
       else if (y > cy) ey = (double)y * a.len[1] - yi;
@@ -87,13 +90,17 @@ __device__ __forceinline__ bool list_lane(const ListArgs &a, int64_t s, double &
 
 // Pass 1: list lengths; the longest of each wavefront into wave_len.
 __global__ __launch_bounds__(kListBlock) void k_list_count(ListArgs a) {
-  const int64_t s = blockIdx.x * (int64_t)kListBlock + threadIdx.x;
+  const int64_t t = blockIdx.x * (int64_t)kListBlock + threadIdx.x;
+  const int64_t s = t >> a.split_log;
+  const int part = (int)t & ((1 << a.split_log) - 1);
   double xi, yi, zi, R;
   int self = -1, cnt = 0;
-  if (list_lane(a, s, xi, yi, zi, R, self)) walk_within(a, xi, yi, zi, R, self, [&](int) { ++cnt; });
+  if (list_lane(a, s, xi, yi, zi, R, self))
+    walk_within(a, xi, yi, zi, R, self, part, [&](int) { ++cnt; });
   if (s < a.n) {
-    a.count[s] = cnt;
-    a.ref[s] = make_double4(xi, yi, zi, R);  // where the list was built, and its radius
+    a.count[t] = cnt;
+    // where the list was built, and its radius
+    if (part == 0) a.ref[s] = make_double4(xi, yi, zi, R);
   }
   int m = cnt;
 #pragma unroll
@@ -101,22 +108,24 @@ __global__ __launch_bounds__(kListBlock) void k_list_count(ListArgs a) {
     const int o = __shfl_xor(m, off, 64);
     m = o > m ? o : m;
   }
-  if ((threadIdx.x & 63) == 0 && (s >> 6) < a.n_waves) a.wave_len[s >> 6] = m;
+  if ((threadIdx.x & 63) == 0 && (t >> 6) < a.n_waves) a.wave_len[t >> 6] = m;
 }
 
 // Pass 2: the entries, at wave_base + 64 k + lane.
 __global__ __launch_bounds__(kListBlock) void k_list_fill(ListArgs a) {
-  const int64_t s = blockIdx.x * (int64_t)kListBlock + threadIdx.x;
+  const int64_t t = blockIdx.x * (int64_t)kListBlock + threadIdx.x;
+  const int64_t s = t >> a.split_log;
+  const int part = (int)t & ((1 << a.split_log) - 1);
   double xi, yi, zi, R;
   int self = -1;
   if (!list_lane(a, s, xi, yi, zi, R, self)) return;
-  const int64_t base = 64 * (int64_t)a.wave_start[s >> 6] + (s & 63);
+  const int64_t base = 64 * (int64_t)a.wave_start[t >> 6] + (t & 63);
   if (64 * (int64_t)a.wave_start[a.n_waves] > a.list_cap) {
     atomicOr(a.status, ST_GHOST_OVERFLOW);
     return;
   }
   int k = 0;
-  walk_within(a, xi, yi, zi, R, self, [&](int j) {
+  walk_within(a, xi, yi, zi, R, self, part, [&](int j) {
     a.list[base + 64 * (int64_t)k] = j;
     ++k;
   });
@@ -222,15 +231,15 @@ void launch_list_update(hipStream_t s, const double *x, const double *y, const d
   hipLaunchKernelGGL(k_list_verdict, dim3(1), dim3(kListBlock), 0, s, part, blocks, out);
 }
 
-int64_t list_waves(int64_t n) { return ceil_div(n, 64); }
+int64_t list_waves(int64_t n, int split_log) { return ceil_div(n << split_log, 64); }
 
 void launch_list_count(hipStream_t s, const ListArgs &a) {
-  const int64_t blocks = ceil_div(a.n, kListBlock) > 0 ? ceil_div(a.n, kListBlock) : 1;
+  const int64_t blocks = std::max<int64_t>(ceil_div(a.n << a.split_log, kListBlock), 1);
   hipLaunchKernelGGL(k_list_count, dim3((unsigned)blocks), dim3(kListBlock), 0, s, a);
 }
 
 void launch_list_fill(hipStream_t s, const ListArgs &a) {
-  const int64_t blocks = ceil_div(a.n, kListBlock) > 0 ? ceil_div(a.n, kListBlock) : 1;
+  const int64_t blocks = std::max<int64_t>(ceil_div(a.n << a.split_log, kListBlock), 1);
   hipLaunchKernelGGL(k_list_fill, dim3((unsigned)blocks), dim3(kListBlock), 0, s, a);
 }
 

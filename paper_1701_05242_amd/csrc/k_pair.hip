@@ -1,8 +1,9 @@
 // Dynamic-cutoff Lennard-Jones force, energy and virial (Section 2.4,
 // Algorithm 2.3, Eqs. 2-3) over the linked cells of Section 2.3.
 //
-// One lane owns one particle i (particles in cell order, so a wavefront
-// covers neighbouring particles with similar cutoffs).  Instead of storing
+// A lane, or a group of up to 16 lanes that deal the particle's rows among
+// them (pair_split_log), owns one particle i (particles in cell order, so a
+// wavefront covers neighbouring particles with similar cutoffs).  Instead of storing
 // the neighbour list of Algorithm 2.2, each lane enumerates the cell rows
 // (fixed y and z cell; consecutive x cells are consecutive in memory) that can
 // hold a j within its search radius and trims each row to the chord of the
@@ -39,13 +40,14 @@ namespace dcm {
 constexpr int kPairBlock = 256;
 // Row ranges per lane per chunk (LDS: 8 B each), for the kernels reading FP64
 // records and for those reading compact records.  A smaller list allows more
-// resident workgroups: the compact-record kernels, with cheaper candidates,
-// gain from that, while the FP64 kernels, bound by their gathers, lose
-// (measured on the large slab).  The compact-record kernels also hold their
+// resident workgroups but cuts a lane's rows into more chunks.  The FP64
+// kernels share a particle among two to sixteen lanes (pair_split_log), whose
+// rows fit a list of 18: four workgroups on a compute unit instead of three
+// with 24 (1.2 M-particle step: 1.231 / 1.206 / 1.213 ms with 24 / 18 / 12).  The compact-record kernels also hold their
 // close-pair queue (kNearCap + 1 entries of 4 B); with 14 row entries both
 // fit in the 40 KB of LDS that keeps four workgroups on a compute unit.
 #ifndef DCM_PAIR_SEGCAP
-#define DCM_PAIR_SEGCAP 24
+#define DCM_PAIR_SEGCAP 18
 #endif
 #ifndef DCM_PAIR_SEGCAP_REL
 #define DCM_PAIR_SEGCAP_REL 14
@@ -70,7 +72,9 @@ constexpr int kXcdGroup = DCM_PAIR_XCD_GROUP;
 constexpr int kFillRows = DCM_PAIR_FILL;  // cell rows whose starts are read together
 static_assert(kSegCap >= kFillRows + 4 && kSegCapRel >= kFillRows + 4,
               "a chunk holds a batch of rows, a sentinel and a look-ahead entry");
-int pair_block_size() { return kPairBlock; }
+int64_t pair_blocks(int64_t n, int split_log) {
+  return n > 0 ? ceil_div(n << split_log, kPairBlock) : 1;
+}
 
 // Per-lane accumulators.
 template <int PREC>
@@ -303,6 +307,7 @@ struct PairView {
   double len[3], sc[3];
   double rc_bound;
   const unsigned long long *rc_all_bits;  // largest cutoff of the system (rule MAX)
+  int split_log;                 // log2 of the lanes that share a particle (pair_split_log)
   double *fx, *fy, *fz;
   int32_t *nnbr;
   const int32_t *ext_src;        // rule DCM_PAIR_MAX_N3: source slot of each extended slot
@@ -334,6 +339,8 @@ struct LaneGeo {
   double sig2;
   int zlo, zhi, cx, cy, cz, self;
   int slot;  // sorted slot of the lane's particle
+  // the lane's share of its particle's rows (row_part): part `part` of `parts`
+  int part, parts, skew;
 };
 
 // Newton's third law (rule MAX): a pair belongs to the endpoint with the
@@ -582,11 +589,13 @@ __device__ __forceinline__ void sweep_rows(const PairView &v, bool run, const La
     const float remz = fmaf(-ez, ez, g.fR2);
     if (remz < 0.0f) return false;
     const float w = __builtin_amdgcn_sqrtf(remz) + g.fguard;
-    ylo_c = clampi(g.cy + cell_off(-w, g, 1), -hy, ny + hy - 1);
+    const int ylo = clampi(g.cy + cell_off(-w, g, 1), -hy, ny + hy - 1);
     yhi_c = clampi(g.cy + cell_off(w, g, 1), -hy, ny + hy - 1);
+    // this lane's first row of the plane; its others follow every `parts` rows
+    ylo_c = ylo + ((g.part - (ylo - g.cy) - g.skew * (z - g.cz)) & (g.parts - 1));
     remz_c = remz;
     rowbase_c = ((z + hz) * ney + hy) * nex + hx;
-    return true;
+    return ylo_c <= yhi_c;
   };
   bool rows_left = false;
   if (run)
@@ -636,7 +645,7 @@ __device__ __forceinline__ void sweep_rows(const PairView &v, bool run, const La
         const int zcur = zc, ycur = yc, rowbase = rowbase_c;
         const float remz = remz_c;
         bool in = rows_left;
-        if (rows_left && ++yc > yhi_c) {
+        if (rows_left && (yc += g.parts) > yhi_c) {
           bool more = false;
           while (++zc <= g.zhi)
             if (plane(zc)) {
@@ -736,23 +745,60 @@ __device__ __forceinline__ void sweep_rows(const PairView &v, bool run, const La
   }
 }
 
+// Sums over aligned groups of lanes with data-parallel moves inside a row of
+// 16 lanes (no trip through LDS): after the lanes of a half hold equal sums,
+// a mirror reaches the other half as an exchange would.
+constexpr int kDppXor1 = 0xb1, kDppXor2 = 0x4e, kDppHalfMirror = 0x141, kDppMirror = 0x140;
+template <int CTRL>
+__device__ __forceinline__ int dpp_move(int v) {
+  return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, true);
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp_move(double v) {
+  const long long b = __double_as_longlong(v);
+  const int lo = dpp_move<CTRL>((int)b), hi = dpp_move<CTRL>((int)(b >> 32));
+  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+template <int CTRL>
+__device__ __forceinline__ void dpp_add(double &a, double &b, double &c, int &k) {
+  a += dpp_move<CTRL>(a);
+  b += dpp_move<CTRL>(b);
+  c += dpp_move<CTRL>(c);
+  k += dpp_move<CTRL>(k);
+}
+// the whole wavefront's sum, in every lane (every lane must be active)
+template <typename T>
+__device__ __forceinline__ T wave_total(T v) {
+  v += dpp_move<kDppXor1>(v);
+  v += dpp_move<kDppXor2>(v);
+  v += dpp_move<kDppHalfMirror>(v);
+  v += dpp_move<kDppMirror>(v);
+  v += __shfl_xor(v, 16, 64);
+  v += __shfl_xor(v, 32, 64);
+  return v;
+}
+
 // The block's deterministic partial sums: E = e_scale * sum of the lanes'
 // energy terms, W = w_scale * virial terms, and the pair count.
-template <int PREC>
-__device__ __forceinline__ void block_partials(const Acc<PREC> &acc, int64_t cnt, double e_scale,
-                                               double w_scale, double (*red)[kPartialSlots],
+// A sum that the kernel's mode EVM leaves at zero is not reduced (a block of
+// few particles, each shared by many lanes, would spend a third of its time
+// on the eight wavefront sums).
+template <int PREC, int EVM>
+__device__ __forceinline__ void block_partials(const Acc<PREC> &acc, int cnt, double cnt_scale,
+                                               double e_scale, double w_scale,
+                                               double (*red)[kPartialSlots],
                                                double *partial_out) {
-  double pv[kPartialSlots];
-  pv[0] = (double)acc.e * e_scale;
-#pragma unroll
-  for (int k = 0; k < 6; ++k) pv[1 + k] = (double)acc.w[k] * w_scale;
-  pv[7] = (double)cnt;
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  double pv[kPartialSlots] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+  if constexpr ((EVM & 1) != 0) pv[0] = wave_total((double)acc.e * e_scale);
+  if constexpr ((EVM & 2) != 0)
 #pragma unroll
-  for (int k = 0; k < kPartialSlots; ++k) {
-    double t = wave_sum(pv[k]);
-    if (lane == 0) red[wid][k] = t;
-  }
+    for (int k = 0; k < 6; ++k) pv[1 + k] = wave_total((double)acc.w[k] * w_scale);
+  // a wavefront's pairs: below 2^31 (64 lanes of < 2^24 candidates each)
+  pv[7] = (double)wave_total(cnt) * cnt_scale;
+  if (lane == 0)
+#pragma unroll
+    for (int k = 0; k < kPartialSlots; ++k) red[wid][k] = pv[k];
   __syncthreads();
   if (threadIdx.x < kPartialSlots) {
     double t = 0.0;
@@ -774,16 +820,18 @@ __device__ __forceinline__ void block_partials(const Acc<PREC> &acc, int64_t cnt
 // particles in the same slots give the same lanes in every kernel using it.
 // scratch: kPairBlock + (kPairBlock / 64) * (kRcBins + 1) ints of LDS, free
 // on entry and on return.  Returns the slot offset (0 .. kPairBlock - 1)
-// this lane takes.
+// this lane takes; with 2^split_log lanes to a particle, the workgroup's
+// kPairBlock >> split_log particles are ranked and the lanes of group k take
+// the particle of rank k.
 constexpr int kRcBins = 8;
 static_assert((kNearCap + 1) * kPairBlock >= kPairBlock + (kPairBlock / 64) * (kRcBins + 1),
               "the lane order borrows the close-pair queue's LDS");
 __device__ __forceinline__ int rc_lane_order(const double4 *pos, int64_t base, int64_t count,
-                                             double rc_bound, int32_t *scratch) {
+                                             int split_log, double rc_bound, int32_t *scratch) {
   constexpr int kKeys = kRcBins + 1;
   const int t = threadIdx.x, wave = t >> 6, lane = t & 63;
   int key = kRcBins;  // empty slot
-  if (t < count) {
+  if (t < count && t < (kPairBlock >> split_log)) {
     const double r = pos[base + t].w;
     const double q = rc_bound > 0.0 ? r * ((double)kRcBins / rc_bound) : 0.0;
     int b = q >= 0.0 ? (int)q : 0;  // NaN: bin 0
@@ -812,30 +860,41 @@ __device__ __forceinline__ int rc_lane_order(const double4 *pos, int64_t base, i
   const int rank = start[wave * kKeys + key] + __popcll(mine & ((1ull << lane) - 1ull));
   scratch[rank] = t;
   __syncthreads();
-  const int mine_t = scratch[t];
+  const int mine_t = scratch[t >> split_log];
   __syncthreads();
   return mine_t;
 }
 
 // Forces of the lane's particle to caller order (24 eps applied), its pair
 // count, and the block's deterministic partial sums E, W[6], pair count.
-template <int PREC>
+// The 2^split_log lanes of a particle first add up their shares (a fixed
+// butterfly, so every lane holds the same sum); the first of them writes.
+template <int PREC, int EVM>
 __device__ __forceinline__ void finish_block(const int32_t *perm, int64_t id0, double *fx,
                                              double *fy, double *fz, int32_t *nnbr, int64_t s,
-                                             bool active, double eps, const Acc<PREC> &acc,
-                                             int cnt, double (*red)[kPartialSlots],
-                                             uint32_t *status, double *partial_out) {
-  if (active) {
+                                             bool active, int split_log, double eps,
+                                             const Acc<PREC> &acc, int cnt,
+                                             double (*red)[kPartialSlots], uint32_t *status,
+                                             double *partial_out) {
+  double ax = acc.fx, ay = acc.fy, az = acc.fz;
+  int pc = cnt;
+  if (split_log > 0) {
+    dpp_add<kDppXor1>(ax, ay, az, pc);
+    if (split_log > 1) dpp_add<kDppXor2>(ax, ay, az, pc);
+    if (split_log > 2) dpp_add<kDppHalfMirror>(ax, ay, az, pc);
+    if (split_log > 3) dpp_add<kDppMirror>(ax, ay, az, pc);
+  }
+  if (active && (threadIdx.x & ((1u << split_log) - 1u)) == 0) {
     const double c24 = 24.0 * eps;
-    const double Fx = c24 * acc.fx, Fy = c24 * acc.fy, Fz = c24 * acc.fz;
+    const double Fx = c24 * ax, Fy = c24 * ay, Fz = c24 * az;
     const int64_t i = perm[s] - id0;
     fx[i] = Fx;
     fy[i] = Fy;
     fz[i] = Fz;
-    if (nnbr) nnbr[i] = cnt;
+    if (nnbr) nnbr[i] = pc;
     if (!finite3(Fx, Fy, Fz)) atomicOr(status, ST_NONFINITE_FORCE);
   }
-  block_partials<PREC>(acc, cnt, 2.0 * eps, 12.0 * eps, red, partial_out);
+  block_partials<PREC, EVM>(acc, cnt, 1.0, 2.0 * eps, 12.0 * eps, red, partial_out);
 }
 
 // One block of kPairBlock particles: sorted slot s for this lane (active if
@@ -874,6 +933,9 @@ __device__ __forceinline__ void pair_block(const PairView &v, int64_t s, bool ac
   g.cy = g.cz = 0;
   g.self = -1;
   g.slot = (int)s;
+  g.parts = 1 << v.split_log;
+  g.part = (int)threadIdx.x & (g.parts - 1);
+  g.skew = row_skew(v.split_log);
   if (active) {
     const double4 pi = v.pos[s];
     g.xi = pi.x;
@@ -977,7 +1039,8 @@ __device__ __forceinline__ void pair_block(const PairView &v, int64_t s, bool ac
   }
   if constexpr (walk_counts<REL, EVM>()) {
     if (v.walk) {  // the lane's own slot lies in its rows but is no candidate
-      const unsigned long long c = wave_sum_u64((unsigned long long)(wcand - (active ? 1 : 0)));
+      const unsigned long long c =
+          wave_sum_u64((unsigned long long)(int64_t)(wcand - (active && g.part == 0 ? 1 : 0)));
       const unsigned long long r = wave_sum_u64((unsigned long long)wrows);
       if ((threadIdx.x & 63) == 0) {
         atomicAdd(&v.walk[0], c);
@@ -995,10 +1058,10 @@ __device__ __forceinline__ void pair_block(const PairView &v, int64_t s, bool ac
       unsafeAtomicAdd(f + 2, acc.fz);
       if (v.n3_cnt) atomicAdd(&v.n3_cnt[s], cnt);
     }
-    block_partials<PREC>(acc, 2 * (int64_t)cnt, 4.0 * eps, 24.0 * eps, red, partial_out);
+    block_partials<PREC, EVM>(acc, cnt, 2.0, 4.0 * eps, 24.0 * eps, red, partial_out);
   } else {
-    finish_block<PREC>(v.perm, v.id0, v.fx, v.fy, v.fz, v.nnbr, s, active, eps, acc, cnt, red,
-                       status, partial_out);
+    finish_block<PREC, EVM>(v.perm, v.id0, v.fx, v.fy, v.fz, v.nnbr, s, active, v.split_log, eps,
+                            acc, cnt, red, status, partial_out);
   }
 }
 
@@ -1008,10 +1071,11 @@ __global__ __launch_bounds__(kPairBlock) void k_pair(PairArgs a) {
   __shared__ int32_t nearq[REL ? kNearCap + 1 : 1][kPairBlock];
   __shared__ double red[kPairBlock / 64][kPartialSlots];
   const int64_t lblock = xcd_block(blockIdx.x, gridDim.x, kXcdGroup);
-  int64_t s = lblock * kPairBlock + threadIdx.x;
-  if constexpr (REL)
-    s = lblock * kPairBlock + rc_lane_order(a.pos, lblock * kPairBlock,
-                                            a.n - lblock * kPairBlock, a.rc_bound, &nearq[0][0]);
+  int64_t s = (lblock * kPairBlock + threadIdx.x) >> a.split_log;
+  if constexpr (REL) {
+    const int64_t first = (lblock * kPairBlock) >> a.split_log;
+    s = first + rc_lane_order(a.pos, first, a.n - first, a.split_log, a.rc_bound, &nearq[0][0]);
+  }
   PairView v;
   v.pos = a.pos;
   v.cell_start = a.cell_start;
@@ -1034,6 +1098,7 @@ __global__ __launch_bounds__(kPairBlock) void k_pair(PairArgs a) {
   }
   v.rc_bound = a.rc_bound;
   v.rc_all_bits = &a.ctl->rc_max_bits;
+  v.split_log = a.split_log;
   v.fx = a.fx;
   v.fy = a.fy;
   v.fz = a.fz;
@@ -1055,7 +1120,9 @@ __global__ __launch_bounds__(kPairBlock) void k_pair_list(PairArgs a, const int3
                                                           const int32_t *wave_start,
                                                           const int32_t *list) {
   __shared__ double red[kPairBlock / 64][kPartialSlots];
-  const int64_t s = blockIdx.x * (int64_t)kPairBlock + threadIdx.x;
+  // lane t of the grid holds share t & (2^split_log - 1) of particle s
+  const int64_t t = blockIdx.x * (int64_t)kPairBlock + threadIdx.x;
+  const int64_t s = t >> a.split_log;
   const bool active = s < a.n;
   Acc<PREC> acc;
   int cnt = 0;
@@ -1067,7 +1134,7 @@ __global__ __launch_bounds__(kPairBlock) void k_pair_list(PairArgs a, const int3
     yi = pi.y;
     zi = pi.z;
     rci = pi.w;
-    len = count[s];
+    len = count[t];
   }
   const double rci2 = rci * rci, sig2 = a.sigma * a.sigma;
   int wmax = len;
@@ -1077,8 +1144,8 @@ __global__ __launch_bounds__(kPairBlock) void k_pair_list(PairArgs a, const int3
     wmax = o > wmax ? o : wmax;
   }
   // wavefronts past the last particle read the first list (their lanes are idle)
-  const int64_t w = (s >> 6) < ((a.n + 63) >> 6) ? (s >> 6) : 0;
-  const int32_t *mine = list + 64 * (int64_t)wave_start[w] + (s & 63);
+  const int64_t w = (t >> 6) < (((a.n << a.split_log) + 63) >> 6) ? (t >> 6) : 0;
+  const int32_t *mine = list + 64 * (int64_t)wave_start[w] + (t & 63);
   // two entries per trip, each loaded a trip ahead of its use
   int k = 0;
   int ja = 0 < len ? mine[0] : 0;
@@ -1095,8 +1162,8 @@ __global__ __launch_bounds__(kPairBlock) void k_pair_list(PairArgs a, const int3
     ja = jc;
     k += 2;
   }
-  finish_block<PREC>(a.perm, 0, a.fx, a.fy, a.fz, a.nnbr, s, active, a.eps, acc, cnt, red,
-                     a.status, a.partials + blockIdx.x * kPartialSlots);
+  finish_block<PREC, EVM>(a.perm, 0, a.fx, a.fy, a.fz, a.nnbr, s, active, a.split_log, a.eps, acc,
+                          cnt, red, a.status, a.partials + blockIdx.x * kPartialSlots);
 }
 
 template <int PREC>
@@ -1113,8 +1180,7 @@ static void launch_pair_list_ev(hipStream_t s, const PairArgs &a, const int32_t 
 
 void launch_pair_list(hipStream_t s, const PairArgs &a, int prec, const int32_t *count,
                       const int32_t *wave_start, const int32_t *list) {
-  const int64_t blocks = ceil_div(a.n, kPairBlock) > 0 ? ceil_div(a.n, kPairBlock) : 1;
-  dim3 g((unsigned)blocks), b(kPairBlock);
+  dim3 g((unsigned)pair_blocks(a.n, a.split_log)), b(kPairBlock);
   if (prec == DCM_FP64) launch_pair_list_ev<DCM_FP64>(s, a, count, wave_start, list, g, b);
   else launch_pair_list_ev<DCM_FP32_MIXED>(s, a, count, wave_start, list, g, b);
 }
@@ -1131,18 +1197,18 @@ __global__ __launch_bounds__(kPairBlock) void k_pair_batched(BatchPairArgs a) {
   __shared__ uint2 segs[CAP][kPairBlock];
   __shared__ int32_t nearq[REL ? kNearCap + 1 : 1][kPairBlock];
   __shared__ double red[kPairBlock / 64][kPartialSlots];
-  __shared__ int32_t next_item;
+  __shared__ int4 next_item;
   const double sig2 = a.sigma * a.sigma;
   const int home = a.nqueues > 1 ? (int)(blockIdx.x % (unsigned)a.nqueues) : 0;
   int tried = 0;  // segments found empty
   while (true) {
     if (threadIdx.x == 0) {
-      int32_t got = -1;
+      int4 got = make_int4(-1, 0, 0, 0);
       while (tried < a.nqueues) {
         const int q = (home + tried) % a.nqueues;
         const int32_t pos = a.qseg[q] + (int32_t)atomicAdd(&a.head[q], 1u);
         if (pos < a.qseg[q + 1]) {
-          got = pos;
+          got = a.queue[pos];
           break;
         }
         ++tried;
@@ -1150,13 +1216,12 @@ __global__ __launch_bounds__(kPairBlock) void k_pair_batched(BatchPairArgs a) {
       next_item = got;
     }
     __syncthreads();
-    const int32_t qi = next_item;
+    const int4 w = next_item;
     __syncthreads();
-    if (qi < 0) break;
-    const int32_t item = __builtin_amdgcn_readfirstlane(a.queue[qi]);
-    const int2 w = a.items[item];
+    if (w.x < 0) break;
     const int b = __builtin_amdgcn_readfirstlane(w.x);
     const int64_t first = __builtin_amdgcn_readfirstlane(w.y);
+    const int32_t item = __builtin_amdgcn_readfirstlane(w.z);
     const SysGeom &g = a.sys[b];
     PairView v;
     v.pos = a.pos;
@@ -1182,6 +1247,7 @@ __global__ __launch_bounds__(kPairBlock) void k_pair_batched(BatchPairArgs a) {
     }
     v.rc_bound = g.rc_cap;
     v.rc_all_bits = a.rc_max_bits + b;
+  v.split_log = g.split_log;
     v.fx = g.fx;
     v.fy = g.fy;
     v.fz = g.fz;
@@ -1189,9 +1255,10 @@ __global__ __launch_bounds__(kPairBlock) void k_pair_batched(BatchPairArgs a) {
     v.ext_src = nullptr;
     v.n3_f = nullptr;
     v.n3_cnt = nullptr;
-    int64_t local = first + threadIdx.x;
+    int64_t local = first + ((int64_t)threadIdx.x >> g.split_log);
     if constexpr (REL)
-      local = first + rc_lane_order(a.pos, g.p0 + first, g.n - first, g.rc_cap, &nearq[0][0]);
+      local = first + rc_lane_order(a.pos, g.p0 + first, g.n - first, g.split_log, g.rc_cap,
+                                    &nearq[0][0]);
     pair_block<RULE, PREC, EVM, REL, CAP>(v, g.p0 + local, local < g.n, a.eps, sig2, segs, nearq,
                                           red,
                                      a.status,
@@ -1216,8 +1283,7 @@ static void launch_pair_ev(hipStream_t s, const PairArgs &a, dim3 g, dim3 b, int
 }
 
 void launch_pair(hipStream_t s, const PairArgs &a, int rule, int prec) {
-  const int64_t blocks = ceil_div(a.n, kPairBlock) > 0 ? ceil_div(a.n, kPairBlock) : 1;
-  dim3 g((unsigned)blocks), b(kPairBlock);
+  dim3 g((unsigned)pair_blocks(a.n, a.split_log)), b(kPairBlock);
   const int evm = ev_mode(a.ev_flags, false);
   if (rule == DCM_PAIR_OWN) {
     if (prec == DCM_FP64) launch_pair_ev<DCM_PAIR_OWN, DCM_FP64, false>(s, a, g, b, evm);
