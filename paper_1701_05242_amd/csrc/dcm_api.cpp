@@ -465,27 +465,36 @@ namespace {
 // maps set: sources from the regularisation passes' bit-packed phase maps
 // (launch_fsm_init_bits) instead of the byte maps seg / iface.
 dcm_status sweep_enqueue(dcm_ctx *ctx, const uint8_t *seg, const uint8_t *iface,
-                         const dcm_grid &grid, int64_t nvox, double rc_grid, int32_t max_waves,
-                         double *dist, int32_t *waves_out, const uint32_t *const *maps = nullptr) {
+                         const dcm_grid &grid, int64_t nvox, bool tiled, double rc_grid,
+                         int32_t max_waves, double *dist, int32_t *waves_out,
+                         const uint32_t *const *maps = nullptr) {
   DCM_TRY(ensure(ctx, ctx->dA, nvox * sizeof(double)));
   DCM_TRY(ensure(ctx, ctx->dB, nvox * sizeof(double)));
-  const int64_t ntiles = fsm_tile_count(grid.n);
-  DCM_TRY(ensure(ctx, ctx->fsm_chg, 2 * ntiles));
-  uint8_t *chg0 = ptr<uint8_t>(ctx->fsm_chg), *chg1 = chg0 + ntiles;
-  DCM_TRY(ensure(ctx, ctx->fsm_flags, (size_t)(max_waves + 2) * sizeof(uint32_t)));
+  DCM_TRY(ensure(ctx, ctx->fsm_chg, fsm_tile_bytes(grid.n)));
+  void *tiles = ctx->fsm_chg.p;
+  DCM_TRY(ensure(ctx, ctx->fsm_flags, fsm_flag_words(max_waves) * sizeof(uint32_t)));
   uint32_t *flags = ptr<uint32_t>(ctx->fsm_flags);
   hipStream_t s = ctx->stream;
   hipEvent_t ev;
   timer_begin(ctx, "sweep", &ev);
   if (maps)
-    launch_fsm_init_bits(s, maps, ctx->ctl, grid.n, ptr<double>(ctx->dA), ptr<double>(ctx->dB),
-                         chg0, flags, max_waves);
+    launch_fsm_init_bits(s, maps, ctx->ctl, grid.n, tiled, ptr<double>(ctx->dA),
+                         ptr<double>(ctx->dB), tiles, flags, max_waves);
   else
-    launch_fsm_init(s, seg, iface, grid.n, ptr<double>(ctx->dA), ptr<double>(ctx->dB), chg0,
-                    flags, max_waves);
-  for (int w = 1; w <= max_waves; ++w)
-    launch_fsm_step(s, ptr<double>(ctx->dA), ptr<double>(ctx->dB), chg0, chg1, grid.n, grid.h,
-                    rc_grid, w, flags);
+    launch_fsm_init(s, seg, iface, grid.n, tiled, ptr<double>(ctx->dA), ptr<double>(ctx->dB),
+                    tiles, flags, max_waves);
+  // 14 passes serve the interfaces met in earnest with rc_grid of 8 voxels;
+  // those beyond share one launch, which one workgroup runs if the sweep has
+  // not ended by then (few tiles still change that late)
+  const double hmin = std::min(grid.h[0], std::min(grid.h[1], grid.h[2]));
+  const double enough = 6.0 + std::ceil(rc_grid / hmin);
+  const int own = tiled && enough < (double)max_waves ? (int)enough : max_waves;
+  auto passes = [&](int from, int to) {
+    launch_fsm_step(s, ptr<double>(ctx->dA), ptr<double>(ctx->dB), tiles, grid.n, tiled,
+                    maps == nullptr, grid.h, rc_grid, from, to, flags, max_waves);
+  };
+  for (int w = 1; w <= own; ++w) passes(w, w);
+  if (own < max_waves) passes(own + 1, max_waves);
   if (dist)
     launch_fsm_final(s, ptr<double>(ctx->dA), ptr<double>(ctx->dB), nvox, rc_grid, flags,
                      max_waves, dist, waves_out, ctx->d_status);
@@ -505,7 +514,8 @@ dcm_status dcm_sweep_distance(dcm_ctx *ctx, const uint8_t *seg, const uint8_t *i
   if (max_waves < 1 || max_waves > 100000)
     return fail(ctx, DCM_ERR_INVALID, "max_waves must be in [1, 100000]");
   ctx->have_field = false;  // dcm_step's field lives in the sweep buffers this call reuses
-  return sweep_enqueue(ctx, seg, iface, grid, nvox, rc_grid, max_waves, dist, waves_out);
+  return sweep_enqueue(ctx, seg, iface, grid, nvox, fsm_tiled(grid.n), rc_grid, max_waves, dist,
+                       waves_out);
 }
 
 dcm_status dcm_assign_cutoffs(dcm_ctx *ctx, const double *x, const double *y, const double *z,
@@ -1124,13 +1134,9 @@ dcm_status dcm_step(dcm_ctx *ctx, double *x, double *y, double *z, double *vx, d
     launch_permute_scatter(s, f, owner(cur), n);
     return check_launch(ctx, "dcm_step");
   };
-  // sweep passes stop early once one changes nothing; the cap only bounds
-  // the launches.  A tiled pass settles whole 16x8x8 tiles, so a front
-  // crosses at least a tile per pass; a plain pass advances one voxel.
-  double hmin = std::min(grid.h[0], std::min(grid.h[1], grid.h[2]));
-  int32_t max_waves = fsm_tiled(grid.n)
-                          ? std::max<int32_t>(12, (int32_t)std::ceil(2.0 * rc_grid / (8.0 * hmin)) + 8)
-                          : std::max<int32_t>(64, (int32_t)std::ceil(4.0 * rc_grid / hmin) + 8);
+  // sweep passes stop early once one changes nothing; the limit only bounds
+  // them (those past the first few dozen share one launch)
+  const int32_t max_waves = 1024;
   double *scal = ptr<double>(ctx->scalars);
   const dcm_detect_opts dopts = {0.0, -1.0, 0};
   // the cell build beside the sweep (set below; a no-op where it does not apply)
@@ -1148,8 +1154,8 @@ dcm_status dcm_step(dcm_ctx *ctx, double *x, double *y, double *z, double *vx, d
     binned = false;
     const uint32_t *const maps[2] = {sc.seg_a, sc.seg_b};
     if (build_beside) DCM_TRY(build_beside());
-    DCM_TRY(sweep_enqueue(ctx, nullptr, nullptr, grid, nvox, rc_grid, max_waves, nullptr, nullptr,
-                          maps));
+    DCM_TRY(sweep_enqueue(ctx, nullptr, nullptr, grid, nvox, true, rc_grid, max_waves, nullptr,
+                          nullptr, maps));
     ctx->have_field = true;
     ctx->field_waves = max_waves;
     for (int a = 0; a < 3; ++a) {

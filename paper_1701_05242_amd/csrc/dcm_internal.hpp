@@ -288,21 +288,31 @@ void launch_interface(hipStream_t s, const uint32_t *buf0, const uint32_t *buf1,
                       const int32_t nv[3], const Ctl *ctl, uint8_t *seg, uint8_t *iface);
 
 // k_fsm.hip
-// initial distances; with tiles also the first pass's tile flags in chg0
-// the same from the regularisation passes' two bit-packed phase maps (the
-// final one chosen from the pass flags, as launch_interface does)
-void launch_fsm_init_bits(hipStream_t s, const uint32_t *const maps[2], const Ctl *ctl,
-                          const int32_t nv[3], double *dA, double *dB, uint8_t *chg0,
-                          uint32_t *flags, int max_steps);
+// The sweep's scratch: fsm_tile_bytes for its tiles, fsm_flag_words(max_steps)
+// words of pass flags and counts.
+int64_t fsm_tile_bytes(const int32_t nv[3]);
+int64_t fsm_flag_words(int max_steps);
+// initial distances and cleared flags; tiled: also the tiles' flags.  The
+// second form takes its sources from the regularisation passes' two bit-packed
+// phase maps (the final one chosen from the pass flags, as launch_interface
+// does).
 void launch_fsm_init(hipStream_t s, const uint8_t *seg, const uint8_t *iface, const int32_t nv[3],
-                     double *dA, double *dB, uint8_t *chg0, uint32_t *flags, int max_steps);
-// one launch of the sweep: a temporally blocked tile pass when fsm_tiled(nv),
-// else one synchronous wave; chg0/chg1 hold one flag per tile
+                     bool tiled, double *dA, double *dB, void *tiles, uint32_t *flags,
+                     int max_steps);
+void launch_fsm_init_bits(hipStream_t s, const uint32_t *const maps[2], const Ctl *ctl,
+                          const int32_t nv[3], bool tiled, double *dA, double *dB, void *tiles,
+                          uint32_t *flags, int max_steps);
+// passes step .. last of the sweep in one launch (last > step only with
+// tiled: one workgroup runs them in turn): temporally blocked tile passes, or
+// (tiled false, last = step) one synchronous wave.  settle: every pass runs
+// its tiles until they have settled (fewer, longer passes).  Tiles serve any
+// grid; dcm_sweep_distance, whose caller counts and bounds its waves, takes
+// settled passes where fsm_tiled(nv).
 bool fsm_tiled(const int32_t nv[3]);
 int64_t fsm_tile_count(const int32_t nv[3]);
-void launch_fsm_step(hipStream_t s, double *dA, double *dB, uint8_t *chg0, uint8_t *chg1,
-                     const int32_t nv[3], const double h[3], double rc_grid, int step,
-                     uint32_t *flags);
+void launch_fsm_step(hipStream_t s, double *dA, double *dB, void *tiles, const int32_t nv[3],
+                     bool tiled, bool settle, const double h[3], double rc_grid, int step,
+                     int last, uint32_t *flags, int max_steps);
 void launch_fsm_final(hipStream_t s, const double *dA, const double *dB, int64_t nvox,
                       double rc_grid, const uint32_t *flags, int max_steps, double *dist,
                       int32_t *waves_out, uint32_t *status);
