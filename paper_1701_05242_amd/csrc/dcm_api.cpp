@@ -50,6 +50,14 @@ dcm_status ensure(dcm_ctx *ctx, DevBuf &b, size_t bytes) {
   return DCM_OK;
 }
 
+dcm_status ensure_zeroed(dcm_ctx *ctx, DevBuf &b, size_t bytes) {
+  const size_t before = b.cap;
+  const dcm_status st = ensure(ctx, b, bytes);
+  if (st == DCM_OK && b.cap != before)
+    launch_fill_u32(ctx->stream, static_cast<uint32_t *>(b.p), 0u, (int64_t)(b.cap / 4));
+  return st;
+}
+
 dcm_status check_launch(dcm_ctx *ctx, const char *what) {
   hipError_t e = hipGetLastError();
   if (e != hipSuccess)
@@ -147,6 +155,11 @@ namespace {
 template <typename T>
 T *ptr(const DevBuf &b) {
   return static_cast<T *>(b.p);
+}
+
+// the ghost-extended count that the last complete build left in pinned memory
+int64_t ext_total(const dcm_ctx *ctx) {
+  return *static_cast<volatile int32_t *>(ctx->h_ext_total);
 }
 
 bool finite_pos(double v) { return std::isfinite(v) && v > 0.0; }
@@ -600,8 +613,8 @@ dcm_status dcm_build_cells(dcm_ctx *ctx, const double *x, const double *y, const
     ncell *= nc[a];
   }
   if (ncell >= (int64_t(1) << 30)) return fail(ctx, DCM_ERR_RANGE, "too many cells");
-  DCM_TRY(ensure(ctx, ctx->cell_count, ncell * sizeof(int32_t)));
-  DCM_TRY(ensure(ctx, ctx->cell_fill, ncell * sizeof(int32_t)));
+  DCM_TRY(ensure_zeroed(ctx, ctx->cell_count, ncell * sizeof(int32_t)));
+  DCM_TRY(ensure(ctx, ctx->cell_slot, std::max<int64_t>(n, 1) * sizeof(int32_t)));
   DCM_TRY(ensure(ctx, ctx->cell_start, (ncell + 1) * sizeof(int32_t)));
   DCM_TRY(ensure(ctx, ctx->scan_tmp, scan_tmp_elems(ncell) * sizeof(int32_t)));
   if (n >= (int64_t(1) << 24))
@@ -654,7 +667,7 @@ dcm_status dcm_build_cells(dcm_ctx *ctx, const double *x, const double *y, const
     if (hipEventSynchronize(ctx->ext_event) != hipSuccess)
       return fail(ctx, DCM_ERR_HIP, "dcm_build_cells: ghost count read-back failed");
     ctx->ext_copy_pending = false;
-    ctx->ext_exact = *ctx->h_ext_total;
+    ctx->ext_exact = ext_total(ctx);
   }
   const double max_need = hard * (double)n + 64.0;  // the most any arrangement needs
   const bool known = same_geom && ctx->ext_exact >= 0 && !ctx->ext_copy_pending;
@@ -690,36 +703,47 @@ dcm_status dcm_build_cells(dcm_ctx *ctx, const double *x, const double *y, const
   hipStream_t s = ctx->stream;
   hipEvent_t ev;
   timer_begin(ctx, "cells", &ev);
-  launch_zero2_i32(s, ptr<int32_t>(ctx->cell_count), ptr<int32_t>(ctx->cell_fill), ncell);
   const double *rc_in = no_rc ? nullptr : rc;
-  launch_cell_count(s, x, y, z, rc_in, n, box.L, nc, sc, rc_cap, cof, ptr<int32_t>(ctx->cell_count),
-                    ptr<unsigned long long>(ctx->rcmax_part), ptr<uint32_t>(ctx->xkey), ctx->ctl,
-                    ctx->d_status);
-  launch_exclusive_scan(s, ptr<int32_t>(ctx->cell_count), ptr<int32_t>(ctx->cell_start), ncell,
-                        ptr<int32_t>(ctx->scan_tmp));
-  // the scatter's order (arbitrary within a cell) goes to sort_tmp; the sort
-  // writes the final order into perm and the sorted copy beside it
-  launch_cell_scatter(s, cof, n, ptr<int32_t>(ctx->cell_start), ptr<int32_t>(ctx->cell_fill),
-                      ptr<int32_t>(ctx->sort_tmp), ptr<uint32_t>(ctx->xkey),
-                      ptr<uint32_t>(ctx->skey));
-  const GatherOut go = {x, y, z, rc_in, {box.L[0], box.L[1], box.L[2]}, rc_cap,
-                        ptr<double4>(ctx->sorted)};
-  launch_cell_sort(s, ptr<int32_t>(ctx->cell_start), ncell, cof, n, ptr<int32_t>(ctx->sort_tmp),
-                   ptr<uint32_t>(ctx->xkey), ptr<uint32_t>(ctx->skey),
-                   qtab ? ptr<uint32_t>(ctx->qword) : nullptr, ptr<int32_t>(ctx->perm),
-                   ptr<int32_t>(ctx->sort_list), &ctx->ctl->big_cells, &go);
-  launch_ext_count(s, ptr<int32_t>(ctx->cell_start), nc, halo, box.L,
-                   ptr<int32_t>(ctx->ext_row_count), ptr<int32_t>(ctx->ext_row_start),
-                   ptr<int32_t>(ctx->ext_row_lo), ptr<int32_t>(ctx->ext_start),
-                   ptr<int32_t>(ctx->scan_tmp), qtab ? ptr<uint32_t>(ctx->qword) : nullptr,
-                   qtab ? ptr<int2>(ctx->ext_sq) : nullptr);
+  launch_cell_count(s, x, y, z, rc_in, n, box.L, nc, sc, rc_cap, cof, ptr<int32_t>(ctx->cell_slot),
+                    ptr<int32_t>(ctx->cell_count), ptr<unsigned long long>(ctx->rcmax_part),
+                    ptr<uint32_t>(ctx->xkey), ctx->ctl, ctx->d_status);
+  launch_cell_scan(s, ptr<int32_t>(ctx->cell_count), ptr<int32_t>(ctx->cell_start), ncell,
+                   qtab ? ptr<uint32_t>(ctx->qword) : nullptr, ptr<int32_t>(ctx->scan_tmp));
+  CellOrder o;
+  o.n = n;
+  for (int a = 0; a < 3; ++a) {
+    o.nc[a] = nc[a];
+    o.h[a] = halo[a];
+    o.L[a] = box.L[a];
+  }
+  o.cell_start = ptr<int32_t>(ctx->cell_start);
+  o.cell_of = cof;
+  o.slot = ptr<int32_t>(ctx->cell_slot);
+  o.xq = ptr<uint32_t>(ctx->xkey);
+  o.skey = ptr<uint32_t>(ctx->skey);
+  o.qword = qtab ? ptr<uint32_t>(ctx->qword) : nullptr;
+  o.scratch = ptr<int32_t>(ctx->sort_tmp);
+  o.perm = ptr<int32_t>(ctx->perm);
+  o.big_list = ptr<int32_t>(ctx->sort_list);
+  o.big_count = &ctx->ctl->big_cells;
+  o.block_max = ptr<unsigned long long>(ctx->rcmax_part);
+  o.ctl = ctx->ctl;
+  o.go = {x, y, z, rc_in, {box.L[0], box.L[1], box.L[2]}, rc_cap, ptr<double4>(ctx->sorted)};
+  o.row_count = ptr<int32_t>(ctx->ext_row_count);
+  o.row_start = ptr<int32_t>(ctx->ext_row_start);
+  o.row_lo = ptr<int32_t>(ctx->ext_row_lo);
+  o.scan_tmp = ptr<int32_t>(ctx->scan_tmp);
+  o.ext_start = ptr<int32_t>(ctx->ext_start);
+  o.ext_sq = qtab ? ptr<int2>(ctx->ext_sq) : nullptr;
+  // (a stream being captured does not write the host's count: its replays
+  // would change it behind later builds)
+  o.host_total = capturing ? nullptr : ctx->h_ext_total;
+  launch_cell_order(s, o);
   if (!known && !capturing) {
     // a new geometry: this build's exact count sizes the buffers
-    if (hipMemcpyAsync(ctx->h_ext_total, ptr<int32_t>(ctx->ext_start) + next, sizeof(int32_t),
-                       hipMemcpyDeviceToHost, s) != hipSuccess ||
-        hipStreamSynchronize(s) != hipSuccess)
+    if (hipStreamSynchronize(s) != hipSuccess)
       return fail(ctx, DCM_ERR_HIP, "dcm_build_cells: ghost count read-back failed");
-    ctx->ext_exact = *ctx->h_ext_total;
+    ctx->ext_exact = ext_total(ctx);
     sizes((double)ctx->ext_exact, &need, &want);
   }
   if (!capturing && ctx->ext_exact > kMaxExtSlots)
@@ -735,9 +759,7 @@ dcm_status dcm_build_cells(dcm_ctx *ctx, const double *x, const double *y, const
   // exact ghost-extended count, read by the next build of this geometry
   std::copy(key, key + 7, ctx->ext_key);
   if (!capturing) {
-    if (hipMemcpyAsync(ctx->h_ext_total, ptr<int32_t>(ctx->ext_start) + next, sizeof(int32_t),
-                       hipMemcpyDeviceToHost, s) != hipSuccess ||
-        hipEventRecord(ctx->ext_event, s) != hipSuccess)
+    if (hipEventRecord(ctx->ext_event, s) != hipSuccess)
       return fail(ctx, DCM_ERR_HIP, "dcm_build_cells: ghost count read-back failed");
     ctx->ext_copy_pending = true;
   }

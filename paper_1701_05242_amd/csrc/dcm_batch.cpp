@@ -54,7 +54,7 @@ struct BatchState {
          table_bytes = 0;
   std::vector<unsigned char> table_host;
   // device memory
-  DevBuf tables, cell_of, cell_count, cell_fill, cell_start, perm, sorted, scan_tmp, row_count,
+  DevBuf tables, cell_of, cell_count, cell_slot, cell_start, perm, sorted, scan_tmp, row_count,
       row_start, row_lo, ext_start, ext_pos, ext_rel, partials, rcmax, rcmax_part, head,
       sort_tmp, sort_list, xkey, skey, qword, ext_sq;
   // recorded graph
@@ -274,8 +274,10 @@ dcm_status make_plan(dcm_ctx *ctx, BatchState &B, double edge, int queues, dcm_l
   if ((st = ensure(ctx, B.tables, B.table_bytes)) != DCM_OK) return st;
   if ((st = ensure(ctx, B.cell_of, sizeof(int32_t) * std::max<int64_t>(B.n_total, 1))) != DCM_OK)
     return st;
-  if ((st = ensure(ctx, B.cell_count, sizeof(int32_t) * B.cells_total)) != DCM_OK) return st;
-  if ((st = ensure(ctx, B.cell_fill, sizeof(int32_t) * B.cells_total)) != DCM_OK) return st;
+  if ((st = ensure_zeroed(ctx, B.cell_count, sizeof(int32_t) * B.cells_total)) != DCM_OK)
+    return st;
+  if ((st = ensure(ctx, B.cell_slot, sizeof(int32_t) * std::max<int64_t>(B.n_total, 1))) != DCM_OK)
+    return st;
   if ((st = ensure(ctx, B.cell_start, sizeof(int32_t) * (B.cells_total + 1))) != DCM_OK) return st;
   if ((st = ensure(ctx, B.sort_tmp, sizeof(int32_t) * std::max<int64_t>(B.n_total, 1))) != DCM_OK)
     return st;
@@ -329,36 +331,48 @@ void enqueue(dcm_ctx *ctx, BatchState &B, hipStream_t s, dcm_lj lj, int rule, in
              int ev_flags, bool timed) {
   const int32_t nsys = (int32_t)B.desc.size();
   const SysGeom *geo = dptr<SysGeom>(B.tables, B.off_geo);
-  const int2 *items = dptr<int2>(B.tables, B.off_items);
-  const int2 *eblk = dptr<int2>(B.tables, B.off_eblk);
-  const int64_t nitems = (int64_t)B.items.size();
   // FP32-mixed own-cutoff forces read the compact records
   float4 *rel = compact_records(B, lj, rule, prec) ? dptr<float4>(B.ext_rel) : nullptr;
   hipEvent_t ev = nullptr;
   if (timed) timer_begin(ctx, "batch_cells", &ev);
-  launch_zero2_i32(s, dptr<int32_t>(B.cell_count), dptr<int32_t>(B.cell_fill), B.cells_total);
-  launch_fill_u32(s, dptr<uint32_t>(B.head), 0u, kBatchQueues + 1);
-  launch_batch_cell_count(s, geo, nsys, items, nitems, dptr<int32_t>(B.cell_of),
-                          dptr<int32_t>(B.cell_count), dptr<unsigned long long>(B.rcmax_part),
-                          dptr<unsigned long long>(B.rcmax), dptr<uint32_t>(B.xkey),
-                          ctx->d_status);
-  launch_exclusive_scan(s, dptr<int32_t>(B.cell_count), dptr<int32_t>(B.cell_start),
-                        B.cells_total, dptr<int32_t>(B.scan_tmp));
-  launch_batch_cell_scatter(s, geo, items, nitems, dptr<int32_t>(B.cell_of),
-                            dptr<int32_t>(B.cell_start), dptr<int32_t>(B.cell_fill),
-                            dptr<int32_t>(B.perm), dptr<uint32_t>(B.xkey), dptr<uint32_t>(B.skey));
-  launch_cell_sort(s, dptr<int32_t>(B.cell_start), B.cells_total, dptr<int32_t>(B.cell_of),
-                   B.n_total, dptr<int32_t>(B.perm), dptr<uint32_t>(B.xkey),
-                   dptr<uint32_t>(B.skey), dptr<uint32_t>(B.qword), dptr<int32_t>(B.sort_tmp),
-                   dptr<int32_t>(B.sort_list), dptr<uint32_t>(B.head) + kBatchQueues);
-  launch_batch_gather(s, geo, items, nitems, dptr<int32_t>(B.sort_tmp), dptr<double4>(B.sorted),
-                      dptr<int32_t>(B.perm));
-  launch_batch_ext(s, geo, eblk, (int64_t)B.eblk.size(), dptr<int2>(B.tables, B.off_rblk),
-                   (int64_t)B.rblk.size(), dptr<int32_t>(B.cell_start), dptr<double4>(B.sorted),
-                   B.ext_cells_total, B.ext_rows_total, B.ext_cap, dptr<int32_t>(B.row_count),
-                   dptr<int32_t>(B.row_start), dptr<int32_t>(B.row_lo), dptr<int32_t>(B.ext_start),
-                   dptr<int32_t>(B.scan_tmp), dptr<double4>(B.ext_pos), rel,
-                   dptr<uint32_t>(B.qword), dptr<int2>(B.ext_sq), ctx->d_status);
+  BatchCells c;
+  c.sys = geo;
+  c.nsys = nsys;
+  c.pblk = dptr<int2>(B.tables, B.off_items);
+  c.rblk = dptr<int2>(B.tables, B.off_rblk);
+  c.eblk = dptr<int2>(B.tables, B.off_eblk);
+  c.npblk = (int64_t)B.items.size();
+  c.nrblk = (int64_t)B.rblk.size();
+  c.neblk = (int64_t)B.eblk.size();
+  c.cells_total = B.cells_total;
+  c.next_total = B.ext_cells_total;
+  c.nrows_total = B.ext_rows_total;
+  c.ext_cap = B.ext_cap;
+  c.cell_of = dptr<int32_t>(B.cell_of);
+  c.slot = dptr<int32_t>(B.cell_slot);
+  c.cell_count = dptr<int32_t>(B.cell_count);
+  c.cell_start = dptr<int32_t>(B.cell_start);
+  c.scratch = dptr<int32_t>(B.sort_tmp);
+  c.perm = dptr<int32_t>(B.perm);
+  c.big_list = dptr<int32_t>(B.sort_list);
+  c.xq = dptr<uint32_t>(B.xkey);
+  c.skey = dptr<uint32_t>(B.skey);
+  c.qword = dptr<uint32_t>(B.qword);
+  c.head = dptr<uint32_t>(B.head);
+  c.nhead = kBatchQueues + 1;
+  c.block_max = dptr<unsigned long long>(B.rcmax_part);
+  c.rc_max_bits = rule == DCM_PAIR_MAX ? dptr<unsigned long long>(B.rcmax) : nullptr;
+  c.sorted = dptr<double4>(B.sorted);
+  c.row_count = dptr<int32_t>(B.row_count);
+  c.row_start = dptr<int32_t>(B.row_start);
+  c.row_lo = dptr<int32_t>(B.row_lo);
+  c.scan_tmp = dptr<int32_t>(B.scan_tmp);
+  c.ext_start = dptr<int32_t>(B.ext_start);
+  c.ext_sq = dptr<int2>(B.ext_sq);
+  c.ext_pos = dptr<double4>(B.ext_pos);
+  c.ext_rel = rel;
+  c.status = ctx->d_status;
+  launch_batch_cells(s, c);
   if (timed) timer_end(ctx, "batch_cells", ev);
   BatchPairArgs a;
   a.sys = geo;

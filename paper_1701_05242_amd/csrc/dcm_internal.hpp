@@ -150,7 +150,7 @@ struct dcm_ctx {
   dcm::DevBuf delta, rc, partials, ke, scalars;
   dcm::DevBuf tune_f;  // forces of the cell-edge tuner's trial passes (dcm_build_cells)
   // cells
-  dcm::DevBuf cell_of, cell_count, cell_start, cell_fill, perm, sorted, scan_tmp, rcmax_part;
+  dcm::DevBuf cell_of, cell_count, cell_start, cell_slot, perm, sorted, scan_tmp, rcmax_part;
   // x key of every particle (within-cell order), sub-cell word of every real
   // cell and (start, sub-cell word) of every extended cell (the pair walk's
   // x trimming)
@@ -166,7 +166,7 @@ struct dcm_ctx {
   dcm::DevBuf n3_f, n3_cnt;  // Newton's-third-law forces and counts in sorted order
   int64_t ext_cap = 0;             // particles ext_pos can hold
   int32_t *h_ext_total = nullptr;  // pinned: ghost-extended count of the last build
-  // the copy into h_ext_total completes with ext_event; the count is kept for
+  // (complete with ext_event; the build's last scan writes it); it is kept for
   // the next build of the same cell geometry (ext_key: cells, halo, n)
   hipEvent_t ext_event = nullptr;
   bool ext_copy_pending = false;
@@ -243,6 +243,8 @@ dcm_status noalloc_scratch_setup(int device, std::string *err);
 // ---- context helpers (dcm_api.cpp)
 dcm_status fail(dcm_ctx *ctx, dcm_status code, const std::string &msg);
 dcm_status ensure(dcm_ctx *ctx, DevBuf &b, size_t bytes);
+// a buffer of counters that its users leave zeroed: cleared when it is new
+dcm_status ensure_zeroed(dcm_ctx *ctx, DevBuf &b, size_t bytes);
 dcm_status check_launch(dcm_ctx *ctx, const char *what);
 void timer_begin(dcm_ctx *ctx, const char *family, hipEvent_t *ev);
 void timer_end(dcm_ctx *ctx, const char *family, hipEvent_t ev);
@@ -254,8 +256,6 @@ inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 // k_common.hip
 void launch_fill_u32(hipStream_t s, uint32_t *p, uint32_t v, int64_t n);
 void launch_fill_i32(hipStream_t s, int32_t *p, int32_t v, int64_t n);
-// p[0..n) = q[0..n) = 0 in one launch
-void launch_zero2_i32(hipStream_t s, int32_t *p, int32_t *q, int64_t n);
 // p[0..np) = 0 and q[0..nq) = 0 in one launch
 void launch_zero2_u32(hipStream_t s, uint32_t *p, int64_t np, uint32_t *q, int64_t nq);
 void launch_reset_ctl(hipStream_t s, Ctl *ctl);
@@ -336,49 +336,59 @@ void launch_assign_cutoffs(hipStream_t s, const double *x, const double *y, cons
                            double *delta, double *rc);
 // workgroups of the cell-count kernel: the size of its block_max scratch
 int64_t cell_count_blocks(int64_t n);
+// slot[i]: the particle's slot in its cell (arbitrary within it); cell_count
+// must be zero on entry, and ctl->big_cells is zeroed
 void launch_cell_count(hipStream_t s, const double *x, const double *y, const double *z,
                        const double *rc, int64_t n, const double L[3], const int32_t nc[3],
-                       const double sc[3], double rc_cap, int32_t *cell_of, int32_t *cell_count,
-                       unsigned long long *block_max, uint32_t *xq, Ctl *ctl, uint32_t *status);
+                       const double sc[3], double rc_cap, int32_t *cell_of, int32_t *slot,
+                       int32_t *cell_count, unsigned long long *block_max, uint32_t *xq, Ctl *ctl,
+                       uint32_t *status);
 void launch_exclusive_scan(hipStream_t s, const int32_t *in, int32_t *out, int64_t n,
                            int32_t *tmp);
+// cell starts from the counts, which are zeroed for the next build, as are
+// the sub-cell words (qword, null: none)
+void launch_cell_scan(hipStream_t s, int32_t *cell_count, int32_t *cell_start, int64_t ncell,
+                      uint32_t *qword, int32_t *tmp);
 int64_t scan_tmp_elems(int64_t n);
-// perm[slot] = id and skey[slot] = xq[id] for every particle's slot in its cell
-void launch_cell_scatter(hipStream_t s, const int32_t *cell_of, int64_t n,
-                         const int32_t *cell_start, int32_t *cell_fill, int32_t *perm,
-                         const uint32_t *xq, uint32_t *skey);
-// The sorted copy written by the cell sort itself (launch_cell_sort with go
-// not null): sorted[slot] = (x, y, z, rc) of the particle sorted_perm[slot],
-// positions wrapped into the box (0 when not finite), rc clamped to
-// [0, rc_cap] (NaN -> 0).
+// The sorted copy, written with the order: sorted[slot] = (x, y, z, rc) of the
+// particle perm[slot], positions wrapped into the box (0 when not finite), rc
+// clamped to [0, rc_cap] (NaN -> 0).
 struct GatherOut {
   const double *x, *y, *z, *rc;
   double L[3];
   double rc_cap;
   double4 *sorted;
 };
-// sorted_perm receives the entries of perm (particle ids in cell order, cell
-// c of particle id holding cell_of[id], x keys xq by id and skey by slot)
-// with each cell's sorted by (x key, id); perm is left as scratch.  qword (null: none) receives the
-// cells' sub-cell words (sub_word: prefix counts of each cell's eighths
-// along x, 0 for cells of more than 15).  big_list holds
-// cell_sort_list_elems(n) entries; big_count must be 0 on entry.
-void launch_cell_sort(hipStream_t s, const int32_t *cell_start, int64_t ncell,
-                      const int32_t *cell_of, int64_t n, int32_t *perm, const uint32_t *xq,
-                      const uint32_t *skey, uint32_t *qword, int32_t *sorted_perm,
-                      int32_t *big_list, uint32_t *big_count, const GatherOut *go = nullptr);
 int64_t cell_sort_list_elems(int64_t n);
 // rows of the extended grid + 1: the size of each per-row scratch array
 int64_t ext_row_scratch_elems(const int32_t nc[3], const int32_t h[3]);
-// ghost-extended cells in two parts: the per-row tables and the extended
-// cell starts (ext_start[next] then holds the extended particle count), and
-// the images themselves into buffers of ext_cap slots.  ext_sq (null: none;
-// int2 [next + 1]) receives (ext_start, sub-cell word of the real cell) of
-// every extended cell and (extended count, 0) past the last.
-void launch_ext_count(hipStream_t s, const int32_t *cell_start, const int32_t nc[3],
-                      const int32_t h[3], const double L[3], int32_t *row_count,
-                      int32_t *row_start, int32_t *row_lo, int32_t *ext_start,
-                      int32_t *scan_tmp, const uint32_t *qword, int2 *ext_sq);
+// From cells and slots to the final order, in three launches (four when the
+// extended rows are very many): the particles in slot order (scratch, skey)
+// and the extended rows' counts; perm (ids in cell order, each cell's sorted
+// by (x key, id)), the sorted copy and the cells' sub-cell words (qword, null:
+// none; prefix counts of each cell's eighths along x, 0 for cells of more than
+// 15); the extended cell starts (ext_start[next] = the extended particle count,
+// also to host_total if not null; ext_sq, null: none, int2 [next + 1]: (start,
+// sub-cell word) of every extended cell and (extended count, 0) past the last)
+// and the cells too large to rank.  big_list holds cell_sort_list_elems(n)
+// entries; big_count must be 0 on entry.
+struct CellOrder {
+  int64_t n;
+  int32_t nc[3], h[3];
+  double L[3];
+  const int32_t *cell_start, *cell_of, *slot;
+  const uint32_t *xq;
+  uint32_t *skey, *qword;
+  int32_t *scratch, *perm, *big_list;
+  uint32_t *big_count;
+  GatherOut go;
+  int32_t *row_count, *row_start, *row_lo, *scan_tmp, *ext_start;
+  int2 *ext_sq;
+  int32_t *host_total;
+  const unsigned long long *block_max;  // the count's maxima: their largest to ctl->rc_max_bits
+  Ctl *ctl;
+};
+void launch_cell_order(hipStream_t s, const CellOrder &o);
 void launch_ext_images(hipStream_t s, const int32_t *cell_start, const int32_t *row_start,
                        const int32_t *row_lo, const double4 *sorted, const int32_t nc[3],
                        const int32_t h[3], const double L[3], int64_t ext_cap, double4 *ext_pos,
@@ -542,25 +552,30 @@ void launch_pair_batched(hipStream_t s, const BatchPairArgs &a, int rule, int pr
                          int row_lists);
 int batched_row_lists(int k);
 
-// k_batch.hip: build kernels of the batched form.  pblk holds one (system,
-// first local particle) entry per block of 256 particles, eblk one (system,
-// first local extended cell) entry per block of 256 extended cells.
-void launch_batch_cell_count(hipStream_t s, const SysGeom *sys, int32_t nsys, const int2 *pblk,
-                             int64_t npblk, int32_t *cell_of, int32_t *cell_count,
-                             unsigned long long *block_max, unsigned long long *rc_max_bits,
-                             uint32_t *xq, uint32_t *status);
-void launch_batch_cell_scatter(hipStream_t s, const SysGeom *sys, const int2 *pblk,
-                               int64_t npblk, const int32_t *cell_of, const int32_t *cell_start,
-                               int32_t *cell_fill, int32_t *perm, const uint32_t *xq,
-                               uint32_t *skey);
-void launch_batch_gather(hipStream_t s, const SysGeom *sys, const int2 *pblk, int64_t npblk,
-                         const int32_t *order, double4 *sorted, int32_t *perm);
-void launch_batch_ext(hipStream_t s, const SysGeom *sys, const int2 *eblk, int64_t neblk,
-                      const int2 *rblk, int64_t nrblk, const int32_t *cell_start,
-                      const double4 *sorted, int64_t next_total, int64_t nrows_total,
-                      int64_t ext_cap, int32_t *row_count, int32_t *row_start, int32_t *row_lo,
-                      int32_t *ext_start, int32_t *scan_tmp, double4 *ext_pos, float4 *ext_rel,
-                      const uint32_t *qword, int2 *ext_sq, uint32_t *status);
+// k_batch.hip: the cell build of the batched form (what launch_cell_count to
+// launch_ext_images do for one system).  pblk holds one (system, first local
+// particle) entry per block of 256 particles, rblk and eblk the same for
+// extended rows and extended cells.  cell_count must be zero on entry and is
+// zero afterwards; head[0, nhead) is zeroed, its last word then counts the
+// large cells.  rc_max_bits null: no largest cutoffs.
+struct BatchCells {
+  const SysGeom *sys;
+  int32_t nsys;
+  const int2 *pblk, *rblk, *eblk;
+  int64_t npblk, nrblk, neblk;
+  int64_t cells_total, next_total, nrows_total, ext_cap;
+  int32_t *cell_of, *slot, *cell_count, *cell_start, *scratch, *perm, *big_list;
+  uint32_t *xq, *skey, *qword, *head;
+  int nhead;
+  unsigned long long *block_max, *rc_max_bits;
+  double4 *sorted;
+  int32_t *row_count, *row_start, *row_lo, *scan_tmp, *ext_start;
+  int2 *ext_sq;
+  double4 *ext_pos;
+  float4 *ext_rel;
+  uint32_t *status;
+};
+void launch_batch_cells(hipStream_t s, const BatchCells &c);
 void launch_batch_reduce(hipStream_t s, const SysGeom *sys, int32_t nsys,
                          const double *partials, int ev_flags);
 void launch_fill_u64(hipStream_t s, unsigned long long *p, unsigned long long v, int64_t n);

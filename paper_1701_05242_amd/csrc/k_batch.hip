@@ -5,8 +5,7 @@
 // keeps each system's sorted particles in its own contiguous slice.  A block
 // of 256 threads always works inside one system: the host lists one
 // (system, first index) entry per block.
-#include "dcm_device.hpp"
-#include "dcm_internal.hpp"
+#include "cells_device.hpp"
 
 namespace dcm {
 
@@ -35,8 +34,10 @@ __device__ __forceinline__ ExtGeom ext_geom(const SysGeom &g) {
 // kb_reduce_rcmax).
 __global__ __launch_bounds__(kBatchBlock) void kb_cell_count(
     const SysGeom *__restrict__ sys, const int2 *__restrict__ pblk, int32_t *__restrict__ cell_of,
-    int32_t *count, unsigned long long *__restrict__ block_max, uint32_t *__restrict__ xq,
-    uint32_t *status) {
+    int32_t *__restrict__ slot, int32_t *count, unsigned long long *__restrict__ block_max,
+    uint32_t *__restrict__ xq, uint32_t *head, int nhead, uint32_t *status) {
+  // the pair kernel's queue positions and the count of large cells start at 0
+  if (blockIdx.x == 0 && (int)threadIdx.x < nhead) head[threadIdx.x] = 0u;
   int64_t first;
   const int b = block_system(pblk, first);
   const SysGeom &g = sys[b];
@@ -68,7 +69,9 @@ __global__ __launch_bounds__(kBatchBlock) void kb_cell_count(
     c = (int)g.cell0 + lc;
     cell_of[g.p0 + i] = c;
   }
-  wave_run_add(count, (uint32_t)c, valid);
+  // the counter's value before is the particle's slot in its cell
+  const int sl = wave_run_slot(count, (uint32_t)c, valid);
+  if (valid) slot[g.p0 + i] = sl;
   __shared__ unsigned long long wmax[kBatchBlock / 64];
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) {
@@ -109,56 +112,6 @@ __global__ __launch_bounds__(256) void kb_reduce_rcmax(const SysGeom *__restrict
   }
 }
 
-// Slot of every particle inside its cell; perm[slot] = concatenated id,
-// skey[slot] = its x key.
-__global__ __launch_bounds__(kBatchBlock) void kb_cell_scatter(
-    const SysGeom *__restrict__ sys, const int2 *__restrict__ pblk,
-    const int32_t *__restrict__ cell_of, const int32_t *__restrict__ cell_start, int32_t *fill,
-    int32_t *__restrict__ perm, const uint32_t *__restrict__ xq, uint32_t *__restrict__ skey) {
-  int64_t first;
-  const int b = block_system(pblk, first);
-  const SysGeom &g = sys[b];
-  const int64_t i = first + threadIdx.x;
-  const bool valid = i < g.n;
-  const int c = valid ? cell_of[g.p0 + i] : 0;
-  const int slot = wave_run_slot(fill, (uint32_t)c, valid);
-  if (valid) {
-    const int64_t p = cell_start[c] + slot;
-    perm[p] = (int32_t)(g.p0 + i);
-    skey[p] = xq[g.p0 + i];
-  }
-}
-
-// Sorted copy (x, y, z, rc) in the order order[] (concatenated ids, copied
-// to perm) with positions wrapped into each system's box.
-__global__ __launch_bounds__(kBatchBlock) void kb_gather(const SysGeom *__restrict__ sys,
-                                                         const int2 *__restrict__ pblk,
-                                                         const int32_t *__restrict__ order,
-                                                         double4 *__restrict__ sorted,
-                                                         int32_t *__restrict__ perm) {
-  int64_t first;
-  const int b = block_system(pblk, first);
-  const SysGeom &g = sys[b];
-  const int64_t k = first + threadIdx.x;
-  if (k >= g.n) return;
-  const int64_t s = g.p0 + k;
-  const int32_t id = order[s];
-  perm[s] = id;
-  const int64_t i = id - g.p0;
-  const double px = g.x[i], py = g.y[i], pz = g.z[i];
-  double4 o;
-  if (finite3(px, py, pz)) {
-    o.x = wrap_coord(px, g.L[0]);
-    o.y = wrap_coord(py, g.L[1]);
-    o.z = wrap_coord(pz, g.L[2]);
-  } else {
-    o.x = o.y = o.z = 0.0;
-  }
-  const double r = g.rc[i];
-  o.w = (r >= 0.0) ? (r < g.rc_cap ? r : g.rc_cap) : 0.0;  // NaN -> 0
-  sorted[s] = o;
-}
-
 __device__ __forceinline__ int64_t ext_cells_of(const SysGeom &g) {
   return (int64_t)g.ne[0] * g.ne[1] * g.ne[2];
 }
@@ -172,32 +125,103 @@ __device__ __forceinline__ int64_t ext_rows_of(const SysGeom &g) {
   return (int64_t)g.ne[1] * g.ne[2];
 }
 
-__global__ __launch_bounds__(kBatchBlock) void kb_ext_rows(const SysGeom *__restrict__ sys,
-                                                           const int2 *__restrict__ rblk,
-                                                           const int32_t *__restrict__ cell_start,
-                                                           int32_t *__restrict__ row_count,
-                                                           int32_t *__restrict__ row_lo) {
-  int64_t first;
-  const int b = block_system(rblk, first);
+// Every particle to its slot (the count's): perm[slot] = concatenated id,
+// skey[slot] = its x key.  The first nrblk workgroups instead form the extended
+// rows' counts, which also need only the cell starts.
+__global__ __launch_bounds__(kBatchBlock) void kb_cell_scatter(
+    const SysGeom *__restrict__ sys, const int2 *__restrict__ pblk,
+    const int2 *__restrict__ rblk, unsigned nrblk, const int32_t *__restrict__ cell_of,
+    const int32_t *__restrict__ slot, const int32_t *__restrict__ cell_start,
+    int32_t *__restrict__ perm, const uint32_t *__restrict__ xq, uint32_t *__restrict__ skey,
+    int32_t *__restrict__ row_count, int32_t *__restrict__ row_lo) {
+  const bool rows = blockIdx.x < nrblk;
+  const int2 w = rows ? rblk[blockIdx.x] : pblk[blockIdx.x - nrblk];
+  const int b = __builtin_amdgcn_readfirstlane(w.x);
+  const int64_t k = __builtin_amdgcn_readfirstlane(w.y) + (int64_t)threadIdx.x;
   const SysGeom &g = sys[b];
-  const int64_t row = first + threadIdx.x;
-  if (row >= ext_rows_of(g)) return;
-  const ExtGeom eg = ext_geom(g);
-  const ExtRow r = ext_row(eg, (int)row);
-  const int32_t *cs = cell_start + g.cell0;
-  const int64_t T = cs[r.r0 + g.nc[0]] - cs[r.r0];
-  const int64_t lo = row_prefix(cs, r.r0, g.nc[0], T, -g.h[0]);
-  const int64_t hi = row_prefix(cs, r.r0, g.nc[0], T, g.nc[0] + g.h[0]);
-  row_count[g.row0 + row] = (int32_t)(hi - lo);
-  row_lo[g.row0 + row] = (int32_t)lo;
+  if (rows) {
+    if (k < ext_rows_of(g))
+      row_count[g.row0 + k] =
+          ext_row_count(cell_start + g.cell0, ext_geom(g), (int)k, row_lo[g.row0 + k]);
+    return;
+  }
+  if (k >= g.n) return;
+  const int64_t id = g.p0 + k;
+  const int64_t p = cell_start[cell_of[id]] + slot[id];
+  perm[p] = (int32_t)id;
+  skey[p] = xq[id];
 }
 
+// A particle's record from its system's arrays (concatenated id).
+__device__ __forceinline__ double4 system_record(const SysGeom &g, int64_t id) {
+  const int64_t i = id - g.p0;
+  return gather_record(g.L, g.rc_cap, g.x[i], g.y[i], g.z[i], g.rc[i]);
+}
+
+// The order within the cells and the sorted copy (k_cell_rank's work, system
+// by system: a block's slots belong to one system).  SCAN: the first workgroup
+// instead scans the extended rows' counts of all systems.
+template <bool SCAN>
+__global__ __launch_bounds__(kBatchBlock) void kb_cell_rank(
+    const SysGeom *__restrict__ sys, const int2 *__restrict__ pblk,
+    const int32_t *__restrict__ cell_start, const int32_t *__restrict__ cell_of,
+    const int32_t *__restrict__ scattered, const uint32_t *__restrict__ skey,
+    uint32_t *__restrict__ qword, int32_t *__restrict__ perm, int32_t *__restrict__ big_list,
+    uint32_t *big_count, double4 *__restrict__ sorted, const int32_t *__restrict__ row_count,
+    int64_t nrows, int32_t *__restrict__ row_start) {
+  if constexpr (SCAN) {
+    __shared__ int32_t lds[kBatchBlock / 64];
+    if (blockIdx.x == 0) {
+      scan_by_block<kBatchBlock>(row_count, nrows, row_start, lds, ScanClear{nullptr, nullptr});
+      return;
+    }
+  }
+  const int2 w = pblk[blockIdx.x - (SCAN ? 1u : 0u)];
+  const int s = __builtin_amdgcn_readfirstlane(w.x);
+  const int64_t k = __builtin_amdgcn_readfirstlane(w.y) + (int64_t)threadIdx.x;
+  const SysGeom &g = sys[s];
+  if (k >= g.n) return;
+  const int64_t p = g.p0 + k;
+  const int id = scattered[p];
+  const double4 rec = system_record(g, id);
+  const int c = cell_of[id];
+  const int a = cell_start[c], b = cell_start[c + 1];
+  if (p == a) {
+    qword[c] = sub_word(skey, a, b);
+    if (b - a > kSmallCell) big_list[atomicAdd(big_count, 1u)] = (int32_t)c;
+  }
+  if (b - a > kSmallCell) {
+    perm[p] = id;
+    return;
+  }
+  const int r = rank_in_cell(scattered, skey, p, id, a, b);
+  perm[a + r] = id;
+  sorted[a + r] = rec;
+}
+
+// The last big_blocks workgroups instead sort the cells too large to rank.
 __global__ __launch_bounds__(kBatchBlock) void kb_ext_starts(
     const SysGeom *__restrict__ sys, const int2 *__restrict__ eblk,
     const int32_t *__restrict__ cell_start, const int32_t *__restrict__ row_start,
     const int32_t *__restrict__ row_lo, int64_t next_total, int64_t nrows_total,
     int32_t *__restrict__ ext_start, const uint32_t *__restrict__ qword,
-    int2 *__restrict__ ext_sq) {
+    int2 *__restrict__ ext_sq, int nsys, unsigned big_blocks, int32_t *perm, int32_t *tmp,
+    const uint32_t *__restrict__ xq, const int32_t *__restrict__ big_list,
+    const uint32_t *big_count, double4 *__restrict__ sorted) {
+  if (blockIdx.x >= gridDim.x - big_blocks) {
+    sort_big_cells(cell_start, perm, tmp, xq, big_list, big_count,
+                   blockIdx.x - (gridDim.x - big_blocks), big_blocks,
+                   [&](int64_t c, int slot, int id) {
+                     int lo = 0, hi = nsys;  // the last system whose first cell is at most c
+                     while (hi - lo > 1) {
+                       const int m = (lo + hi) >> 1;
+                       if (sys[m].cell0 <= c) lo = m;
+                       else hi = m;
+                     }
+                     sorted[slot] = system_record(sys[lo], id);
+                   });
+    return;
+  }
   int64_t first;
   const int b = block_system(eblk, first);
   const SysGeom &g = sys[b];
@@ -288,50 +312,38 @@ __global__ __launch_bounds__(kReduceThreads) void kb_reduce(const SysGeom *__res
   }
 }
 
-void launch_batch_cell_count(hipStream_t s, const SysGeom *sys, int32_t nsys, const int2 *pblk,
-                             int64_t npblk, int32_t *cell_of, int32_t *cell_count,
-                             unsigned long long *block_max, unsigned long long *rc_max_bits,
-                             uint32_t *xq, uint32_t *status) {
-  if (npblk > 0)
-    hipLaunchKernelGGL(kb_cell_count, dim3((unsigned)npblk), dim3(kBatchBlock), 0, s, sys, pblk,
-                       cell_of, cell_count, block_max, xq, status);
-  if (nsys > 0)
-    hipLaunchKernelGGL(kb_reduce_rcmax, dim3((unsigned)nsys), dim3(256), 0, s, sys, block_max,
-                       rc_max_bits);
-}
-
-void launch_batch_cell_scatter(hipStream_t s, const SysGeom *sys, const int2 *pblk,
-                               int64_t npblk, const int32_t *cell_of, const int32_t *cell_start,
-                               int32_t *cell_fill, int32_t *perm, const uint32_t *xq,
-                               uint32_t *skey) {
-  if (npblk <= 0) return;
-  hipLaunchKernelGGL(kb_cell_scatter, dim3((unsigned)npblk), dim3(kBatchBlock), 0, s, sys, pblk,
-                     cell_of, cell_start, cell_fill, perm, xq, skey);
-}
-
-void launch_batch_gather(hipStream_t s, const SysGeom *sys, const int2 *pblk, int64_t npblk,
-                         const int32_t *order, double4 *sorted, int32_t *perm) {
-  if (npblk <= 0) return;
-  hipLaunchKernelGGL(kb_gather, dim3((unsigned)npblk), dim3(kBatchBlock), 0, s, sys, pblk, order,
-                     sorted, perm);
-}
-
-void launch_batch_ext(hipStream_t s, const SysGeom *sys, const int2 *eblk, int64_t neblk,
-                      const int2 *rblk, int64_t nrblk, const int32_t *cell_start,
-                      const double4 *sorted, int64_t next_total, int64_t nrows_total,
-                      int64_t ext_cap, int32_t *row_count, int32_t *row_start, int32_t *row_lo,
-                      int32_t *ext_start, int32_t *scan_tmp, double4 *ext_pos, float4 *ext_rel,
-                      const uint32_t *qword, int2 *ext_sq, uint32_t *status) {
-  if (nrblk <= 0 || neblk <= 0) return;
-  hipLaunchKernelGGL(kb_ext_rows, dim3((unsigned)nrblk), dim3(kBatchBlock), 0, s, sys, rblk,
-                     cell_start, row_count, row_lo);
-  launch_exclusive_scan(s, row_count, row_start, nrows_total, scan_tmp);
-  hipLaunchKernelGGL(kb_ext_starts, dim3((unsigned)neblk), dim3(kBatchBlock), 0, s, sys, eblk,
-                     cell_start, row_start, row_lo, next_total, nrows_total, ext_start, qword,
-                     ext_sq);
-  hipLaunchKernelGGL(kb_ext_fill, dim3((unsigned)(nrblk * kFillGroups)), dim3(kBatchBlock), 0, s,
-                     sys, rblk, cell_start, row_start, row_lo, sorted, ext_cap, ext_pos, ext_rel,
-                     status);
+void launch_batch_cells(hipStream_t s, const BatchCells &c) {
+  if (c.npblk > 0)
+    hipLaunchKernelGGL(kb_cell_count, dim3((unsigned)c.npblk), dim3(kBatchBlock), 0, s, c.sys,
+                       c.pblk, c.cell_of, c.slot, c.cell_count, c.block_max, c.xq, c.head, c.nhead,
+                       c.status);
+  if (c.rc_max_bits && c.nsys > 0)
+    hipLaunchKernelGGL(kb_reduce_rcmax, dim3((unsigned)c.nsys), dim3(256), 0, s, c.sys,
+                       c.block_max, c.rc_max_bits);
+  launch_cell_scan(s, c.cell_count, c.cell_start, c.cells_total, c.qword, c.scan_tmp);
+  if (c.nrblk <= 0 || c.neblk <= 0) return;
+  hipLaunchKernelGGL(kb_cell_scatter, dim3((unsigned)(c.nrblk + c.npblk)), dim3(kBatchBlock), 0, s,
+                     c.sys, c.pblk, c.rblk, (unsigned)c.nrblk, c.cell_of, c.slot, c.cell_start,
+                     c.scratch, c.xq, c.skey, c.row_count, c.row_lo);
+  const bool fused = c.npblk > 0 && c.nrows_total <= kRowScanMax;
+  if (!fused) launch_exclusive_scan(s, c.row_count, c.row_start, c.nrows_total, c.scan_tmp);
+  uint32_t *big_count = c.head + c.nhead - 1;
+  if (fused)
+    hipLaunchKernelGGL(kb_cell_rank<true>, dim3((unsigned)c.npblk + 1u), dim3(kBatchBlock), 0, s,
+                       c.sys, c.pblk, c.cell_start, c.cell_of, c.scratch, c.skey, c.qword, c.perm,
+                       c.big_list, big_count, c.sorted, c.row_count, c.nrows_total, c.row_start);
+  else if (c.npblk > 0)
+    hipLaunchKernelGGL(kb_cell_rank<false>, dim3((unsigned)c.npblk), dim3(kBatchBlock), 0, s,
+                       c.sys, c.pblk, c.cell_start, c.cell_of, c.scratch, c.skey, c.qword, c.perm,
+                       c.big_list, big_count, c.sorted, nullptr, 0, nullptr);
+  const unsigned big_blocks = c.npblk > 0 ? (unsigned)kBigSortBlocks : 0u;
+  hipLaunchKernelGGL(kb_ext_starts, dim3((unsigned)c.neblk + big_blocks), dim3(kBatchBlock), 0, s,
+                     c.sys, c.eblk, c.cell_start, c.row_start, c.row_lo, c.next_total,
+                     c.nrows_total, c.ext_start, c.qword, c.ext_sq, (int)c.nsys, big_blocks,
+                     c.perm, c.scratch, c.xq, c.big_list, big_count, c.sorted);
+  hipLaunchKernelGGL(kb_ext_fill, dim3((unsigned)(c.nrblk * kFillGroups)), dim3(kBatchBlock), 0, s,
+                     c.sys, c.rblk, c.cell_start, c.row_start, c.row_lo, c.sorted, c.ext_cap,
+                     c.ext_pos, c.ext_rel, c.status);
 }
 
 void launch_batch_reduce(hipStream_t s, const SysGeom *sys, int32_t nsys,

@@ -1,6 +1,5 @@
 // Cutoff assignment (Section 2.2) and linked-cell binning (Section 2.3).
-#include "dcm_device.hpp"
-#include "dcm_internal.hpp"
+#include "cells_device.hpp"
 
 namespace dcm {
 
@@ -130,9 +129,10 @@ __global__ __launch_bounds__(256) void k_cell_count(
     const double *__restrict__ x, const double *__restrict__ y, const double *__restrict__ z,
     const double *__restrict__ rc, int64_t n, double Lx, double Ly, double Lz, int nx, int ny,
     int nz, double sx, double sy, double sz, double rc_cap, int32_t *__restrict__ cell_of,
-    int32_t *count, unsigned long long *__restrict__ block_max, uint32_t *__restrict__ xq,
-    uint32_t *status) {
+    int32_t *__restrict__ slot, int32_t *count, unsigned long long *__restrict__ block_max,
+    uint32_t *__restrict__ xq, Ctl *ctl, uint32_t *status) {
   unsigned long long rmax = 0;
+  if (blockIdx.x == 0 && threadIdx.x == 0) ctl->big_cells = 0u;  // for the cell sort that follows
   // uniform trip count: every lane reaches the run-aggregated atomic
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t base = blockIdx.x * (int64_t)blockDim.x; base < n; base += stride) {
@@ -163,7 +163,9 @@ __global__ __launch_bounds__(256) void k_cell_count(
       rmax = bits > rmax ? bits : rmax;
       cell_of[i] = c;
     }
-    wave_run_add(count, (uint32_t)c, valid);
+    // the counter's value before is the particle's slot in its cell
+    const int sl = wave_run_slot(count, (uint32_t)c, valid);
+    if (valid) slot[i] = sl;
   }
   // the workgroup's largest cutoff, stored without atomics (one address
   // shared by every workgroup would serialise them)
@@ -182,27 +184,6 @@ __global__ __launch_bounds__(256) void k_cell_count(
   }
 }
 
-// Largest of the workgroup maxima into the control block.
-__global__ __launch_bounds__(1024) void k_reduce_rcmax(const unsigned long long *__restrict__ bm,
-                                                       int64_t nb, Ctl *ctl) {
-  __shared__ unsigned long long wmax[16];
-  unsigned long long m = 0;
-  for (int64_t b = threadIdx.x; b < nb; b += 1024) m = bm[b] > m ? bm[b] : m;
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    unsigned long long o = __shfl_xor(m, off, 64);
-    m = o > m ? o : m;
-  }
-  if ((threadIdx.x & 63) == 0) wmax[threadIdx.x >> 6] = m;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    for (int w = 1; w < 16; ++w) m = wmax[w] > m ? wmax[w] : m;
-    m = wmax[0] > m ? wmax[0] : m;
-    ctl->rc_max_bits = m;
-    ctl->big_cells = 0u;  // for the cell sort that follows
-  }
-}
-
 int64_t cell_count_blocks(int64_t n) {
   int64_t b = ceil_div(n, 256);
   if (b > 16384) b = 16384;
@@ -211,76 +192,17 @@ int64_t cell_count_blocks(int64_t n) {
 
 void launch_cell_count(hipStream_t s, const double *x, const double *y, const double *z,
                        const double *rc, int64_t n, const double L[3], const int32_t nc[3],
-                       const double sc[3], double rc_cap, int32_t *cell_of, int32_t *cell_count,
-                       unsigned long long *block_max, uint32_t *xq, Ctl *ctl, uint32_t *status) {
-  const int64_t b = cell_count_blocks(n);
-  if (n > 0)
-    hipLaunchKernelGGL(k_cell_count, dim3((unsigned)b), dim3(256), 0, s, x, y, z, rc, n, L[0],
-                       L[1], L[2], nc[0], nc[1], nc[2], sc[0], sc[1], sc[2], rc_cap, cell_of,
-                       cell_count, block_max, xq, status);
-  hipLaunchKernelGGL(k_reduce_rcmax, dim3(1), dim3(1024), 0, s, block_max, n > 0 ? b : 0, ctl);
+                       const double sc[3], double rc_cap, int32_t *cell_of, int32_t *slot,
+                       int32_t *cell_count, unsigned long long *block_max, uint32_t *xq, Ctl *ctl,
+                       uint32_t *status) {
+  if (n <= 0) return;
+  hipLaunchKernelGGL(k_cell_count, dim3((unsigned)cell_count_blocks(n)), dim3(256), 0, s, x, y, z,
+                     rc, n, L[0], L[1], L[2], nc[0], nc[1], nc[2], sc[0], sc[1], sc[2], rc_cap,
+                     cell_of, slot, cell_count, block_max, xq, ctl, status);
 }
 
 // ------------------------------------------------------- exclusive scan
-// Three phases over tiles of kScanTile elements: tile totals, one workgroup
-// scanning the totals, then each tile's local scan plus its offset.  A thread
-// owns kScanPer consecutive elements, read and written as int4.
-constexpr int kScanThreads = 256;
-constexpr int kScanPer = 16;
-constexpr int kScanTile = kScanThreads * kScanPer;
-constexpr int kTotalsThreads = 1024;
-constexpr int64_t kScanSumTiles = 4096;  // up to this many tiles: no pass over the totals
-
 int64_t scan_tmp_elems(int64_t n) { return ceil_div(n, kScanTile) + 1; }
-
-// Inclusive scan over the 64 lanes of a wavefront.
-__device__ __forceinline__ int32_t wave_inclusive_scan(int32_t v) {
-  const int lane = threadIdx.x & 63;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const int32_t o = __shfl_up(v, off, 64);
-    if (lane >= off) v += o;
-  }
-  return v;
-}
-
-// Exclusive scan over the workgroup (NW wavefronts); lds holds NW entries.
-template <int NW>
-__device__ __forceinline__ int32_t block_exclusive_scan(int32_t v, int32_t *lds, int32_t *total) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int32_t incl = wave_inclusive_scan(v);
-  if (lane == 63) lds[w] = incl;
-  __syncthreads();
-  int32_t before = 0, all = 0;
-#pragma unroll
-  for (int k = 0; k < NW; ++k) {
-    const int32_t t = lds[k];
-    before += k < w ? t : 0;
-    all += t;
-  }
-  __syncthreads();  // lds may be reused after this
-  *total = all;
-  return before + incl - v;
-}
-
-// this thread's kScanPer elements starting at base (zeros past n)
-__device__ __forceinline__ void load_run(const int32_t *__restrict__ in, int64_t base, int64_t n,
-                                         int32_t (&v)[kScanPer]) {
-  if (base + kScanPer <= n) {
-    const int4 *p = reinterpret_cast<const int4 *>(in + base);
-#pragma unroll
-    for (int q = 0; q < kScanPer / 4; ++q) {
-      const int4 t = p[q];
-      v[4 * q] = t.x;
-      v[4 * q + 1] = t.y;
-      v[4 * q + 2] = t.z;
-      v[4 * q + 3] = t.w;
-    }
-  } else {
-#pragma unroll
-    for (int q = 0; q < kScanPer; ++q) v[q] = base + q < n ? in[base + q] : 0;
-  }
-}
 
 __global__ __launch_bounds__(kScanThreads) void k_scan_tiles(const int32_t *__restrict__ in,
                                                              int64_t n, int32_t *tile_sum) {
@@ -320,10 +242,10 @@ __global__ __launch_bounds__(kTotalsThreads) void k_scan_totals(int32_t *tile_su
 // false), or the sum of the raw totals of the tiles before it (SUM true: no
 // separate pass over the totals; the last tile also writes out[n]).
 template <bool SUM>
-__global__ __launch_bounds__(kScanThreads) void k_scan_apply(const int32_t *__restrict__ in,
-                                                             int64_t n,
+__global__ __launch_bounds__(kScanThreads) void k_scan_apply(const int32_t *in, int64_t n,
                                                              const int32_t *__restrict__ tile_off,
-                                                             int32_t *__restrict__ out) {
+                                                             int32_t *__restrict__ out,
+                                                             ScanClear clr) {
   __shared__ int32_t lds[kScanThreads / 64];
   int32_t off;
   if constexpr (SUM) {
@@ -340,120 +262,106 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_apply(const int32_t *__re
 #pragma unroll
   for (int q = 0; q < kScanPer; ++q) s += v[q];
   int32_t total;
-  int32_t run = block_exclusive_scan<kScanThreads / 64>(s, lds, &total) + off;
+  const int32_t run = block_exclusive_scan<kScanThreads / 64>(s, lds, &total) + off;
   if (SUM && blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) out[n] = off + total;
-  int32_t o[kScanPer];
-#pragma unroll
-  for (int q = 0; q < kScanPer; ++q) {
-    o[q] = run;
-    run += v[q];
-  }
-  if (base + kScanPer <= n) {
-    int4 *p = reinterpret_cast<int4 *>(out + base);
-#pragma unroll
-    for (int q = 0; q < kScanPer / 4; ++q)
-      p[q] = make_int4(o[4 * q], o[4 * q + 1], o[4 * q + 2], o[4 * q + 3]);
-  } else {
-#pragma unroll
-    for (int q = 0; q < kScanPer; ++q)
-      if (base + q < n) out[base + q] = o[q];
-  }
+  store_run(out, base, n, v, run, clr);
 }
 
-void launch_exclusive_scan(hipStream_t s, const int32_t *in, int32_t *out, int64_t n,
-                           int32_t *tmp) {
-  // out has n + 1 entries; out[n] = total.  in and out are 16-byte aligned.
-  int64_t ntiles = ceil_div(n, kScanTile);
-  if (ntiles < 1) ntiles = 1;
+__global__ __launch_bounds__(kTotalsThreads) void k_scan_one(const int32_t *in, int64_t n,
+                                                             int32_t *out, ScanClear clr) {
+  __shared__ int32_t lds[kTotalsThreads / 64];
+  scan_by_block<kTotalsThreads>(in, n, out, lds, clr);
+}
+
+// Up to this many elements one workgroup scans in one launch, in one round
+// (4.6 us traced against 4.1 + 4.3 for two launches; two rounds take 10.7).
+constexpr int64_t kScanOneMax = (int64_t)kTotalsThreads * kScanPer;
+
+static void launch_scan(hipStream_t s, const int32_t *in, int32_t *out, int64_t n, int32_t *tmp,
+                        const ScanClear &clr) {
+  // out has n + 1 entries; out[n] = total.  in, out and the cleared arrays are
+  // 16-byte aligned.
+  if (n <= kScanOneMax) {
+    hipLaunchKernelGGL(k_scan_one, dim3(1), dim3(kTotalsThreads), 0, s, in, n, out, clr);
+    return;
+  }
+  const int64_t ntiles = ceil_div(n, kScanTile);
   hipLaunchKernelGGL(k_scan_tiles, dim3((unsigned)ntiles), dim3(kScanThreads), 0, s, in, n, tmp);
   if (ntiles <= kScanSumTiles) {
     // each tile sums the totals before it (at most kScanSumTiles / 256 reads
     // per thread): two launches
     hipLaunchKernelGGL(k_scan_apply<true>, dim3((unsigned)ntiles), dim3(kScanThreads), 0, s, in,
-                       n, tmp, out);
+                       n, tmp, out, clr);
     return;
   }
   hipLaunchKernelGGL(k_scan_totals, dim3(1), dim3(kTotalsThreads), 0, s, tmp, ntiles, out + n);
   hipLaunchKernelGGL(k_scan_apply<false>, dim3((unsigned)ntiles), dim3(kScanThreads), 0, s, in, n,
-                     tmp, out);
+                     tmp, out, clr);
+}
+
+void launch_exclusive_scan(hipStream_t s, const int32_t *in, int32_t *out, int64_t n,
+                           int32_t *tmp) {
+  launch_scan(s, in, out, n, tmp, ScanClear{nullptr, nullptr});
+}
+
+void launch_cell_scan(hipStream_t s, int32_t *cell_count, int32_t *cell_start, int64_t ncell,
+                      uint32_t *qword, int32_t *tmp) {
+  launch_scan(s, cell_count, cell_start, ncell, tmp, ScanClear{cell_count, qword});
 }
 
 // ------------------------------------------------ scatter + stable order
-// Slot of every particle inside its cell: perm[slot] = id, skey[slot] = its
-// x key.
-__global__ __launch_bounds__(256) void k_cell_scatter(const int32_t *__restrict__ cell_of,
-                                                      int64_t n,
-                                                      const int32_t *__restrict__ cell_start,
-                                                      int32_t *fill, int32_t *__restrict__ perm,
-                                                      const uint32_t *__restrict__ xq,
-                                                      uint32_t *__restrict__ skey) {
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t base = blockIdx.x * (int64_t)blockDim.x; base < n; base += stride) {
-    const int64_t i = base + threadIdx.x;
-    const bool valid = i < n;
-    const int c = valid ? cell_of[i] : 0;
-    const int slot = wave_run_slot(fill, (uint32_t)c, valid);
-    if (valid) {
-      const int64_t p = cell_start[c] + slot;
-      perm[p] = (int32_t)i;
-      skey[p] = xq[i];
-    }
+// Every particle to its slot (the count's): perm[slot] = id, skey[slot] = its x
+// key.  The first row_blocks workgroups instead form the extended rows' counts
+// (one thread per row), which also need only the cell starts, and the last one
+// the largest cutoff from the count's maxima per workgroup.
+struct ExtRows {
+  ExtGeom g;
+  int64_t nrows;
+  int32_t *row_count, *row_lo;
+};
+__device__ __forceinline__ void reduce_rcmax(const unsigned long long *__restrict__ bm, int nb,
+                                             Ctl *ctl) {
+  __shared__ unsigned long long wmax[4];
+  unsigned long long m = 0;
+#pragma unroll 8
+  for (int b = threadIdx.x; b < nb; b += 256) m = bm[b] > m ? bm[b] : m;
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    unsigned long long o = __shfl_xor(m, off, 64);
+    m = o > m ? o : m;
+  }
+  if ((threadIdx.x & 63) == 0) wmax[threadIdx.x >> 6] = m;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 0; w < 4; ++w) m = wmax[w] > m ? wmax[w] : m;
+    ctl->rc_max_bits = m;
   }
 }
-
-void launch_cell_scatter(hipStream_t s, const int32_t *cell_of, int64_t n,
-                         const int32_t *cell_start, int32_t *cell_fill, int32_t *perm,
-                         const uint32_t *xq, uint32_t *skey) {
-  if (n <= 0) return;
-  int64_t b = ceil_div(n, 256);
-  if (b > 16384) b = 16384;
-  hipLaunchKernelGGL(k_cell_scatter, dim3((unsigned)b), dim3(256), 0, s, cell_of, n, cell_start,
-                     cell_fill, perm, xq, skey);
-}
-
-// Atomic slots give an arbitrary order inside a cell; sort each cell's
-// entries by (x key, caller index) so the layout (and every FP sum) is
-// reproducible and each cell's particles are in x order.  Cells of at most
-// kSmallCell entries are ranked one thread per particle (k_cell_rank);
-// larger cells go to a list that whole workgroups sort (k_cell_sort_big).
-constexpr int kSmallCell = 32;
-constexpr int kSortChunk = 4096;  // entries a workgroup sorts at once in LDS
-constexpr int kBigSortBlocks = 256;
-
-// Order of two particles of one cell: by x key, then by caller index (the
-// keys are x positions quantised to 2^-20 of the cell, so a cell's particles
-// end up in x order and every extended row is x-sorted).
-__device__ __forceinline__ uint64_t sort_key(const uint32_t *__restrict__ xq, int i) {
-  return ((uint64_t)xq[i] << 32) | (uint32_t)i;
-}
-
-// A cell's sub-cell word from the x keys of its slots [a, b): nibble k
-// (k = 0..6) counts its particles with x keys below (k + 1)/8 of the cell --
-// with the particles in key order, the first slot of sub-cell k + 1 is the
-// cell's first plus that count -- and nibble 7 counts them all; 0 (no
-// sub-cells) for a cell of more than 15.  A nibble histogram of the
-// sub-cells times 0x11111111 is its prefix sums.
-__device__ __forceinline__ uint32_t sub_word(const uint32_t *__restrict__ skey, int a, int b) {
-  if (b - a > 15) return 0u;
-  uint32_t hist = 0;
-  for (int p = a; p < b; ++p) hist += 1u << (4 * (skey[p] >> (20 - kXSubLog)));
-  return hist * 0x11111111u;
-}
-
-// One thread per cell: its sub-cell word, and a cell of more than
-// kSmallCell particles goes to the list that whole workgroups sort
-// (k_cell_sort_big).
-__global__ __launch_bounds__(256) void k_cell_small(const int32_t *__restrict__ cell_start,
-                                                    int64_t ncell,
-                                                    const uint32_t *__restrict__ skey,
-                                                    uint32_t *__restrict__ qword,
-                                                    int32_t *__restrict__ big_list,
-                                                    uint32_t *big_count) {
-  for (int64_t c = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; c < ncell;
-       c += (int64_t)gridDim.x * blockDim.x) {
-    const int a = cell_start[c], b = cell_start[c + 1];
-    if (qword) qword[c] = sub_word(skey, a, b);
-    if (b - a > kSmallCell) big_list[atomicAdd(big_count, 1u)] = (int32_t)c;
+__global__ __launch_bounds__(256) void k_cell_scatter(const int32_t *__restrict__ cell_of,
+                                                      const int32_t *__restrict__ slot, int64_t n,
+                                                      const int32_t *__restrict__ cell_start,
+                                                      int32_t *__restrict__ perm,
+                                                      const uint32_t *__restrict__ xq,
+                                                      uint32_t *__restrict__ skey,
+                                                      unsigned row_blocks, ExtRows rows,
+                                                      const unsigned long long *__restrict__ bm,
+                                                      int nmax, Ctl *ctl) {
+  if (blockIdx.x == gridDim.x - 1) {
+    reduce_rcmax(bm, nmax, ctl);
+    return;
+  }
+  if (blockIdx.x < row_blocks) {
+    const int row = (int)(blockIdx.x * 256 + threadIdx.x);
+    if (row < (int)rows.nrows)
+      rows.row_count[row] = ext_row_count(cell_start, rows.g, row, rows.row_lo[row]);
+    return;
+  }
+  const int64_t stride = (int64_t)(gridDim.x - 1 - row_blocks) * blockDim.x;
+  for (int64_t i = (blockIdx.x - row_blocks) * (int64_t)blockDim.x + threadIdx.x; i < n;
+       i += stride) {
+    const int64_t p = cell_start[cell_of[i]] + slot[i];
+    perm[p] = (int32_t)i;
+    skey[p] = xq[i];
   }
 }
 
@@ -462,172 +370,50 @@ __global__ __launch_bounds__(256) void k_cell_small(const int32_t *__restrict__ 
 // (the count of the cell's particles with smaller (x key, id)); a particle
 // of a large cell keeps its slot.  out receives the result; no thread waits
 // on another.
-// The sorted record of particle i: (x, y, z) wrapped into the box (0 when
-// not finite) and rc clamped to [0, rc_cap] (NaN -> 0).
-__device__ __forceinline__ double4 gather_record(const GatherOut &go, double px, double py,
-                                                 double pz, double r) {
-  double4 o;
-  if (finite3(px, py, pz)) {
-    o.x = wrap_coord(px, go.L[0]);
-    o.y = wrap_coord(py, go.L[1]);
-    o.z = wrap_coord(pz, go.L[2]);
-  } else {
-    o.x = o.y = o.z = 0.0;
-  }
-  o.w = (r >= 0.0) ? (r < go.rc_cap ? r : go.rc_cap) : 0.0;
-  return o;
-}
-
-__device__ __forceinline__ double4 gather_record(const GatherOut &go, int i) {
-  return gather_record(go, go.x[i], go.y[i], go.z[i], go.rc ? go.rc[i] : 0.0);
-}
-
-// GATHER: a particle of a small cell also writes its sorted record at its
-// final slot (the gather of the sorted copy done here, not in a pass of its
-// own); out is then the final order.
-template <bool GATHER>
+// A particle of a small cell also writes its sorted record at its final slot
+// (no gather pass of its own).  The thread of a cell's first slot writes the
+// cell's sub-cell word (cells without particles keep the 0 that the scan of the
+// counts left), and lists a cell too large to rank.
+// SCAN: the first workgroup instead scans the extended rows' counts, beside
+// the others' work.
+template <bool SCAN>
 __global__ __launch_bounds__(256) void k_cell_rank(const int32_t *__restrict__ cell_start,
                                                    const int32_t *__restrict__ cell_of,
                                                    const int32_t *__restrict__ perm, int64_t n,
                                                    const uint32_t *__restrict__ skey,
-                                                   int32_t *__restrict__ out, GatherOut go) {
-  for (int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; p < n;
-       p += (int64_t)gridDim.x * blockDim.x) {
+                                                   uint32_t *__restrict__ qword,
+                                                   int32_t *__restrict__ out,
+                                                   int32_t *__restrict__ big_list,
+                                                   uint32_t *big_count, GatherOut go,
+                                                   const int32_t *__restrict__ row_count,
+                                                   int64_t nrows, int32_t *__restrict__ row_start) {
+  if constexpr (SCAN) {
+    __shared__ int32_t lds[256 / 64];
+    if (blockIdx.x == 0) {
+      scan_by_block<256>(row_count, nrows, row_start, lds, ScanClear{nullptr, nullptr});
+      return;
+    }
+  }
+  const unsigned skip = SCAN ? 1u : 0u;
+  for (int64_t p = (blockIdx.x - skip) * (int64_t)blockDim.x + threadIdx.x; p < n;
+       p += (int64_t)(gridDim.x - skip) * blockDim.x) {
     const int i = perm[p];
     // the record's inputs are read while the cell's keys are counted
-    double px = 0.0, py = 0.0, pz = 0.0, pr = 0.0;
-    if constexpr (GATHER) {
-      px = go.x[i];
-      py = go.y[i];
-      pz = go.z[i];
-      pr = go.rc ? go.rc[i] : 0.0;
-    }
+    const double px = go.x[i], py = go.y[i], pz = go.z[i], pr = go.rc ? go.rc[i] : 0.0;
     const int c = cell_of[i];
     const int a = cell_start[c], b = cell_start[c + 1];
+    if (p == a) {
+      if (qword) qword[c] = sub_word(skey, a, b);
+      if (b - a > kSmallCell) big_list[atomicAdd(big_count, 1u)] = (int32_t)c;
+    }
     if (b - a > kSmallCell) {
       out[p] = i;
       continue;
     }
-    const uint32_t ki = skey[p];
-    int r = 0;
-    // four keys per round, all read before they are compared
-    for (int q0 = a; q0 < b; q0 += 4) {
-      uint32_t kj[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) kj[u] = q0 + u < b ? skey[q0 + u] : 0xffffffffu;
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        if (q0 + u >= b) continue;
-        r += kj[u] < ki ? 1 : 0;
-        if (kj[u] == ki) r += perm[q0 + u] < i ? 1 : 0;  // equal keys (rare): by id
-      }
-    }
+    const int r = rank_in_cell(perm, skey, p, i, a, b);
     out[a + r] = i;
-    if constexpr (GATHER) go.sorted[a + r] = gather_record(go, px, py, pz, pr);
+    go.sorted[a + r] = gather_record(go.L, go.rc_cap, px, py, pz, pr);
   }
-}
-
-// One workgroup per listed cell: chunks of kSortChunk entries are sorted in
-// LDS (bitonic), then runs are merged pairwise, each entry moving to its own
-// offset in its run plus the count of smaller keys in the partner run (keys
-// are distinct: they end in the caller index), ping-ponging between perm and
-// tmp.  Entries are caller indices; their keys are looked up (sort_key).
-template <bool GATHER>
-__global__ __launch_bounds__(256) void k_cell_sort_big(const int32_t *__restrict__ cell_start,
-                                                       int32_t *perm, int32_t *tmp,
-                                                       const uint32_t *__restrict__ xq,
-                                                       const int32_t *__restrict__ big_list,
-                                                       const uint32_t *big_count, GatherOut go) {
-  __shared__ int32_t buf[kSortChunk];
-  const int tid = threadIdx.x;
-  const uint32_t nbig = *big_count;
-  for (uint32_t q = blockIdx.x; q < nbig; q += gridDim.x) {
-    const int64_t c = big_list[q];
-    const int a = cell_start[c], n = cell_start[c + 1] - a;
-    for (int c0 = 0; c0 < n; c0 += kSortChunk) {
-      const int len = n - c0 < kSortChunk ? n - c0 : kSortChunk;
-      int P = 1;
-      while (P < len) P <<= 1;
-      // padding entries (-1) sort after every particle
-      for (int i = tid; i < P; i += 256) buf[i] = i < len ? perm[a + c0 + i] : -1;
-      __syncthreads();
-      auto key = [&](int v) -> uint64_t { return v < 0 ? ~uint64_t(0) : sort_key(xq, v); };
-      for (int k = 2; k <= P; k <<= 1)
-        for (int j = k >> 1; j > 0; j >>= 1) {
-          for (int i = tid; i < P; i += 256) {
-            const int l = i ^ j;
-            if (l > i) {
-              const int u = buf[i], w = buf[l];
-              if ((key(u) > key(w)) == ((i & k) == 0)) {
-                buf[i] = w;
-                buf[l] = u;
-              }
-            }
-          }
-          __syncthreads();
-        }
-      for (int i = tid; i < len; i += 256) perm[a + c0 + i] = buf[i];
-      __syncthreads();
-    }
-    int32_t *src = perm + a, *dst = tmp + a;
-    for (int L = kSortChunk; L < n; L <<= 1) {
-      for (int p = tid; p < n; p += 256) {
-        const int r = p / L, off = p - r * L;
-        const int x = src[p];
-        const uint64_t kx = sort_key(xq, x);
-        const int o = (r ^ 1) * L;  // partner run
-        int lo = 0, hi = 0;
-        if (o < n) {
-          hi = n - o < L ? n - o : L;
-          while (lo < hi) {  // count of partner keys below x's
-            const int m = (lo + hi) >> 1;
-            if (sort_key(xq, src[o + m]) < kx) lo = m + 1;
-            else hi = m;
-          }
-        }
-        dst[(r & ~1) * L + off + lo] = x;
-      }
-      __syncthreads();
-      int32_t *t = src;
-      src = dst;
-      dst = t;
-    }
-    if (src != perm + a) {
-      for (int p = tid; p < n; p += 256) perm[a + p] = src[p];
-      __syncthreads();
-    }
-    if constexpr (GATHER)
-      for (int p = tid; p < n; p += 256) go.sorted[a + p] = gather_record(go, perm[a + p]);
-  }
-}
-
-void launch_cell_sort(hipStream_t s, const int32_t *cell_start, int64_t ncell,
-                      const int32_t *cell_of, int64_t n, int32_t *perm, const uint32_t *xq,
-                      const uint32_t *skey, uint32_t *qword, int32_t *sorted_perm,
-                      int32_t *big_list, uint32_t *big_count, const GatherOut *go) {
-  int64_t b = ceil_div(ncell, 256);
-  if (b < 1) b = 1;
-  if (b > 16384) b = 16384;
-  hipLaunchKernelGGL(k_cell_small, dim3((unsigned)b), dim3(256), 0, s, cell_start, ncell, skey,
-                     qword, big_list, big_count);
-  const GatherOut g = go ? *go : GatherOut{};
-  if (n > 0) {
-    int64_t bn = ceil_div(n, 256);
-    if (bn > 16384) bn = 16384;
-    if (go)
-      hipLaunchKernelGGL(k_cell_rank<true>, dim3((unsigned)bn), dim3(256), 0, s, cell_start,
-                         cell_of, perm, n, skey, sorted_perm, g);
-    else
-      hipLaunchKernelGGL(k_cell_rank<false>, dim3((unsigned)bn), dim3(256), 0, s, cell_start,
-                         cell_of, perm, n, skey, sorted_perm, g);
-  }
-  // the large cells, in place in sorted_perm with perm as scratch
-  if (go)
-    hipLaunchKernelGGL(k_cell_sort_big<true>, dim3(kBigSortBlocks), dim3(256), 0, s, cell_start,
-                       sorted_perm, perm, xq, big_list, big_count, g);
-  else
-    hipLaunchKernelGGL(k_cell_sort_big<false>, dim3(kBigSortBlocks), dim3(256), 0, s, cell_start,
-                       sorted_perm, perm, xq, big_list, big_count, g);
 }
 
 int64_t cell_sort_list_elems(int64_t n) { return n / (kSmallCell + 1) + 1; }
@@ -645,40 +431,36 @@ int64_t cell_sort_list_elems(int64_t n) { return n / (kSmallCell + 1) + 1; }
 // unwrapped particle P = F(-h_x) + k, i.e. particle P mod T of the real row
 // shifted by floor(P / T) periods.
 
-// Per extended row: its particle count and F(-h_x).
-__global__ __launch_bounds__(256) void k_ext_rows(const int32_t *__restrict__ cell_start,
-                                                  ExtGeom g, int64_t nrows,
-                                                  int32_t *__restrict__ row_count,
-                                                  int32_t *__restrict__ row_lo) {
-  for (int row = blockIdx.x * blockDim.x + threadIdx.x; row < (int)nrows;
-       row += gridDim.x * blockDim.x) {
-    const ExtRow r = ext_row(g, row);
-    const int64_t T = cell_start[r.r0 + g.nc[0]] - cell_start[r.r0];
-    const int64_t lo = row_prefix(cell_start, r.r0, g.nc[0], T, -g.h[0]);
-    const int64_t hi = row_prefix(cell_start, r.r0, g.nc[0], T, g.nc[0] + g.h[0]);
-    row_count[row] = (int32_t)(hi - lo);
-    row_lo[row] = (int32_t)lo;
-  }
-}
-
 // ext_start of every extended cell (and of one past the last) from the row
 // starts, one wavefront per extended row with the row's values uniform.  Cell
 // u of the unwrapped row lies p = floor(u / n_x) periods away; with a halo of
 // at most n_x cells, u is in [-n_x, 2 n_x) and p in {-1, 0, 1}.
-__global__ __launch_bounds__(256) void k_ext_starts(const int32_t *__restrict__ cell_start,
-                                                    const int32_t *__restrict__ row_start,
-                                                    const int32_t *__restrict__ row_lo,
-                                                    ExtGeom g, int64_t next, int64_t nrows,
-                                                    int32_t *__restrict__ ext_start,
-                                                    const uint32_t *__restrict__ qword,
-                                                    int2 *__restrict__ ext_sq) {
+// The last big_blocks workgroups instead sort the cells too large to rank.
+// host_total (pinned, null: none) receives the extended count as well: read
+// by the host once the launch is complete, without a copy of its own.
+__global__ __launch_bounds__(256) void k_ext_starts(
+    const int32_t *__restrict__ cell_start, const int32_t *__restrict__ row_start,
+    const int32_t *__restrict__ row_lo, ExtGeom g, int64_t next, int64_t nrows,
+    int32_t *__restrict__ ext_start, const uint32_t *__restrict__ qword,
+    int2 *__restrict__ ext_sq, int32_t *host_total, unsigned big_blocks, int32_t *perm,
+    int32_t *tmp, const uint32_t *__restrict__ xq, const int32_t *__restrict__ big_list,
+    const uint32_t *big_count, GatherOut go) {
+  const unsigned own = gridDim.x - big_blocks;
+  if (blockIdx.x >= own) {
+    sort_big_cells(cell_start, perm, tmp, xq, big_list, big_count, blockIdx.x - own, big_blocks,
+                   [&](int64_t, int slot, int id) { go.sorted[slot] = gather_record(go, id); });
+    return;
+  }
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(
       (int)((blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6));
-  const int nwaves = (int)(((int64_t)gridDim.x * blockDim.x) >> 6);
+  const int nwaves = (int)(((int64_t)own * blockDim.x) >> 6);
   if (wave == 0 && lane == 0) {
-    ext_start[next] = row_start[nrows];
-    if (ext_sq) ext_sq[next] = make_int2(row_start[nrows], 0);
+    const int32_t total = row_start[nrows];
+    ext_start[next] = total;
+    if (ext_sq) ext_sq[next] = make_int2(total, 0);
+    if (host_total)
+      __hip_atomic_store(host_total, total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   }
   const int nx = g.nc[0], hx = g.h[0], nex = g.ne[0];
   const bool near = hx <= nx;
@@ -815,23 +597,43 @@ void launch_ext_refill(hipStream_t s, const int32_t *cell_start, const int32_t *
                   nullptr, nullptr, status);
 }
 
-void launch_ext_count(hipStream_t s, const int32_t *cell_start, const int32_t nc[3],
-                      const int32_t h[3], const double L[3], int32_t *row_count,
-                      int32_t *row_start, int32_t *row_lo, int32_t *ext_start,
-                      int32_t *scan_tmp, const uint32_t *qword, int2 *ext_sq) {
-  const ExtGeom g = ext_geom(nc, h, L);
+// Seven launches a build: count, scan (one up to 16K cells, else two), scatter
+// with the rows' counts and the largest cutoff, rank with the gather and the
+// rows' scan, starts with the sort of large cells, fill.  Each of them takes
+// 4-6 us below about 100,000 particles, whatever it does, so stages that wait
+// for the same predecessor share a launch and no launch clears scratch memory:
+// a whole step went from 1217 to 1082 us per ten steps of 20,000 particles
+// (FP32-mixed), from 1974 to 1850 at 99,000 (FP64) and from 12089 to 11924 at
+// 1.2 million.  At 2.6 million the count takes 55 us instead of 33 (its atomics
+// return the slots) and the scatter 28 instead of 35, without its own atomics.
+void launch_cell_order(hipStream_t s, const CellOrder &o) {
+  const ExtGeom g = ext_geom(o.nc, o.h, o.L);
   const int64_t next = (int64_t)g.ne[0] * g.ne[1] * g.ne[2];
   const int64_t nrows = (int64_t)g.ne[1] * g.ne[2];
-  int64_t b = ceil_div(nrows, 256);
-  if (b > 16384) b = 16384;
-  hipLaunchKernelGGL(k_ext_rows, dim3((unsigned)b), dim3(256), 0, s, cell_start, g, nrows,
-                     row_count, row_lo);
-  launch_exclusive_scan(s, row_count, row_start, nrows, scan_tmp);
-  b = ceil_div(nrows, 4);  // four rows per workgroup of 256
-  if (b < 1) b = 1;
-  if (b > 16384) b = 16384;
-  hipLaunchKernelGGL(k_ext_starts, dim3((unsigned)b), dim3(256), 0, s, cell_start, row_start,
-                     row_lo, g, next, nrows, ext_start, qword, ext_sq);
+  const unsigned row_blocks = (unsigned)ceil_div(nrows, 256);
+  const unsigned pblocks = (unsigned)std::min<int64_t>(ceil_div(o.n, 256), 16384);
+  const ExtRows rows = {g, nrows, o.row_count, o.row_lo};
+  hipLaunchKernelGGL(k_cell_scatter, dim3(row_blocks + pblocks + 1), dim3(256), 0, s,
+                     o.cell_of, o.slot, o.n, o.cell_start, o.scratch, o.xq, o.skey, row_blocks,
+                     rows, o.block_max, o.n > 0 ? (int)cell_count_blocks(o.n) : 0, o.ctl);
+  const bool fused = o.n > 0 && nrows <= kRowScanMax;
+  if (!fused) launch_exclusive_scan(s, o.row_count, o.row_start, nrows, o.scan_tmp);
+  if (fused)
+    hipLaunchKernelGGL(k_cell_rank<true>, dim3(pblocks + 1), dim3(256), 0, s, o.cell_start,
+                       o.cell_of, o.scratch, o.n, o.skey, o.qword, o.perm, o.big_list,
+                       o.big_count, o.go, o.row_count, nrows, o.row_start);
+  else if (o.n > 0)
+    hipLaunchKernelGGL(k_cell_rank<false>, dim3(pblocks), dim3(256), 0, s, o.cell_start,
+                       o.cell_of, o.scratch, o.n, o.skey, o.qword, o.perm, o.big_list,
+                       o.big_count, o.go, nullptr, 0, nullptr);
+  // the large cells are sorted in place in perm, with the scatter's order as
+  // scratch
+  const unsigned big_blocks = o.n > kSmallCell ? (unsigned)kBigSortBlocks : 0u;
+  const unsigned b = (unsigned)std::min<int64_t>(std::max<int64_t>(ceil_div(nrows, 4), 1), 16384);
+  hipLaunchKernelGGL(k_ext_starts, dim3(b + big_blocks), dim3(256), 0, s, o.cell_start,
+                     o.row_start, o.row_lo, g, next, nrows, o.ext_start, o.qword, o.ext_sq,
+                     o.host_total, big_blocks, o.perm, o.scratch, o.xq, o.big_list, o.big_count,
+                     o.go);
 }
 
 void launch_ext_images(hipStream_t s, const int32_t *cell_start, const int32_t *row_start,
