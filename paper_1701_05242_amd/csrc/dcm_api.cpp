@@ -132,12 +132,11 @@ dcm_status detect_enqueue(dcm_ctx *ctx, const double *x, const double *y, const 
   launch_gray_hist(s, sc.counts, sc.gray, grid.n, sc.hist, ctx->d_status);
   if (opts.split <= 0.0) launch_otsu(s, sc.hist, nvox, ctx->ctl, threshold_out, ctx->d_status);
   launch_threshold(s, sc.gray, grid.n, opts.split, ctx->ctl, sc.seg_a, threshold_out);
-  for (int p = 1; p <= kMajorityMaxPasses; ++p) {
-    if (opts.nu < 0.0)
-      launch_majority_pass(s, sc.seg_a, sc.seg_b, grid.n, p, kMajorityMaxPasses, ctx->ctl);
-    else
+  if (opts.nu < 0.0)  // the gray values are not read again: the passes' scratch
+    launch_majority(s, sc.seg_a, sc.seg_b, sc.gray, nvox, grid.n, ctx->ctl);
+  else
+    for (int p = 1; p <= kMajorityMaxPasses; ++p)
       launch_potts_pass(s, sc.seg_a, sc.seg_b, sc.gray, grid.n, opts.nu, p, ctx->ctl);
-  }
   // seg null (dcm_step): the phase maps feed the distance sweep directly
   if (seg) launch_interface(s, sc.seg_a, sc.seg_b, grid.n, ctx->ctl, seg, iface);
   if (opts.min_volume > 0)

@@ -273,7 +273,8 @@ void launch_otsu(hipStream_t s, const uint32_t *hist, int64_t nvox, Ctl *ctl, in
 // phase maps of the majority passes are bit-packed: ceil(nx/32) words per
 // x-row; phase_bits_words gives the words of one map
 int64_t phase_bits_words(const int32_t nv[3]);
-// one length-term pass (same buffers and flags as launch_majority_pass)
+// one length-term pass (state p goes to buf[p & 1]; same flags as the
+// majority vote's)
 void launch_potts_pass(hipStream_t s, uint32_t *buf0, uint32_t *buf1, const uint32_t *gray,
                        const int32_t nv[3], double nu, int pass, Ctl *ctl);
 // k_ccl.hip: bubble filter on the byte phase map, then its interface
@@ -281,8 +282,10 @@ void launch_bubble_filter(hipStream_t s, const int32_t nv[3], int64_t min_volume
                           uint8_t *iface, int32_t *label, int32_t *size, uint32_t *status);
 void launch_threshold(hipStream_t s, const uint32_t *gray, const int32_t nv[3], double split,
                       const Ctl *ctl, uint32_t *bits0, int32_t *t_out);
-void launch_majority_pass(hipStream_t s, uint32_t *buf0, uint32_t *buf1, const int32_t nv[3],
-                          int pass, int max_passes, Ctl *ctl);
+// all passes of the majority vote: buf0 holds the initial map, final_phase_map
+// of (buf0, buf1) is the result; spare (spare_words entries): scratch
+void launch_majority(hipStream_t s, uint32_t *buf0, uint32_t *buf1, uint32_t *spare,
+                     int64_t spare_words, const int32_t nv[3], Ctl *ctl);
 // byte maps of the final phase and the interface
 void launch_interface(hipStream_t s, const uint32_t *buf0, const uint32_t *buf1,
                       const int32_t nv[3], const Ctl *ctl, uint8_t *seg, uint8_t *iface);

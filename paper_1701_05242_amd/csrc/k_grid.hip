@@ -479,6 +479,181 @@ __global__ __launch_bounds__(256) void k_majority(uint32_t *buf0, uint32_t *buf1
   }
 }
 
+// kMajBlock passes in one launch.  A workgroup holds kMajTile x kMajTile rows
+// (y, z) of the map, whole along x, and kMajBlock rows around them in LDS, in
+// the states of the last two passes; pass j is valid up to kMajBlock - j rows
+// outside the tile.  A word that changes marks its neighbourhood, and the next
+// pass evaluates the marked words only (the others have the same value in both
+// states); the first pass of the first launch evaluates all, and the second
+// launch starts from the words in which its two states differ.  Every pass
+// counts as run: after a fixed point the states stay, after a 2-cycle they
+// alternate, and the buffer in which the unblocked iteration would have left
+// its last map (final_phase_map) holds the same map.
+// in: state s, in_prev: state s - 1 (null in the first launch, s = 0); out and
+// out_prev: states s + kMajBlock and one before, in buffers of their own, since
+// neighbours read in.
+//
+// One pass per launch is bound by the launches, and on a large map by reading
+// 27 words for each of which hardly any changes: after the first pass 1 to 7%
+// of the words of a cylinder's, droplet's or slab's map have a changed
+// neighbour, after four passes under 2%.  All passes, a launch each (as traced,
+// and their launches took the host 74 us) and in two launches: 13 x 13 x 60
+// voxels 37 -> 12 us, 54 x 54 x 120 73 -> 18, 120^3 66 -> 27,
+// 200 x 100 x 100 77 -> 55, 160 x 160 x 400 91 -> 42 us.  (Tiles of 16 x 16
+// rows: 11, 22, 41, 103, 38 us.  Marks by block of 8 x 8 rows, or by row:
+// 23 to 26 us at 54 x 54 x 120.)
+constexpr int kMajBlock = 8;
+constexpr int kMajTile = 8;
+constexpr int kMajThreads = 1024;
+constexpr int kMajWords = 12;  // most words of a row
+
+// one full adder per bit: sum and carry
+__device__ __forceinline__ void full_add(uint32_t a, uint32_t b, uint32_t c, uint32_t &s,
+                                         uint32_t &m) {
+  s = a ^ b ^ c;
+  m = (a & b) | (c & (a ^ b));
+}
+
+// [window count >= 14] of the 32 voxels of the word at r, in rows of W words
+// and planes of plane words; kl, kr: offsets of the words left and right of it,
+// sl: bit of the left one next to this word, sr: bit of this word next to the
+// right one.  The 27 bits are added by 22 full adders, least weight first.
+__device__ __forceinline__ uint32_t majority_word(const uint32_t *r, int W, int plane, int kl,
+                                                  int kr, int sl, int sr) {
+  uint32_t h0[9], h1[9];
+#pragma unroll
+  for (int q = 0; q < 9; ++q) {
+    const uint32_t *p = r + (q / 3 - 1) * plane + (q % 3 - 1) * W;
+    const uint32_t w = p[0];
+    const uint32_t a = (w << 1) | ((p[kl] >> sl) & 1u), c = (w >> 1) | ((p[kr] & 1u) << sr);
+    full_add(a, w, c, h0[q], h1[q]);
+  }
+  uint32_t s[3], k[4], u;
+  full_add(h0[0], h0[1], h0[2], s[0], k[0]);
+  full_add(h0[3], h0[4], h0[5], s[1], k[1]);
+  full_add(h0[6], h0[7], h0[8], s[2], k[2]);
+  full_add(s[0], s[1], s[2], u, k[3]);  // u: weight 1, does not matter for >= 14
+  // weight 2: h1[0..8], k[0..3]
+  uint32_t t[4], q4[6];
+  full_add(h1[0], h1[1], h1[2], t[0], q4[0]);
+  full_add(h1[3], h1[4], h1[5], t[1], q4[1]);
+  full_add(h1[6], h1[7], h1[8], t[2], q4[2]);
+  full_add(k[0], k[1], k[2], t[3], q4[3]);
+  full_add(t[0], t[1], t[2], u, q4[4]);
+  uint32_t c1;
+  full_add(u, t[3], k[3], c1, q4[5]);
+  // weight 4: q4[0..5]
+  uint32_t e0, e1, f0, f1;
+  full_add(q4[0], q4[1], q4[2], e0, f0);
+  full_add(q4[3], q4[4], q4[5], e1, f1);
+  const uint32_t c2 = e0 ^ e1, f2 = e0 & e1;
+  uint32_t c3, c4;
+  full_add(f0, f1, f2, c3, c4);
+  return c4 | (c3 & c2 & c1);  // 16..27, or 14 and 15 (0111x)
+}
+
+__global__ __launch_bounds__(kMajThreads) void k_majority_block(
+    const uint32_t *__restrict__ in, const uint32_t *__restrict__ in_prev,
+    uint32_t *__restrict__ out, uint32_t *__restrict__ out_prev, int nx, int ny, int nz, int pass0,
+    Ctl *ctl) {
+  constexpr int T = kMajTile, S = T + 2 * kMajBlock;
+  static_assert(S <= 32, "a plane's rows have a bit each");
+  extern __shared__ uint32_t maj_lds[];  // [state][word of the row][z][y]
+  __shared__ uint32_t todo[3][kMajWords * S];  // [word][z]: bit y, of pass j in [j mod 3]
+  __shared__ uint32_t moved[3];                // any change of pass j, in [j mod 3]
+  __shared__ uint32_t chg;  // changes in the tile: bit j, from j - 1; j + 16, from j - 2
+  const int W = row_words(nx);
+  const int top = (nx - 1) & 31;
+  const uint32_t last_mask = (nx & 31) ? ((1u << (nx & 31)) - 1u) : 0xffffffffu;
+  constexpr int plane = S * S;
+  const int state = W * plane;
+  const int nty = (ny + T - 1) / T, tz = (int)blockIdx.x / nty;
+  const int y0 = ((int)blockIdx.x - tz * nty) * T - kMajBlock, z0 = tz * T - kMajBlock;
+  const int tid = threadIdx.x;
+  for (int e = tid; e < 3 * kMajWords * S; e += kMajThreads) (&todo[0][0])[e] = 0u;
+  if (tid < 3) moved[tid] = 0u;
+  if (tid == 3) chg = 0u;
+  // the words that pass j + 1 evaluates because the word (k, ry, rz) changed in
+  // pass j: its neighbourhood
+  auto mark = [&](uint32_t *next, int k, int ry, int rz) {
+    const uint32_t y3 = (7u << ry) >> 1;
+    const int kl = k == 0 ? W - 1 : k - 1, kr = k == W - 1 ? 0 : k + 1;
+#pragma unroll
+    for (int dz = -1; dz <= 1; ++dz) {
+      if (rz + dz < 0 || rz + dz >= S) continue;
+      atomicOr(&next[k * S + rz + dz], y3);
+      if (kl != k) atomicOr(&next[kl * S + rz + dz], y3);
+      if (kr != kl) atomicOr(&next[kr * S + rz + dz], y3);
+    }
+  };
+  if (in_prev) __syncthreads();  // todo cleared before it is marked
+  for (int e = tid; e < state; e += kMajThreads) {
+    const int k = e / plane, r = e - k * plane, rz = r / S, ry = r - rz * S;
+    const uint32_t src =
+        (uint32_t)((wrap_near(z0 + rz, nz) * ny + wrap_near(y0 + ry, ny)) * W + k);
+    const uint32_t v = in[src];
+    maj_lds[e] = v;
+    if (in_prev) {
+      const uint32_t p = in_prev[src];
+      maj_lds[state + e] = p;
+      if (p != v) mark(todo[1], k, ry, rz);
+    }
+  }
+  __syncthreads();
+  uint32_t seen = 0;
+  int third = 1;  // j mod 3
+  for (int j = 1; j <= kMajBlock; ++j) {
+    const uint32_t *cur = maj_lds + ((j - 1) & 1) * state;
+    uint32_t *nxt = maj_lds + (j & 1) * state;
+    const int next = third == 2 ? 0 : third + 1;
+    const bool all = j == 1 && !in_prev;
+    const uint32_t rows = (~0u << j) & (~0u >> (32 - S + j));  // valid in pass j
+    for (int e = tid; e < state; e += kMajThreads) {
+      const int kz = e / S, ry = e - kz * S, k = kz / S, rz = kz - k * S;
+      const uint32_t m = all ? ~0u : todo[third][kz];
+      if (!((m & rows) >> ry & 1u) || !(rows >> rz & 1u)) continue;
+      const bool first = k == 0, lastw = k == W - 1;
+      uint32_t nw = majority_word(cur + e, 1, S, (first ? W - 1 : -1) * plane,
+                                  (lastw ? 1 - W : 1) * plane, first ? top : 31,
+                                  lastw ? top : 31);
+      if (lastw) nw &= last_mask;
+      const uint32_t prev = cur[e], old = nxt[e];
+      nxt[e] = nw;
+      const bool mine = ry >= kMajBlock && ry < S - kMajBlock && rz >= kMajBlock &&
+                        rz < S - kMajBlock;
+      if (mine && nw != old && !all) seen |= 0x10000u << j;
+      if (nw != prev) {
+        if (mine) seen |= 1u << j;
+        moved[third] = 1u;
+        mark(todo[next], k, ry, rz);
+      }
+    }
+    __syncthreads();
+    if (moved[third] == 0u) break;
+    // read by pass j only, marked again by pass j + 2; read after pass j - 1
+    // only, set again by pass j + 2
+    for (int e = tid; e < W * S; e += kMajThreads) todo[third][e] = 0u;
+    if (tid == 0) moved[third == 0 ? 2 : third - 1] = 0u;
+    third = next;
+  }
+  if (seen) atomicOr(&chg, seen);
+  for (int e = tid; e < W * T * T; e += kMajThreads) {
+    const int k = e / (T * T), r = e - k * (T * T), rz = r / T + kMajBlock,
+              ry = r % T + kMajBlock;
+    const int gy = y0 + ry, gz = z0 + rz;
+    if (gy >= ny || gz >= nz) continue;
+    const int l = k * plane + rz * S + ry;
+    const uint32_t dst = (uint32_t)((gz * ny + gy) * W + k);
+    out[dst] = maj_lds[(kMajBlock & 1) * state + l];
+    out_prev[dst] = maj_lds[((kMajBlock - 1) & 1) * state + l];
+  }
+  __syncthreads();
+  if (tid >= 1 && tid <= kMajBlock) {
+    if (chg >> tid & 1u) ctl->maj_chg1[pass0 + tid] = 1u;
+    if (chg >> (tid + 16) & 1u) ctl->maj_chg2[pass0 + tid] = 1u;
+  }
+}
+
 // ------------------------------ length-term regularisation (4b', Eq. 4)
 // The two-phase piecewise-constant energy with a length term of weight nu,
 // sum_v (g_v - c_{s_v})^2 + nu * (differing 26-neighbour pairs), lowered by
@@ -575,14 +750,31 @@ int64_t phase_bits_words(const int32_t nv[3]) {
   return (int64_t)nv[1] * nv[2] * row_words(nv[0]);
 }
 
-void launch_majority_pass(hipStream_t s, uint32_t *buf0, uint32_t *buf1, const int32_t nv[3],
-                          int pass, int max_passes, Ctl *ctl) {
-  (void)max_passes;
-  int64_t b = ceil_div(phase_bits_words(nv), 256);
+// All passes of the majority vote.  Rows of more than kMajWords words (384
+// voxels) do not fit LDS with their surroundings, and take a launch per pass.
+// spare: a buffer of two maps (the gray values' has one on a grid one voxel
+// wide: a launch per pass).
+void launch_majority(hipStream_t s, uint32_t *buf0, uint32_t *buf1, uint32_t *spare,
+                     int64_t spare_words, const int32_t nv[3], Ctl *ctl) {
+  const int64_t words = phase_bits_words(nv);
+  const int W = row_words(nv[0]);
+  static_assert(kMajorityMaxPasses == 2 * kMajBlock, "back in the first buffers");
+  if (W <= kMajWords && spare_words >= 2 * words) {
+    constexpr int S = kMajTile + 2 * kMajBlock;
+    const dim3 g((unsigned)(ceil_div(nv[1], kMajTile) * ceil_div(nv[2], kMajTile)));
+    const size_t lds = 2 * sizeof(uint32_t) * (size_t)(S * S * W);
+    hipLaunchKernelGGL(k_majority_block, g, dim3(kMajThreads), lds, s, buf0, nullptr, spare,
+                       spare + words, nv[0], nv[1], nv[2], 0, ctl);
+    hipLaunchKernelGGL(k_majority_block, g, dim3(kMajThreads), lds, s, spare, spare + words, buf0,
+                       buf1, nv[0], nv[1], nv[2], kMajBlock, ctl);
+    return;
+  }
+  int64_t b = ceil_div(words, 256);
   if (b < 1) b = 1;
   if (b > 2048) b = 2048;
-  hipLaunchKernelGGL(k_majority, dim3((unsigned)b), dim3(256), 0, s, buf0, buf1, nv[0], nv[1],
-                     nv[2], pass, ctl);
+  for (int pass = 1; pass <= kMajorityMaxPasses; ++pass)
+    hipLaunchKernelGGL(k_majority, dim3((unsigned)b), dim3(256), 0, s, buf0, buf1, nv[0], nv[1],
+                       nv[2], pass, ctl);
 }
 
 // ------------------------------------------- interface marking (Fig. 4c)
