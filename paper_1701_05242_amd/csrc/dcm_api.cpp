@@ -130,7 +130,7 @@ dcm_status detect_enqueue(dcm_ctx *ctx, const double *x, const double *y, const 
     launch_bin_density(s, x, y, z, n, box.L, grid.n, sc3, sc.counts, ctx->d_status);
   }
   launch_gray_hist(s, sc.counts, sc.gray, grid.n, sc.hist, ctx->d_status);
-  if (opts.split <= 0.0) launch_otsu(s, sc.hist, nvox, ctx->ctl, threshold_out, ctx->d_status);
+  if (opts.split <= 0.0) launch_otsu(s, sc.hist, ctx->ctl, threshold_out, ctx->d_status);
   launch_threshold(s, sc.gray, grid.n, opts.split, ctx->ctl, sc.seg_a, threshold_out);
   if (opts.nu < 0.0)  // the gray values are not read again: the passes' scratch
     launch_majority(s, sc.seg_a, sc.seg_b, sc.gray, nvox, grid.n, ctx->ctl);

@@ -57,12 +57,10 @@ __device__ __forceinline__ const uint32_t *final_phase_map(const uint32_t *chg1,
                                                            const uint32_t *chg2, int max_passes,
                                                            const uint32_t *b0,
                                                            const uint32_t *b1) {
-  int last = max_passes;
-  for (int p = 1; p <= max_passes; ++p)
-    if (phase_pass_stopped(chg1, chg2, p)) {
-      last = p;
-      break;
-    }
+  int last = max_passes;  // (all flags are read at once: no chain of loads)
+#pragma unroll
+  for (int p = max_passes; p >= 1; --p)
+    if (phase_pass_stopped(chg1, chg2, p)) last = p;
   return (last & 1) ? b1 : b0;
 }
 

@@ -28,7 +28,7 @@ enum : uint32_t {
 };
 
 constexpr int kHistBins = 4096;       // gray values (27-window counts) must stay below this
-constexpr int kHistCopies = 32;      // histogram copies the gray-value workgroups add into
+constexpr int kHistCopies = 8;       // histogram copies the gray-value workgroups add into
 constexpr int kMajorityMaxPasses = 16;
 constexpr int kBatchQueues = 8;  // work-queue segments of the XCD-affine batched plan (one per XCD)
 constexpr int kPartialSlots = 8;      // per-block partial sums: E, W[6], pair count
@@ -268,7 +268,7 @@ void launch_bin_density(hipStream_t s, const double *x, const double *y, const d
                         uint32_t *counts, uint32_t *status);
 void launch_gray_hist(hipStream_t s, const uint32_t *counts, uint32_t *gray, const int32_t nv[3],
                       uint32_t *hist, uint32_t *status);
-void launch_otsu(hipStream_t s, const uint32_t *hist, int64_t nvox, Ctl *ctl, int32_t *t_out,
+void launch_otsu(hipStream_t s, const uint32_t *hist, Ctl *ctl, int32_t *t_out,
                  uint32_t *status);
 // phase maps of the majority passes are bit-packed: ceil(nx/32) words per
 // x-row; phase_bits_words gives the words of one map

@@ -75,7 +75,9 @@ extern "C" dcm_status dcm_detect_interface_noalloc(dcm_ctx *ctx, const double *x
   }
   if (!base) return fail(ctx, DCM_ERR_HIP, "no-allocation scratch was not set up on this device");
   // layout: histogram copies, gray values, phase maps, counts (if needed)
-  const size_t hist_b = align256((size_t)kHistCopies * kHistBins * sizeof(uint32_t));
+  // (the histogram's share is fixed, and with it the largest grid, at 32 copies)
+  static_assert(kHistCopies <= 32, "histogram copies past their share");
+  const size_t hist_b = align256((size_t)32 * kHistBins * sizeof(uint32_t));
   const size_t gray_b = align256((size_t)nvox * sizeof(uint32_t));
   const size_t map_b = align256((size_t)phase_bits_words(grid.n) * sizeof(uint32_t));
   const size_t counts_b = counts ? 0 : gray_b;

@@ -39,8 +39,8 @@ int64_t fsm_tile_count(const int32_t nv[3]) {
 // interface can a pass change anything at first (a liquid voxel with a source
 // face neighbour is itself an interface voxel).  Also clears the pass flags
 // and the tiles' stamps, which took a launch of their own before.  Bound by the
-// two fields it writes (39 us on the 160 x 160 x 400 grid, 4.2 TB/s; 64 us
-// beside the cell build, as before).
+// two fields it writes (39 us on the 160 x 160 x 400 grid, 4.2 TB/s; 50 to
+// 60 us beside the cell build).
 constexpr int kInitX = 64;
 struct FsmInit {
   int nx, ny, nz, ntx, nty;
@@ -52,10 +52,10 @@ struct FsmInit {
   int nflags;
 };
 
-// value(x, y, z, interface): whether the voxel is a source; interface set if
-// it is an interface voxel
-template <typename F>
-__device__ __forceinline__ void fsm_init_region(const FsmInit &p, F &&source) {
+// source(x, y, z, interface): whether the voxel is a source; interface set if
+// it is an interface voxel.  prepare: called by the whole workgroup first.
+template <typename P, typename F>
+__device__ __forceinline__ void fsm_init_region(const FsmInit &p, P &&prepare, F &&source) {
   __shared__ int has[kInitX / TX], lives[kInitX / TX];
   const int lx = threadIdx.x & (kInitX - 1), row = threadIdx.x / kInitX;
   const int x = blockIdx.x * kInitX + lx, y0 = blockIdx.y * TY, z0 = blockIdx.z * TZ;
@@ -64,9 +64,11 @@ __device__ __forceinline__ void fsm_init_region(const FsmInit &p, F &&source) {
   for (int64_t f = block * 256 + threadIdx.x; f < p.nflags;
        f += 256 * (int64_t)gridDim.x * gridDim.y * gridDim.z)
     p.flags[f] = 0u;
+  prepare();
   __syncthreads();
   bool any = false, inf = false;
   if (x < p.nx)
+#pragma unroll 4
     for (int r = row; r < TY * TZ; r += 256 / kInitX) {
       const int y = y0 + r % TY, z = z0 + r / TY;
       if (y >= p.ny || z >= p.nz) continue;
@@ -92,7 +94,7 @@ __device__ __forceinline__ void fsm_init_region(const FsmInit &p, F &&source) {
 
 __global__ __launch_bounds__(256) void k_fsm_init(const uint8_t *__restrict__ seg,
                                                   const uint8_t *__restrict__ iface, FsmInit p) {
-  fsm_init_region(p, [&](int x, int y, int z, bool &fc) {
+  fsm_init_region(p, [] {}, [&](int x, int y, int z, bool &fc) {
     const int64_t v = ((int64_t)z * p.ny + y) * p.nx + x;
     fc = iface[v] != 0;
     return seg[v] == 0 || fc;
@@ -102,24 +104,57 @@ __global__ __launch_bounds__(256) void k_fsm_init(const uint8_t *__restrict__ se
 // The same from the bit-packed phase maps of the regularisation passes
 // (final_phase_map), without the byte maps: a voxel starts at +inf iff it
 // and its six face neighbours (periodic) are all high density -- otherwise
-// it is low density or an interface voxel, a source.
+// it is low density or an interface voxel, a source.  Four threads per row of
+// the region form both masks of its 64 voxels, from whole words, in LDS: a look
+// at seven bits per voxel was a chain of loads per row, and the workgroups of a
+// small grid took 13 us for it.
 __global__ __launch_bounds__(256) void k_fsm_init_bits(const uint32_t *b0, const uint32_t *b1,
                                                        const Ctl *ctl, FsmInit p) {
-  const uint32_t *__restrict__ s =
-      final_phase_map(ctl->maj_chg1, ctl->maj_chg2, kMajorityMaxPasses, b0, b1);
+  __shared__ unsigned long long high[TY * TZ], inner[TY * TZ], parts[4][TY * TZ];
+  static_assert(kInitX == 64 && TY * TZ == 64, "two words a row, 64 rows, 4 threads a row");
   const int nx = p.nx, ny = p.ny, nz = p.nz, W = (nx + 31) >> 5;
-  auto bit = [&](int x, int y, int z) -> uint32_t {
-    return (s[((int64_t)z * ny + y) * W + (x >> 5)] >> (x & 31)) & 1u;
-  };
-  fsm_init_region(p, [&](int x, int y, int z, bool &fc) {
-    if (!bit(x, y, z)) return true;
-    const int xm = x == 0 ? nx - 1 : x - 1, xp = x + 1 == nx ? 0 : x + 1;
-    const int ym = y == 0 ? ny - 1 : y - 1, yp = y + 1 == ny ? 0 : y + 1;
-    const int zm = z == 0 ? nz - 1 : z - 1, zp = z + 1 == nz ? 0 : z + 1;
-    fc = (bit(xm, y, z) & bit(xp, y, z) & bit(x, ym, z) & bit(x, yp, z) & bit(x, y, zm) &
-          bit(x, y, zp)) == 0u;
-    return fc;
-  });
+  fsm_init_region(
+      p,
+      [&] {
+        const int r = threadIdx.x & 63, part = threadIdx.x >> 6;
+        const int y = blockIdx.y * TY + r % TY, z = blockIdx.z * TZ + r / TY;
+        if (y < ny && z < nz) {
+          const uint32_t *__restrict__ s =
+              final_phase_map(ctl->maj_chg1, ctl->maj_chg2, kMajorityMaxPasses, b0, b1);
+          const int k = blockIdx.x * 2;
+          auto row = [&](int yy, int zz) {
+            const uint32_t *q = s + ((int64_t)zz * ny + yy) * W + k;
+            return (unsigned long long)q[0] | (k + 1 < W ? (unsigned long long)q[1] << 32 : 0ull);
+          };
+          unsigned long long a;
+          if (part == 0) {
+            const uint32_t *own = s + ((int64_t)z * ny + y) * W;
+            const unsigned long long m = row(y, z);
+            // bits x - 1 and x + 1 at the place of x
+            const unsigned long long before =
+                k == 0 ? own[W - 1] >> ((nx - 1) & 31) & 1u : own[k - 1] >> 31;
+            unsigned long long after = m >> 1;
+            const int last = nx - 1 - k * 32;  // place of the row's last voxel
+            if (last < 64) after |= (unsigned long long)(own[0] & 1u) << last;
+            else after |= (unsigned long long)(own[k + 2] & 1u) << 63;
+            high[r] = m;
+            a = m & (m << 1 | before) & after;
+          } else if (part == 1) {
+            a = row(y == 0 ? ny - 1 : y - 1, z) & row(y + 1 == ny ? 0 : y + 1, z);
+          } else {
+            a = row(y, part == 2 ? (z == 0 ? nz - 1 : z - 1) : (z + 1 == nz ? 0 : z + 1));
+          }
+          parts[part][r] = a;
+        }
+        __syncthreads();
+        if (part == 0) inner[r] = parts[0][r] & parts[1][r] & parts[2][r] & parts[3][r];
+      },
+      [&](int x, int y, int z, bool &fc) {
+        const int r = (z % TZ) * TY + y % TY, b = x & (kInitX - 1);
+        const bool in = inner[r] >> b & 1ull;
+        fc = !in && (high[r] >> b & 1ull);
+        return !in;
+      });
 }
 
 // Godunov solve: with the smaller face neighbour a_k and spacing h_k per axis

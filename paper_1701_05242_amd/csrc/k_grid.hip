@@ -71,38 +71,48 @@ static dim3 stencil_grid(const int32_t nv[3]) {
 // --------------------------------------- gray value and histogram (Fig. 4b)
 // gray[v] = sum of counts over the periodic 3x3x3 window of v, and the
 // histogram of the gray values, in one pass.  A workgroup owns a 64 x 4
-// column of (x, y) outputs and marches through kGrayZ planes of z (32: fewer
-// workgroups merge fewer private histograms, measured 41 us against 50 us
-// for 16 and 47 us for 64 on the 160 x 160 x 400 grid): each plane
+// column of (x, y) outputs and marches through nzb planes of z (gray_planes):
+// each plane
 // of counts is staged in LDS with its one-voxel (x, y) halo and summed over
 // the 3 x 3 window of each output, and the sums of three consecutive planes
 // give the gray value of the middle one.  A plane is read once per column
 // (1.55 words per output with the halo) instead of three times.
 //
 // Histogram: a private LDS histogram per workgroup, merged once into one of
-// kHistCopies global copies (the split sums them).  The low-density phase puts most voxels into the first few
+// kHistCopies global copies (the split sums them).  The low-density phase puts
+// most voxels into the first few
 // bins: a lane counts those in registers and adds them to the LDS histogram
 // at the end; every other voxel takes one LDS atomic (lanes that hit the same
 // bin are serialised by the LDS itself).  Counts are exact integers, so the
 // histogram does not depend on the order of the additions.
-#ifndef DCM_GRAY_Z
-#define DCM_GRAY_Z 32
-#endif
-constexpr int kGrayZ = DCM_GRAY_Z;
 constexpr int kHistLow = 3;
+
+// Planes per workgroup: 32, or as many fewer (down to 4) as leave 512
+// workgroups.  Fewer workgroups merge fewer private histograms (160 x 160 x 400
+// grid: 41 us, against 50 us for 16 planes and 47 us for 64); on a grid of few
+// workgroups the planes, read one after the other, set the time: with 32 and
+// now, 13 x 13 x 60 voxels 18.7 and 7.7 us, 120^3 24 and 18 us, 200 x 100 x 100
+// 26 and 21 us.
+static int gray_planes(const int32_t nv[3]) {
+  const int64_t columns = ceil_div(nv[0], SX) * ceil_div(nv[1], SY);
+  int planes = 32;
+  while (planes > 4 && columns * ceil_div(nv[2], planes) < 512) planes /= 2;
+  return planes;
+}
 
 __global__ __launch_bounds__(SX * SY) void k_gray_hist(const uint32_t *__restrict__ counts,
                                                      uint32_t *__restrict__ gray, int nx, int ny,
-                                                     int nz, uint32_t *hist, uint32_t *status) {
+                                                     int nz, int nzb, uint32_t *hist,
+                                                     uint32_t *status) {
   __shared__ uint32_t plane[HY][HX];
   __shared__ uint32_t lh[kHistBins];
   const int tid = threadIdx.y * SX + threadIdx.x;
   for (int b = tid; b < kHistBins; b += SX * SY) lh[b] = 0u;
-  const int x0 = blockIdx.x * SX, y0 = blockIdx.y * SY, z0 = blockIdx.z * kGrayZ;
+  const int x0 = blockIdx.x * SX, y0 = blockIdx.y * SY, z0 = blockIdx.z * nzb;
   const int lx = threadIdx.x, ly = threadIdx.y;
   const int gx = x0 + lx, gy = y0 + ly;
   const bool mine = gx < nx && gy < ny;
-  const int zend = z0 + kGrayZ < nz ? z0 + kGrayZ : nz;
+  const int zend = z0 + nzb < nz ? z0 + nzb : nz;
   uint32_t low[kHistLow] = {0u, 0u, 0u};
   bool over = false;
   uint32_t s0 = 0u, s1 = 0u;  // 3 x 3 sums of the two planes before plane z
@@ -164,9 +174,9 @@ __global__ __launch_bounds__(SX * SY) void k_gray_hist(const uint32_t *__restric
 void launch_gray_hist(hipStream_t s, const uint32_t *counts, uint32_t *gray, const int32_t nv[3],
                       uint32_t *hist, uint32_t *status) {
   const dim3 g((unsigned)ceil_div(nv[0], SX), (unsigned)ceil_div(nv[1], SY),
-               (unsigned)ceil_div(nv[2], kGrayZ));
-  hipLaunchKernelGGL(k_gray_hist, g, dim3(SX, SY), 0, s, counts, gray, nv[0], nv[1], nv[2], hist,
-                     status);
+               (unsigned)ceil_div(nv[2], gray_planes(nv)));
+  hipLaunchKernelGGL(k_gray_hist, g, dim3(SX, SY), 0, s, counts, gray, nv[0], nv[1], nv[2],
+                     gray_planes(nv), hist, status);
 }
 
 // ------------------------------ two-phase split of the gray values (Eq. 4)
@@ -175,36 +185,31 @@ void launch_gray_hist(hipStream_t s, const uint32_t *counts, uint32_t *gray, con
 // S0^2/n0 + S1^2/n1 is largest (S, n: exact integer sum and count of each
 // phase); ties go to the smallest t.  One workgroup of 1024 threads owns 4
 // consecutive histogram bins each (summed over the histogram's copies).
+// One workgroup reads the whole set, so the loads' latency, not bandwidth, sets
+// the time: eight copies, read at once, and sums by wavefront instead of steps
+// over the workgroup take 7 us where 32 copies took 10 (the gray-value pass
+// adds into eight as fast: 42 us on the 160 x 160 x 400 grid).
 __global__ __launch_bounds__(1024) void k_otsu(const uint32_t *__restrict__ hist, Ctl *ctl,
                                                int32_t *t_out, uint32_t *status) {
-  __shared__ long long sc[1024];
-  __shared__ long long ss[1024];
-  __shared__ double bscore[1024];
-  __shared__ int bt[1024];
-  __shared__ long long best_n1, best_s1;
-  const int tid = threadIdx.x;
+  __shared__ long long wn[16], ws[16];
+  __shared__ double wscore[16];
+  __shared__ int wt[16];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int t0 = tid * 4;
   long long c[4], sm[4];
   long long lc = 0, ls = 0;
   // this thread's 4 bins summed over the copies (16-byte loads; a bin holds
   // at most the voxel count, below 2^31)
-  // (eight copies' loads in flight at a time: one workgroup reads the whole
-  // set, so the loads' latency, not bandwidth, sets the time; 14 us with
-  // one at a time, 11.8 with eight, 12.7 with sixteen)
-  static_assert(kHistCopies % 8 == 0, "copies are read eight at a time");
-  uint4 h = make_uint4(0u, 0u, 0u, 0u);
-  for (int k0 = 0; k0 < kHistCopies; k0 += 8) {
-    uint4 v[8];
+  uint4 h = make_uint4(0u, 0u, 0u, 0u), v[kHistCopies];
 #pragma unroll
-    for (int k = 0; k < 8; ++k)
-      v[k] = *reinterpret_cast<const uint4 *>(hist + (k0 + k) * kHistBins + t0);
+  for (int k = 0; k < kHistCopies; ++k)
+    v[k] = *reinterpret_cast<const uint4 *>(hist + k * kHistBins + t0);
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      h.x += v[k].x;
-      h.y += v[k].y;
-      h.z += v[k].z;
-      h.w += v[k].w;
-    }
+  for (int k = 0; k < kHistCopies; ++k) {
+    h.x += v[k].x;
+    h.y += v[k].y;
+    h.z += v[k].z;
+    h.w += v[k].w;
   }
   const uint32_t hv[4] = {h.x, h.y, h.z, h.w};
 #pragma unroll
@@ -214,21 +219,30 @@ __global__ __launch_bounds__(1024) void k_otsu(const uint32_t *__restrict__ hist
     lc += c[q];
     ls += sm[q];
   }
-  sc[tid] = lc;
-  ss[tid] = ls;
-  __syncthreads();
-  // inclusive suffix scan over threads: sc[tid] = sum over threads u >= tid
-  for (int off = 1; off < 1024; off <<= 1) {
-    long long vc = (tid + off < 1024) ? sc[tid + off] : 0;
-    long long vs = (tid + off < 1024) ? ss[tid + off] : 0;
-    __syncthreads();
-    sc[tid] += vc;
-    ss[tid] += vs;
-    __syncthreads();
+  // sums over the threads above this one: within the wavefront, then the
+  // wavefronts above
+  long long sn = lc, st = ls;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const long long on = __shfl_down(sn, off, 64), os = __shfl_down(st, off, 64);
+    if (lane + off < 64) {
+      sn += on;
+      st += os;
+    }
   }
-  const long long total_n = sc[0], total_s = ss[0];
-  long long above_n = (tid + 1 < 1024) ? sc[tid + 1] : 0;
-  long long above_s = (tid + 1 < 1024) ? ss[tid + 1] : 0;
+  if (lane == 0) {
+    wn[wave] = sn;
+    ws[wave] = st;
+  }
+  __syncthreads();
+  long long above_n = sn - lc, above_s = st - ls, total_n = 0, total_s = 0;
+#pragma unroll
+  for (int w = 0; w < 16; ++w) {
+    total_n += wn[w];
+    total_s += ws[w];
+    above_n += w > wave ? wn[w] : 0;
+    above_s += w > wave ? ws[w] : 0;
+  }
   double best = -1.0;
   int best_t = -1;
   long long n1q[4], s1q[4];
@@ -253,29 +267,41 @@ __global__ __launch_bounds__(1024) void k_otsu(const uint32_t *__restrict__ hist
       best_t = t;
     }
   }
-  bscore[tid] = best;
-  bt[tid] = best_t;
-  __syncthreads();
-  for (int off = 512; off > 0; off >>= 1) {
-    if (tid < off) {
-      double o = bscore[tid + off];
-      int ot = bt[tid + off];
-      bool take = (ot >= 0) && (bt[tid] < 0 || o > bscore[tid] ||
-                                (o == bscore[tid] && ot < bt[tid]));
-      if (take) {
-        bscore[tid] = o;
-        bt[tid] = ot;
-      }
+  // the best of all bins; of equal ones the smallest
+  auto better = [](double o, int ot, double b, int t) {
+    return ot >= 0 && (t < 0 || o > b || (o == b && ot < t));
+  };
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    const double o = __shfl_xor(best, off, 64);
+    const int ot = __shfl_xor(best_t, off, 64);
+    if (better(o, ot, best, best_t)) {
+      best = o;
+      best_t = ot;
     }
-    __syncthreads();
   }
-  const int T = bt[0];
-  if (T >= 0 && T >= t0 && T < t0 + 4) {
-    best_n1 = n1q[T - t0];
-    best_s1 = s1q[T - t0];
+  if (lane == 0) {
+    wscore[wave] = best;
+    wt[wave] = best_t;
   }
   __syncthreads();
-  if (tid == 0) {
+  int T = -1;
+  best = -1.0;
+  for (int w = 0; w < 16; ++w)
+    if (better(wscore[w], wt[w], best, T)) {
+      best = wscore[w];
+      T = wt[w];
+    }
+  // the thread that holds the bin (the first one if there is none) writes
+  const bool holds = T >= 0 ? T >= t0 && T < t0 + 4 : tid == 0;
+  long long best_n1 = 0, best_s1 = 0;
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+    if (t0 + q == T) {
+      best_n1 = n1q[q];
+      best_s1 = s1q[q];
+    }
+  if (holds) {
     int degenerate = 1;
     double c0 = 0.0, c1 = 0.0;
     if (T >= 0) {
@@ -294,9 +320,8 @@ __global__ __launch_bounds__(1024) void k_otsu(const uint32_t *__restrict__ hist
   }
 }
 
-void launch_otsu(hipStream_t s, const uint32_t *hist, int64_t nvox, Ctl *ctl, int32_t *t_out,
+void launch_otsu(hipStream_t s, const uint32_t *hist, Ctl *ctl, int32_t *t_out,
                  uint32_t *status) {
-  (void)nvox;
   hipLaunchKernelGGL(k_otsu, dim3(1), dim3(1024), 0, s, hist, ctl, t_out, status);
 }
 
