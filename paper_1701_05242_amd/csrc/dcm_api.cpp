@@ -500,7 +500,14 @@ dcm_status sweep_enqueue(dcm_ctx *ctx, const uint8_t *seg, const uint8_t *iface,
   // not ended by then (few tiles still change that late)
   const double hmin = std::min(grid.h[0], std::min(grid.h[1], grid.h[2]));
   const double enough = 6.0 + std::ceil(rc_grid / hmin);
-  const int own = tiled && enough < (double)max_waves ? (int)enough : max_waves;
+  // On a grid of at most 32 tiles one workgroup is soon as fast as launches
+  // that take the host 4.6 us each: six passes of their own, then its launch
+  // (twenty steps of 3,000 particles on 16 tiles, 14, 6, 4 and 3 passes: 3870,
+  // 3400, 3370, 3830 us; a droplet on 32 tiles 4100, 3440, 3980, 4670).  On 96
+  // tiles four passes cost ten steps of 20,000 particles, detected once, 74 us
+  // of 1012.
+  const double many = fsm_tile_count(grid.n) <= 32 ? std::min(enough, 6.0) : enough;
+  const int own = tiled && many < (double)max_waves ? (int)many : max_waves;
   auto passes = [&](int from, int to) {
     launch_fsm_step(s, ptr<double>(ctx->dA), ptr<double>(ctx->dB), tiles, grid.n, tiled,
                     maps == nullptr, grid.h, rc_grid, from, to, flags, max_waves);
