@@ -1114,13 +1114,13 @@ dcm_status dcm_step(dcm_ctx *ctx, double *x, double *y, double *z, double *vx, d
   auto owner = [&](int set) { return ptr<int32_t>(ctx->ws_owner[set]); };
   {
     double *src[] = {x, y, z, vx, vy, vz, fx, fy, fz};
-    const int nload = nsteps > 0 ? 9 : 3;
-    for (int k = 0; k < nload; ++k)
-      if (n > 0 && src[k] &&
-          hipMemcpyAsync(field(0, k), src[k], n * sizeof(double), hipMemcpyDeviceToDevice,
-                         s) != hipSuccess)
-        return fail(ctx, DCM_ERR_HIP, "dcm_step: copy into the working arrays failed");
-    launch_iota(s, owner(0), n);
+    PermFields f;
+    f.nf = nsteps > 0 ? 9 : 3;
+    for (int k = 0; k < f.nf; ++k) {
+      f.src[k] = src[k];
+      f.dst[k] = field(0, k);
+    }
+    launch_load_fields(s, f, owner(0), n);
   }
   double *W[WFIELDS];
   auto bind = [&]() {

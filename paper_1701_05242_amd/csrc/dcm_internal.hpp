@@ -592,7 +592,8 @@ struct PermFields {
   double *dst[kPermFields];
   int nf;
 };
-void launch_iota(hipStream_t s, int32_t *p, int64_t n);
+// dst_k[i] = src_k[i] for every field, owner[i] = i
+void launch_load_fields(hipStream_t s, const PermFields &f, int32_t *owner, int64_t n);
 void launch_permute_gather(hipStream_t s, const PermFields &f, const int32_t *perm,
                            const int32_t *owner_src, int32_t *owner_dst, int64_t n);
 void launch_permute_scatter(hipStream_t s, const PermFields &f, const int32_t *owner,

@@ -7,10 +7,23 @@
 
 namespace dcm {
 
-__global__ __launch_bounds__(256) void k_iota(int32_t *__restrict__ p, int64_t n) {
+// The working copies from the caller's arrays, dst_k[i] = src_k[i], and the
+// caller index of each slot, owner[i] = i, in one launch: nine copies and a
+// fill, 2 to 5 us each below a million particles, took the host ten launches
+// (46 us of a call).
+__global__ __launch_bounds__(256) void k_load_fields(PermFields f, int32_t *__restrict__ owner,
+                                                     int64_t n) {
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x)
-    p[i] = (int32_t)i;
+       i += (int64_t)gridDim.x * blockDim.x) {
+    double v[kPermFields];
+#pragma unroll
+    for (int k = 0; k < kPermFields; ++k)
+      if (k < f.nf) v[k] = f.src[k][i];
+#pragma unroll
+    for (int k = 0; k < kPermFields; ++k)
+      if (k < f.nf) f.dst[k][i] = v[k];
+    owner[i] = (int32_t)i;
+  }
 }
 
 // dst_k[s] = src_k[perm[s]] for every field, and the caller index carried
@@ -50,9 +63,9 @@ static unsigned grid_for(int64_t n) {
   return (unsigned)b;
 }
 
-void launch_iota(hipStream_t s, int32_t *p, int64_t n) {
+void launch_load_fields(hipStream_t s, const PermFields &f, int32_t *owner, int64_t n) {
   if (n <= 0) return;
-  hipLaunchKernelGGL(k_iota, dim3(grid_for(n)), dim3(256), 0, s, p, n);
+  hipLaunchKernelGGL(k_load_fields, dim3(grid_for(n)), dim3(256), 0, s, f, owner, n);
 }
 
 void launch_permute_gather(hipStream_t s, const PermFields &f, const int32_t *perm,
