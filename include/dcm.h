@@ -444,7 +444,8 @@ dcm_status dcm_set_batched_row_lists(dcm_ctx *ctx, int32_t entries);
 /* Record HIP events around every launch of the named kernel family
  * ("pair", "cells", "detect", "sweep", "cutoffs", "verlet"; "batch_cells",
  * "batch_pair" for the batched form, "batch_graph" for a replayed graph)
- * when enabled. */
+ * when enabled.  A step of dcm_step without detection assigns its cutoffs in
+ * the cell build's first pass, under "cells". */
 dcm_status dcm_set_profiling(dcm_ctx *ctx, int enable);
 
 /* While profiling, record events only around the launches of one kernel

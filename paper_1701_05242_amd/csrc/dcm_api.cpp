@@ -554,7 +554,17 @@ dcm_status dcm_assign_cutoffs(dcm_ctx *ctx, const double *x, const double *y, co
                         (double)grid.n[2] / box.L[2]};
   hipEvent_t ev;
   timer_begin(ctx, "cutoffs", &ev);
-  launch_assign_cutoffs(ctx->stream, x, y, z, n, box.L, grid.n, sc, dist, rule, delta, rc);
+  CutoffArgs a = {};
+  for (int k = 0; k < 3; ++k) {
+    a.L[k] = box.L[k];
+    a.nv[k] = grid.n[k];
+    a.sc[k] = sc[k];
+  }
+  a.rule = rule;
+  a.D = dist;
+  a.delta = delta;
+  a.rc = rc;
+  launch_assign_cutoffs(ctx->stream, x, y, z, n, a);
   timer_end(ctx, "cutoffs", ev);
   return check_launch(ctx, "dcm_assign_cutoffs");
 }
@@ -567,6 +577,8 @@ dcm_status dcm_build_cells(dcm_ctx *ctx, const double *x, const double *y, const
   // sorted records' cutoffs are written by the cutoff assignment)
   const bool no_rc = ctx->build_no_rc;
   ctx->build_no_rc = false;
+  const CutoffArgs *assign = ctx->build_assign;
+  ctx->build_assign = nullptr;
   ctx->list_n = -1;
   ctx->ext_src_ok = false;
   DCM_TRY(check_n(ctx, n));
@@ -712,7 +724,7 @@ dcm_status dcm_build_cells(dcm_ctx *ctx, const double *x, const double *y, const
   const double *rc_in = no_rc ? nullptr : rc;
   launch_cell_count(s, x, y, z, rc_in, n, box.L, nc, sc, rc_cap, cof, ptr<int32_t>(ctx->cell_slot),
                     ptr<int32_t>(ctx->cell_count), ptr<unsigned long long>(ctx->rcmax_part),
-                    ptr<uint32_t>(ctx->xkey), ctx->ctl, ctx->d_status);
+                    ptr<uint32_t>(ctx->xkey), ctx->ctl, ctx->d_status, assign);
   launch_cell_scan(s, ptr<int32_t>(ctx->cell_count), ptr<int32_t>(ctx->cell_start), ncell,
                    qtab ? ptr<uint32_t>(ctx->qword) : nullptr, ptr<int32_t>(ctx->scan_tmp));
   CellOrder o;
@@ -1223,17 +1235,32 @@ dcm_status dcm_step(dcm_ctx *ctx, double *x, double *y, double *z, double *vx, d
     // take the cutoffs
     if (prebuilt && hipStreamWaitEvent(s, ctx->join_ev, 0) != hipSuccess)
       return fail(ctx, DCM_ERR_HIP, "dcm_step: stream join failed");
-    {  // cutoffs (Section 2.2) from the field in the sweep's buffers; the
-       // distances are kept only when the caller asks for them
+    // cutoffs (Section 2.2) from the field in the sweep's buffers; the
+    // distances are kept only when the caller asks for them
+    CutoffArgs cut = {};
+    for (int k = 0; k < 3; ++k) {
+      cut.L[k] = box.L[k];
+      cut.nv[k] = grid.n[k];
+      cut.sc[k] = vsc[k];
+    }
+    cut.rule = rule;
+    cut.D = ptr<double>(ctx->dA);
+    cut.D2 = ptr<double>(ctx->dB);
+    cut.flags = ptr<uint32_t>(ctx->fsm_flags);
+    cut.max_steps = ctx->field_waves;
+    cut.cap = ctx->field_rc_grid;
+    cut.delta = delta ? W[WDELTA] : nullptr;
+    cut.rc = W[WRC];
+    cut.status = ctx->d_status;
+    // a build in line assigns them in its first pass (the edge tuner's builds
+    // read them)
+    const bool in_build = !prebuilt && step_cell_edge > 0.0;
+    if (!in_build) {
       hipEvent_t cev;
       timer_begin(ctx, "cutoffs", &cev);
-      launch_assign_cutoffs_sweep(s, W[WX], W[WY], W[WZ], n, box.L, grid.n, vsc,
-                                  ptr<double>(ctx->dA), ptr<double>(ctx->dB),
-                                  ptr<uint32_t>(ctx->fsm_flags), ctx->field_waves,
-                                  ctx->field_rc_grid, rule, delta ? W[WDELTA] : nullptr, W[WRC],
-                                  ctx->d_status,
-                                  prebuilt ? ptr<int32_t>(ctx->perm) : nullptr,
-                                  ptr<double4>(ctx->sorted), ctx->rc_bound);
+      launch_assign_cutoffs(s, W[WX], W[WY], W[WZ], n, cut,
+                            prebuilt ? ptr<int32_t>(ctx->perm) : nullptr,
+                            ptr<double4>(ctx->sorted), ctx->rc_bound);
       timer_end(ctx, "cutoffs", cev);
       DCM_TRY(check_launch(ctx, "dcm_step cutoffs"));
     }
@@ -1250,6 +1277,7 @@ dcm_status dcm_step(dcm_ctx *ctx, double *x, double *y, double *z, double *vx, d
       };
       DCM_TRY(tune_edge(ctx, edge_key, edge_cands, run, &step_cell_edge));
     }
+    if (in_build) ctx->build_assign = &cut;
     DCM_TRY(dcm_build_cells(ctx, W[WX], W[WY], W[WZ], W[WRC], n, box, step_cell_edge,
                             rule.rc_max, prec, nullptr, nullptr));
     return step_forces(DCM_EV_ENERGY, e_out ? e_out : scal);

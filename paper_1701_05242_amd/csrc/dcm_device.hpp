@@ -64,6 +64,20 @@ __device__ __forceinline__ const uint32_t *final_phase_map(const uint32_t *chg1,
   return (last & 1) ? b1 : b0;
 }
 
+// The distance sweep's last pass: the first of 1 .. max_steps that changed
+// nothing (flag 0), max_steps if none.  Every lane of the wavefront must call
+// it; 64 flags are read at once (one by one they were a chain of loads in every
+// workgroup).
+__device__ __forceinline__ int sweep_last_pass(const uint32_t *flags, int max_steps) {
+  const int lane = threadIdx.x & 63;
+  for (int base = 1; base <= max_steps; base += 64) {
+    const int q = base + lane;
+    const unsigned long long zero = __ballot(q <= max_steps && flags[q] == 0u);
+    if (zero) return base + __ffsll((long long)zero) - 1;
+  }
+  return max_steps;
+}
+
 __device__ __forceinline__ int wrap_index(int i, int n) {
   int r = i % n;
   return r < 0 ? r + n : r;

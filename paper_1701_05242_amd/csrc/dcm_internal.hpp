@@ -123,6 +123,7 @@ struct SysGeom {
 };
 
 struct BatchState;  // dcm_batch.cpp
+struct CutoffArgs;  // below
 
 }  // namespace dcm
 
@@ -204,6 +205,9 @@ struct dcm_ctx {
   // set for the next cell build: build without the cutoffs (the sorted
   // records' rc comes later, from the cutoff assignment); consumed by that build
   bool build_no_rc = false;
+  // set for the next cell build, which takes it first thing: assign the
+  // cutoffs in the build's first pass
+  const dcm::CutoffArgs *build_assign = nullptr;
   int batch_lists = 0;   // row-list variant asked for (0: tuned, 1: 14 entries, 2: 16)
   // profiling
   bool profile = false;
@@ -321,31 +325,38 @@ void launch_fsm_final(hipStream_t s, const double *dA, const double *dB, int64_t
                       int32_t *waves_out, uint32_t *status);
 
 // k_cells.hip
-// the same from the distance sweep's buffers (dA, dB) and pass flags, as
-// its final pass would have written the field (see launch_fsm_final); with
-// perm, for cells built without the cutoffs: the threads walk the sorted
-// slots and sorted[slot].w takes rc[perm[slot]] clamped to [0, rc_cap]
-// (out of range flagged)
-void launch_assign_cutoffs_sweep(hipStream_t s, const double *x, const double *y,
-                                 const double *z, int64_t n, const double L[3],
-                                 const int32_t nv[3], const double sc[3], const double *dA,
-                                 const double *dB, const uint32_t *flags, int max_steps,
-                                 double rc_grid, dcm_rule rule, double *delta, double *rc,
-                                 uint32_t *status, const int32_t *perm = nullptr,
-                                 double4 *sorted = nullptr, double rc_cap = 0.0);
+// Cutoff assignment: the distance field D on a grid of nv voxels (sc: voxels
+// per length), or (flags set) the sweep's two buffers D, D2 with its pass
+// flags, as its final pass would have written the field capped at `cap` (see
+// launch_fsm_final).
+struct CutoffArgs {
+  double L[3];
+  int32_t nv[3];
+  double sc[3];
+  dcm_rule rule;
+  const double *D, *D2;
+  const uint32_t *flags;
+  int max_steps;
+  double cap;
+  double *delta, *rc;  // outputs; delta null: not wanted
+  uint32_t *status;
+};
+// with perm, for cells built without the cutoffs (sweep form only): the
+// threads walk the sorted slots and sorted[slot].w takes rc[perm[slot]] clamped
+// to [0, rc_cap] (out of range flagged)
 void launch_assign_cutoffs(hipStream_t s, const double *x, const double *y, const double *z,
-                           int64_t n, const double L[3], const int32_t nv[3],
-                           const double sc[3], const double *dist, dcm_rule rule,
-                           double *delta, double *rc);
+                           int64_t n, const CutoffArgs &a, const int32_t *perm = nullptr,
+                           double4 *sorted = nullptr, double rc_cap = 0.0);
 // workgroups of the cell-count kernel: the size of its block_max scratch
 int64_t cell_count_blocks(int64_t n);
 // slot[i]: the particle's slot in its cell (arbitrary within it); cell_count
-// must be zero on entry, and ctl->big_cells is zeroed
+// must be zero on entry, and ctl->big_cells is zeroed.  assign (sweep form;
+// null: rc is read): the cutoffs are assigned in the same pass.
 void launch_cell_count(hipStream_t s, const double *x, const double *y, const double *z,
                        const double *rc, int64_t n, const double L[3], const int32_t nc[3],
                        const double sc[3], double rc_cap, int32_t *cell_of, int32_t *slot,
                        int32_t *cell_count, unsigned long long *block_max, uint32_t *xq, Ctl *ctl,
-                       uint32_t *status);
+                       uint32_t *status, const CutoffArgs *assign);
 void launch_exclusive_scan(hipStream_t s, const int32_t *in, int32_t *out, int64_t n,
                            int32_t *tmp);
 // cell starts from the counts, which are zeroed for the next build, as are

@@ -494,12 +494,7 @@ __global__ __launch_bounds__(256) void k_fsm_final(const double *dA, const doubl
                                                    const uint32_t *flags, int max_steps,
                                                    double *__restrict__ dist, int32_t *waves_out,
                                                    uint32_t *status) {
-  int last = max_steps;
-  for (int p = 1; p <= max_steps; ++p)
-    if (flags[p] == 0u) {
-      last = p;
-      break;
-    }
+  const int last = sweep_last_pass(flags, max_steps);
   const double *__restrict__ D = (last & 1) ? dB : dA;
   for (int64_t v = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; v < nvox;
        v += (int64_t)gridDim.x * blockDim.x) {
