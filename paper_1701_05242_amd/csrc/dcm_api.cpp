@@ -831,7 +831,8 @@ namespace {
 // current cell build
 dcm_status forces_impl(dcm_ctx *ctx, dcm_lj lj, int pair_rule, int prec, int ev_flags, double *fx,
                        double *fy, double *fz, double *energy, double *virial, int32_t *nnbr,
-                       uint64_t *npairs, bool use_list, bool alone = false) {
+                       uint64_t *npairs, bool use_list, bool alone = false,
+                       bool no_total = false) {
   if (!ctx) return DCM_ERR_INVALID;
   if (ctx->cell_n < 0) return fail(ctx, DCM_ERR_INVALID, "dcm_forces before dcm_build_cells");
   if (use_list && ctx->list_n != ctx->cell_n)
@@ -940,7 +941,8 @@ dcm_status forces_impl(dcm_ctx *ctx, dcm_lj lj, int pair_rule, int prec, int ev_
   if (n3)
     launch_n3_out(ctx->stream, a.n3_f, a.n3_cnt, a.perm, n, lj.epsilon, fx, fy, fz, a.nnbr,
                   ctx->d_status);
-  if (ev_flags & (DCM_EV_ENERGY | DCM_EV_VIRIAL | DCM_EV_COUNTS))
+  ctx->partial_rows = blocks;
+  if (!no_total && (ev_flags & (DCM_EV_ENERGY | DCM_EV_VIRIAL | DCM_EV_COUNTS)))
     launch_reduce_partials(ctx->stream, a.partials, blocks, lj.epsilon, ev_flags, energy, virial,
                            npairs);
   return check_launch(ctx, use_list ? "dcm_forces_list" : "dcm_forces");
@@ -1141,14 +1143,12 @@ dcm_status dcm_step(dcm_ctx *ctx, double *x, double *y, double *z, double *vx, d
   bind();
   // reorder the working copies into the order of the last cell build.  Only
   // the fields read before the next force pass rewrites them move: positions
-  // and velocities, and the forces when the next step opens with its own kick
-  // (an energy series is recorded); delta and rc are always recomputed.
+  // and velocities; forces, delta and rc are always recomputed.
   auto reorder = [&]() {
     PermFields f;
     f.nf = 0;
     for (int k = 0; k < WFIELDS; ++k) {
-      const bool force = k == WFX || k == WFY || k == WFZ;
-      if (k == WDELTA || k == WRC || (force && !energy_series)) continue;
+      if (k > WVZ) continue;
       f.src[f.nf] = field(cur, k);
       f.dst[f.nf] = field(1 - cur, k);
       ++f.nf;
@@ -1226,11 +1226,13 @@ dcm_status dcm_step(dcm_ctx *ctx, double *x, double *y, double *z, double *vx, d
   // the cells of this step were built beside the sweep (prebuild), and only
   // their records' cutoffs are missing
   bool prebuilt = false;
-  auto step_forces = [&](int ev_flags, double *e_out) -> dcm_status {
-    return forces_impl(ctx, lj, pair_rule, prec, ev_flags, W[WFX], W[WFY], W[WFZ], e_out, nullptr,
-                       nullptr, nullptr, false, true);
+  // the energies stay in the pass's partials: a step that records them sums
+  // them after its kick, with the kinetic energy
+  auto step_forces = [&](int ev_flags) -> dcm_status {
+    return forces_impl(ctx, lj, pair_rule, prec, ev_flags, W[WFX], W[WFY], W[WFZ], scal, nullptr,
+                       nullptr, nullptr, false, true, true);
   };
-  auto forces = [&](double *e_out) -> dcm_status {
+  auto forces = [&]() -> dcm_status {
     // cells built on the second stream: complete before their records
     // take the cutoffs
     if (prebuilt && hipStreamWaitEvent(s, ctx->join_ev, 0) != hipSuccess)
@@ -1266,21 +1268,21 @@ dcm_status dcm_step(dcm_ctx *ctx, double *x, double *y, double *z, double *vx, d
     }
     if (prebuilt) {
       prebuilt = false;
-      return step_forces(DCM_EV_ENERGY, e_out ? e_out : scal);
+      return step_forces(DCM_EV_ENERGY);
     }
     if (step_cell_edge <= 0.0) {
       auto run = [&](double e) -> dcm_status {
         DCM_TRY(dcm_build_cells(ctx, W[WX], W[WY], W[WZ], W[WRC], n, box, e, rule.rc_max, prec,
                                 nullptr, nullptr));
         // forces only (a kernel instance apart from the steps' energy passes)
-        return step_forces(0, nullptr);
+        return step_forces(0);
       };
       DCM_TRY(tune_edge(ctx, edge_key, edge_cands, run, &step_cell_edge));
     }
     if (in_build) ctx->build_assign = &cut;
     DCM_TRY(dcm_build_cells(ctx, W[WX], W[WY], W[WZ], W[WRC], n, box, step_cell_edge,
                             rule.rc_max, prec, nullptr, nullptr));
-    return step_forces(DCM_EV_ENERGY, e_out ? e_out : scal);
+    return step_forces(DCM_EV_ENERGY);
   };
   // Build the cells of a step on a second stream while the sweep runs on the
   // context's stream: the build reads only the positions, and the
@@ -1337,7 +1339,7 @@ dcm_status dcm_step(dcm_ctx *ctx, double *x, double *y, double *z, double *vx, d
   build_beside = prebuild;
   if (nsteps == 0) {
     DCM_TRY(detect());
-    DCM_TRY(forces(nullptr));
+    DCM_TRY(forces());
     return unload();
   }
   const double c = (0.5 * dt) / mass;
@@ -1355,31 +1357,33 @@ dcm_status dcm_step(dcm_ctx *ctx, double *x, double *y, double *z, double *vx, d
       DCM_TRY(detect());
     else
       binned = false;  // (never set for such a step)
-    DCM_TRY(forces(energy_series ? energy_series + 2 * (int64_t)st : nullptr));
+    DCM_TRY(forces());
     timer_begin(ctx, "verlet", &ev);
-    // without an energy series to record in between, the closing kick and
-    // the next step's opening kick and drift share one pass
-    drifted = !energy_series && st + 1 < nsteps;
-    // a next step with detection has its density counts binned here, from
-    // the new positions (the field exists from this step on)
-    const bool bin_next = drifted && (step0 + st + 2) % redetect_every == 0;
-    if (bin_next) {
-      DetectScratch sc;
-      DCM_TRY(detect_scratch(ctx, grid, nvox, dopts, nullptr, &sc));
-      launch_zero2_u32(s, sc.counts, nvox, sc.hist, (int64_t)kHistCopies * kHistBins);
-      launch_kick_kick_drift_bin(s, W[WX], W[WY], W[WZ], W[WVX], W[WVY], W[WVZ], W[WFX], W[WFY],
-                                 W[WFZ], n, c, dt, box.L, grid.n, vsc, sc.counts, ctx->d_status);
-      binned = true;
-    } else if (drifted) {
+    // the closing kick and the next step's opening kick and drift share one
+    // pass, which also sums the squares of the velocities in between for an
+    // energy series
+    drifted = st + 1 < nsteps;
+    double *ke = energy_series ? ptr<double>(ctx->ke) : nullptr;
+    if (drifted) {
+      // a next step with detection has its density counts binned here, from
+      // the new positions (the field exists from this step on)
+      uint32_t *counts = nullptr;
+      if ((step0 + st + 2) % redetect_every == 0) {
+        DetectScratch sc;
+        DCM_TRY(detect_scratch(ctx, grid, nvox, dopts, nullptr, &sc));
+        launch_zero2_u32(s, sc.counts, nvox, sc.hist, (int64_t)kHistCopies * kHistBins);
+        counts = sc.counts;
+        binned = true;
+      }
       launch_kick_kick_drift(s, W[WX], W[WY], W[WZ], W[WVX], W[WVY], W[WVZ], W[WFX], W[WFY],
-                             W[WFZ], n, c, dt, box.L);
+                             W[WFZ], n, c, dt, box.L, ke, grid.n, vsc, counts, ctx->d_status);
     } else {
-      launch_kick(s, W[WVX], W[WVY], W[WVZ], W[WFX], W[WFY], W[WFZ], n, c);
+      launch_kick(s, W[WVX], W[WVY], W[WVZ], W[WFX], W[WFY], W[WFZ], n, c, ke);
     }
     timer_end(ctx, "verlet", ev);
     if (energy_series)
-      launch_kinetic(s, W[WVX], W[WVY], W[WVZ], n, mass, ptr<double>(ctx->ke), kinetic_blocks(n),
-                     energy_series + 2 * (int64_t)st + 1);
+      launch_step_energies(s, ptr<double>(ctx->partials), ctx->partial_rows, ke, mass,
+                           energy_series + 2 * (int64_t)st);
     // keep the working copies in cell order: after the first build, then
     // every few steps (particles move little between steps)
     if (st + 1 < nsteps && (st == 0 || (st + 1) % kReorderEvery == 0)) {

@@ -157,6 +157,7 @@ struct dcm_ctx {
   // x trimming)
   dcm::DevBuf xkey, skey, qword, ext_sq;
   // candidates tested and rows visited by the last DCM_EV_COUNTS cell walk
+  int64_t partial_rows = 0;  // rows of partials that the last force pass wrote
   dcm::DevBuf walk;
   bool walk_valid = false;
   dcm::DevBuf sort_tmp, sort_list;  // large-cell sort: scratch entries and the cells' list
@@ -611,23 +612,24 @@ void launch_permute_scatter(hipStream_t s, const PermFields &f, const int32_t *o
                             int64_t n);
 
 // k_verlet.hip
+// ke (null: none): kinetic_blocks sums of v^2 after the kick (of the closing
+// kick); n may be 0
 void launch_kick(hipStream_t s, double *vx, double *vy, double *vz, const double *fx,
-                 const double *fy, const double *fz, int64_t n, double c);
+                 const double *fy, const double *fz, int64_t n, double c, double *ke);
+// counts (null: none): the next detection's density counts on the grid of nv
+// voxels, sc voxels per length (zeroed by the caller)
 void launch_kick_kick_drift(hipStream_t s, double *x, double *y, double *z, double *vx,
                             double *vy, double *vz, const double *fx, const double *fy,
-                            const double *fz, int64_t n, double c, double dt, const double L[3]);
+                            const double *fz, int64_t n, double c, double dt, const double L[3],
+                            double *ke, const int32_t *nv, const double *sc, uint32_t *counts,
+                            uint32_t *status);
 void launch_kick_drift(hipStream_t s, double *x, double *y, double *z, double *vx, double *vy,
                        double *vz, const double *fx, const double *fy, const double *fz,
                        int64_t n, double c, double dt, const double L[3]);
-// the same as launch_kick_kick_drift, and the next detection's density
-// counts of the new positions (counts zeroed beforehand)
-void launch_kick_kick_drift_bin(hipStream_t s, double *x, double *y, double *z, double *vx,
-                                double *vy, double *vz, const double *fx, const double *fy,
-                                const double *fz, int64_t n, double c, double dt,
-                                const double L[3], const int32_t nv[3], const double sc[3],
-                                uint32_t *counts, uint32_t *status);
-void launch_kinetic(hipStream_t s, const double *vx, const double *vy, const double *vz,
-                    int64_t n, double mass, double *partials, int64_t blocks, double *out);
+// out[0]: the pair energy from the force pass's partials (rows of them);
+// out[1]: the kinetic energy from the kick's
+void launch_step_energies(hipStream_t s, const double *pair, int64_t rows, const double *ke,
+                          double mass, double *out);
 int64_t kinetic_blocks(int64_t n);
 
 }  // namespace dcm
