@@ -156,8 +156,8 @@ struct dcm_ctx {
   // cell and (start, sub-cell word) of every extended cell (the pair walk's
   // x trimming)
   dcm::DevBuf xkey, skey, qword, ext_sq;
-  // candidates tested and rows visited by the last DCM_EV_COUNTS cell walk
   int64_t partial_rows = 0;  // rows of partials that the last force pass wrote
+  // candidates tested and rows visited by the last DCM_EV_COUNTS cell walk
   dcm::DevBuf walk;
   bool walk_valid = false;
   dcm::DevBuf sort_tmp, sort_list;  // large-cell sort: scratch entries and the cells' list
@@ -167,9 +167,10 @@ struct dcm_ctx {
   bool ext_src_ok = false;  // ext_src belongs to the current cell build
   dcm::DevBuf n3_f, n3_cnt;  // Newton's-third-law forces and counts in sorted order
   int64_t ext_cap = 0;             // particles ext_pos can hold
-  int32_t *h_ext_total = nullptr;  // pinned: ghost-extended count of the last build
-  // (complete with ext_event; the build's last scan writes it); it is kept for
-  // the next build of the same cell geometry (ext_key: cells, halo, n)
+  // pinned: ghost-extended count of the last build, which writes it; complete
+  // with ext_event, and kept for the next build of the same cell geometry
+  // (ext_key: cells, halo, n)
+  int32_t *h_ext_total = nullptr;
   hipEvent_t ext_event = nullptr;
   bool ext_copy_pending = false;
   int64_t ext_key[7] = {-1, -1, -1, -1, -1, -1, -1};
