@@ -304,6 +304,22 @@ __device__ __forceinline__ void scan_ranges(const uint2 (*segs)[kPairBlock], int
   }
 }
 
+// The same sums one candidate after the other: the second pass of the few lanes
+// that start over in the compact-record kernels, which have no registers to
+// spare for it (with scan_ranges there the batched kernel holds 163 instead of
+// 128 and one workgroup fewer: 1245 us instead of 1000 for 64 systems).
+template <int RULE, int PREC, int EVM>
+__device__ __forceinline__ void scan_again(const uint2 (*segs)[kPairBlock], int nseg,
+                                           const double4 *__restrict__ pos, int self, double xi,
+                                           double yi, double zi, double rci, double rci2,
+                                           double sig2, Acc<PREC> &acc, int &cnt) {
+  for (int q = 0; q < nseg; ++q) {
+    const uint2 sg = segs[q][threadIdx.x];
+    for (int j = (int)sg.x; j < (int)sg.y; ++j)
+      candidate<RULE, PREC, EVM>(pos[j], j, self, xi, yi, zi, rci, rci2, sig2, acc, cnt);
+  }
+}
+
 // Kernels that count the walk's candidates and rows (for dcm_walk_stats):
 // the compact-record ones in their pair-count instance, the others (which
 // always count pairs) whenever a counter buffer is passed.
@@ -592,8 +608,9 @@ __device__ __forceinline__ int sub_off(float p, const LaneGeo &g) {
 
 // Walk this lane's rows (fill a list, scan it, repeat) for a lane with run
 // set.  REL: compact records (FP32-mixed, own-cutoff rule); else the FP64
-// records.  CAP: the row capacity of segs.
-template <int RULE, int PREC, int EVM, bool REL, int CAP>
+// records.  CAP: the row capacity of segs.  AGAIN: the compact-record kernels'
+// pass over the FP64 records.
+template <int RULE, int PREC, int EVM, bool REL, int CAP, bool AGAIN = false>
 __device__ __forceinline__ void sweep_rows(const PairView &v, bool run, const LaneGeo &g,
                                            double sig2, uint2 (*segs)[kPairBlock],
                                            int32_t (*nearq)[kPairBlock], Acc<PREC> &acc,
@@ -771,6 +788,9 @@ __device__ __forceinline__ void sweep_rows(const PairView &v, bool run, const La
         acc.px = acc.py = acc.pz = 0.0f;
       } else if constexpr (RULE == DCM_PAIR_MAX_N3)
         scan_n3<PREC, EVM>(segs, nseg, v, g, sig2, acc, cnt);
+      else if constexpr (AGAIN)
+        scan_again<RULE, PREC, EVM>(segs, nseg, v.ext_pos, g.self, g.xi, g.yi, g.zi, g.rci,
+                                    g.rci2, sig2, acc, cnt);
       else {
         segs[nseg][lane_id] = make_uint2(0u, 0x7fffffffu);
         scan_ranges<RULE, PREC, EVM>(segs, steps, rs, g.self, g.xi, g.yi, g.zi, g.rci,
@@ -1068,8 +1088,8 @@ __device__ __forceinline__ void pair_block(const PairView &v, int64_t s, bool ac
         cnt = 0;
       }
       bool unused = false;
-      sweep_rows<RULE, PREC, EVM, false, CAP>(v, active && redo, g, sig2, segs, nearq, acc, cnt,
-                                              unused, wcand, wrows);
+      sweep_rows<RULE, PREC, EVM, false, CAP, true>(v, active && redo, g, sig2, segs, nearq, acc,
+                                                    cnt, unused, wcand, wrows);
     }
   }
   if constexpr (walk_counts<REL, EVM>()) {
