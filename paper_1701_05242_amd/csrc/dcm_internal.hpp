@@ -482,7 +482,11 @@ int64_t pair_blocks(int64_t n, int split_log);
 //     1555 1878
 //   FP64: 8, 6: 328 190 131 107 96; 99, 6: 364 245 216 198 216; 200, 4.5: 278
 //     230 206 221 236; 341, 8 (cylinder): 1581 1421 1285 1191 1270; 400, 4.5:
-//     413 340 316 343 389; 1200, 8: 1451 1245 1206 1229 1555
+//     413 340 316 343 389
+//   FP64, 500,000 and more, us per call at 1, 2, 4 lanes: steps 600, 6 (five):
+//     2673 2255 2253; 1200, 8 (ten): 14500 10753 11107; cells and forces 1000,
+//     8: 923 764 768; 1000, 4.2: 527 511 571; 2600, 8: 1772 1727 1853; forces on
+//     a list 1000, 8: 1320 1013 875; 1000, 4.2: 620 560 545
 //   64-system batch, compact: 1440 1516 1743 2319; FP64: 2106 2073 2243 2665
 // From 500,000 particles on, FP64 passes use one number everywhere, so
 // dcm_step's forces there are those of dcm_forces on the same cells.
@@ -493,7 +497,7 @@ inline int pair_split_log(int64_t n, double rc_max, int rule, bool compact, bool
     if (alone) return m < 16e3 ? 4 : (m < 150e3 ? 3 : (m < 300e3 ? 2 : (m < 3e6 ? 1 : 0)));
     return n < 8000 ? 2 : (n < 32000 ? 1 : 0);
   }
-  if (n >= 500000) return 2;
+  if (n >= 500000) return m < 450e3 ? 2 : 1;
   // (the symmetric rule walks every particle with the largest cutoff and
   // gains least from many lanes)
   if (alone && rule == DCM_PAIR_OWN) return m < 20e3 ? 4 : (m < 150e3 ? 3 : 2);

@@ -89,3 +89,34 @@ def test_list_and_batch_equal_single_calls(n, prec):
         dcm.dcm_forces_list(ctx, dcm.make_lj(), *f, prec=prec)
         assert dcm.dcm_sync_status(ctx) == dcm.DCM_OK
     np.testing.assert_array_equal(np.stack([host(t) for t in f], 1), one["F"])
+
+
+# 500,000 particles: two lanes with cutoffs up to 5, four with up to 8 (and two
+# at one particle fewer)
+@pytest.mark.parametrize("n,bound", [(499999, 8.0), (500000, 5.0), (500000, 8.0)])
+def test_half_a_million(n, bound):
+    print(f"[gpu] cell walk and list n={n} cutoffs up to {bound}", flush=True)
+    rng = np.random.default_rng(n)
+    m, box = 80, (90.0, 90.0, 90.0)
+    site = rng.permutation(m ** 3)[:n]
+    p = (np.stack(np.unravel_index(site, (m, m, m)), 1) + 0.5) * (90.0 / m)
+    p += rng.uniform(-0.1, 0.1, p.shape)
+    x, y, z = (np.ascontiguousarray(p[:, a]) for a in range(3))
+    rc = rng.uniform(2.5, bound, n)
+    idx = workloads.sample_indices(n, 400, seed=6)
+    ref = oracle.forces(x, y, z, rc, box, idx=idx)
+    d = [dev(a) for a in (x, y, z, rc)]
+    f, fl = ([torch.zeros(n, **F64) for _ in range(3)] for _ in range(2))
+    nn = torch.zeros(n, dtype=torch.int32, device=d[0].device)
+    with Ctx() as ctx:
+        dcm.dcm_build_cells(ctx, *d, box, 1.5, dcm.DCM_FP64, rc_bound=bound)
+        dcm.dcm_forces(ctx, dcm.make_lj(), *f, prec=dcm.DCM_FP64, ev_flags=dcm.DCM_EV_COUNTS,
+                       nnbr=nn)
+        dcm.dcm_build_list(ctx, 0.1)
+        dcm.dcm_forces_list(ctx, dcm.make_lj(), *fl, prec=dcm.DCM_FP64)
+        assert dcm.dcm_sync_status(ctx) == dcm.DCM_OK
+    F = np.stack([host(t) for t in f], 1)
+    np.testing.assert_array_equal(np.stack([host(t) for t in fl], 1), F)
+    np.testing.assert_array_equal(host(nn)[idx], ref["nnbr"])
+    R = np.stack([ref["fx"], ref["fy"], ref["fz"]], 1)
+    assert max(force_errors(F[idx], R)) <= 1e-12
