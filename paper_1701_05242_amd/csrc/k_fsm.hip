@@ -250,7 +250,7 @@ __device__ __forceinline__ double godunov(double a0, double a1, double a2, const
 // ------------------------------------------------------------- tiled sweep
 // Launch L reads buf[(L-1)&1] and writes buf[L&1] for its active tiles.
 // Active in the first launch are the tiles with an interface voxel and their
-// face neighbours (found from the init's flags); a tile that changes in launch
+// face neighbours (found from the init's flags, or listed by k_fsm_first); a tile that changes in launch
 // L puts itself, and the face neighbours next to a voxel that changed, on
 // launch L + 1's list (stamp: the last launch a tile was listed for).  live: tiles with a voxel that is not a
 // source; the others never run.  With last > launch the workgroup (there must
@@ -294,10 +294,32 @@ __device__ __forceinline__ int near_tile(const SweepTiles &w, int tx, int ty, in
   return (z * w.nty + y) * w.ntx + x;
 }
 
+// The first launch's list on a grid of more tiles than workgroups: without it
+// each workgroup looks through its share of the tiles, and the few whose share
+// holds two or three active ones set the time.
+__global__ __launch_bounds__(256) void k_fsm_first(SweepTiles w) {
+  const int ntiles = w.ntx * w.nty * w.ntz, t = (int)(blockIdx.x * 256 + threadIdx.x);
+  bool act = false;
+  if (t < ntiles) {
+    const int tx = t % w.ntx, tr = t / w.ntx, ty = tr % w.nty, tz = tr / w.nty;
+    int seen = 0;
+#pragma unroll
+    for (int k = 0; k < 7; ++k) seen |= w.first[near_tile(w, tx, ty, tz, k)];
+    act = seen != 0 && w.live[t] != 0;
+  }
+  const unsigned long long m = __ballot(act);
+  const int lane = threadIdx.x & 63;
+  uint32_t base = 0;
+  if (lane == 0 && m) base = atomicAdd(&w.count[1], (uint32_t)__popcll(m));
+  base = (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
+  if (act) w.list[1][base + (uint32_t)__popcll(m & ((1ull << lane) - 1ull))] = t;
+}
+
 template <bool ISO>
 __global__ __launch_bounds__(kTileThreads) void k_fsm_tiles(double *dA, double *dB, SweepTiles w,
                                                             SweepGeom g, int launch, int last,
-                                                            int max_sub, uint32_t *flags) {
+                                                            bool listed, int max_sub,
+                                                            uint32_t *flags) {
   constexpr int NT = kTileThreads, BX = TX / 4;
   static_assert(TY == 8 && TZ == 8, "two blocks of 4 along y and z");
   __shared__ double A[2][QZ * QY * QX];
@@ -321,7 +343,8 @@ __global__ __launch_bounds__(kTileThreads) void k_fsm_tiles(double *dA, double *
     double *dst = (launch & 1) ? dB : dA;
     // a pass runs only while the previous one changed something
     int entries = 0;
-    if (launch > 1) {
+    const bool from_list = launch > 1 || listed;
+    if (from_list) {
       entries = (int)__hip_atomic_load(&w.count[launch], __ATOMIC_RELAXED,
                                        __HIP_MEMORY_SCOPE_AGENT);
       if (entries == 0) return;
@@ -334,7 +357,7 @@ __global__ __launch_bounds__(kTileThreads) void k_fsm_tiles(double *dA, double *
     unsigned long long todo = 0ull;
     while (true) {
       int t;
-      if (launch > 1) {
+      if (from_list) {
         if (at_entry >= entries) break;
         t = __builtin_amdgcn_readfirstlane(w.list[launch & 1][at_entry]);
         at_entry += gridDim.x;
@@ -607,12 +630,20 @@ void launch_fsm_step(hipStream_t s, double *dA, double *dB, void *tiles, const i
     if (blocks > kFsmTileBlocks) blocks = kFsmTileBlocks;
     if (last > step) blocks = 1;
     const int subs = settle || step > kShortPasses ? kSettleSubWaves : kShortSubWaves;
+    // The list pays its launch (5 us) while a workgroup's share of the tiles is
+    // small: first pass of 1,800 tiles (droplet) 36 -> 18 us, 2,197 (cylinder)
+    // 36 -> 32; of 10,000 (slab) 35 -> 31, less than its cost.
+    const int64_t tiles_n = fsm_tile_count(nv);
+    const bool listed = step == 1 && tiles_n > kFsmTileBlocks && tiles_n <= 8 * kFsmTileBlocks;
+    if (listed)
+      hipLaunchKernelGGL(k_fsm_first, dim3((unsigned)ceil_div(tiles_n, 256)),
+                         dim3(256), 0, s, w);
     if (h[0] == h[1] && h[1] == h[2])
       hipLaunchKernelGGL(k_fsm_tiles<true>, dim3((unsigned)blocks), dim3(kTileThreads), 0, s, dA,
-                         dB, w, g, step, last, subs, flags);
+                         dB, w, g, step, last, listed, subs, flags);
     else
       hipLaunchKernelGGL(k_fsm_tiles<false>, dim3((unsigned)blocks), dim3(kTileThreads), 0, s, dA,
-                         dB, w, g, step, last, subs, flags);
+                         dB, w, g, step, last, listed, subs, flags);
   } else {
     int zb = nv[2] < 64 ? nv[2] : 64;
     hipLaunchKernelGGL(k_fsm_wave,

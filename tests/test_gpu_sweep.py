@@ -82,3 +82,23 @@ def test_sweep_along_a_cylinder(nv, hv):
             dcm.dcm_sweep_distance(ctx, dev(seg, torch.uint8), dev(iface, torch.uint8), grid, rcg,
                                    n - 1, dist2)
             assert dcm.dcm_sync_status(ctx) == dcm.DCM_ERR_NOT_CONVERGED
+
+
+# tiles of the first pass searched by the workgroups (512, 4352) and listed
+# beforehand (576, 4096)
+@pytest.mark.parametrize("nv", [(128, 64, 64), (129, 64, 64), (256, 128, 128), (257, 128, 128)])
+def test_first_pass_of_a_ball(nv):
+    print(f"[gpu] ball sweep {nv}", flush=True)
+    z, y, x = np.meshgrid(*(np.arange(k, dtype=np.float32) for k in nv[::-1]), indexing="ij")
+    r = np.sqrt((x - 20.3) ** 2 + (y - nv[1] / 2.0 + 0.3) ** 2 + (z - nv[2] / 2.0) ** 2)
+    seg = (r < 0.3 * nv[1]).astype(np.uint8).ravel()
+    iface = oracle.interface(nv, seg)
+    rcg = 8.0
+    D, _ = oracle.fsm(nv, (1.0, 1.0, 1.0), seg, iface, rcg)
+    grid = dcm.make_grid(tuple(float(k) for k in nv), 1.0)
+    dist = torch.zeros(int(np.prod(nv)), **F64)
+    with Ctx() as ctx:
+        dcm.dcm_sweep_distance(ctx, dev(seg, torch.uint8), dev(iface, torch.uint8), grid, rcg, 200,
+                               dist)
+        assert dcm.dcm_sync_status(ctx) == dcm.DCM_OK
+    bounded(host(dist), D, rcg)
