@@ -21,6 +21,11 @@ namespace dcm {
 
 constexpr int TX = 16, TY = 8, TZ = 8;                // tile
 constexpr int QX = TX + 2, QY = TY + 2, QZ = TZ + 2;  // with halo
+// LDS pitches of a row and a plane (doubles): the half wavefront that reads two
+// planes of a 4 x 4 x 4 block meets 64 different banks (without the padding
+// half of them twice: 2 to 3% of a pass)
+constexpr int PX = QX + 2, PXY = QY * PX + 8;
+static_assert(2 * PX % 64 == 40 && 2 * PXY % 64 == 32, "bank spread of a block");
 constexpr int kTileThreads = TX * TY * TZ;            // one voxel per thread
 constexpr int kTileWaves = kTileThreads / 64;
 
@@ -322,7 +327,7 @@ __global__ __launch_bounds__(kTileThreads) void k_fsm_tiles(double *dA, double *
                                                             uint32_t *flags) {
   constexpr int NT = kTileThreads, BX = TX / 4;
   static_assert(TY == 8 && TZ == 8, "two blocks of 4 along y and z");
-  __shared__ double A[2][QZ * QY * QX];
+  __shared__ double A[2][QZ * PXY];
   __shared__ unsigned int map[3];  // blocks changed by sub-waves 0, 1, 2 mod 3
   __shared__ unsigned int faces;   // the tile's faces (as near_tile) with a changed voxel
   __shared__ unsigned long long todo_s[kTileWaves];  // first launch: active tiles, 64 to a wavefront
@@ -332,7 +337,7 @@ __global__ __launch_bounds__(kTileThreads) void k_fsm_tiles(double *dA, double *
   // this thread's voxel in the tile, and its place in LDS
   const int bx = wave % BX, by = (wave / BX) & 1, bz = wave / (2 * BX);
   const int lx = bx * 4 + (lane & 3), ly = by * 4 + ((lane >> 2) & 3), lz = bz * 4 + (lane >> 4);
-  const int at = ((lz + 1) * QY + ly + 1) * QX + lx + 1;
+  const int at = (lz + 1) * PXY + (ly + 1) * PX + lx + 1;
   // this wavefront's block and its face neighbours
   const unsigned int near = (1u << wave) | (bx > 0 ? 1u << (wave - 1) : 0u) |
                             (bx + 1 < BX ? 1u << (wave + 1) : 0u) |
@@ -404,8 +409,9 @@ __global__ __launch_bounds__(kTileThreads) void k_fsm_tiles(double *dA, double *
         // (far outside a thin grid only behind its own halo: never read)
         if (gx >= g.nx || gy >= g.ny || gz >= g.nz) continue;
         const double v = src[((int64_t)gz * g.ny + gy) * g.nx + gx];
-        A[0][e] = v;
-        A[1][e] = v;
+        const int l = ez * PXY + ey * PX + ex;
+        A[0][l] = v;
+        A[1][l] = v;
       }
       if (tid < 3) map[tid] = 0u;
       if (tid == 3) faces = 0u;
@@ -420,8 +426,8 @@ __global__ __launch_bounds__(kTileThreads) void k_fsm_tiles(double *dA, double *
           bool c = false;
           if (d != 0.0) {
             const double ax = fmin(in[at - 1], in[at + 1]);
-            const double ay = fmin(in[at - QX], in[at + QX]);
-            const double az = fmin(in[at - QX * QY], in[at + QX * QY]);
+            const double ay = fmin(in[at - PX], in[at + PX]);
+            const double az = fmin(in[at - PXY], in[at + PXY]);
             if (fmin(fmin(ax, ay), az) < d) {
               const double v = godunov<ISO>(ax, ay, az, g);
               c = v < d && v <= g.rc_grid;
@@ -604,8 +610,13 @@ void launch_fsm_init_bits(hipStream_t s, const uint32_t *const maps[2], const Ct
   hipLaunchKernelGGL(k_fsm_init_bits, grid, dim3(256), 0, s, maps[0], maps[1], ctl, p);
 }
 
-// Workgroups of a tiled pass, each walking tiles in turn: what the chip holds.
-constexpr int64_t kFsmTileBlocks = 512;
+// Workgroups of a tiled pass, each walking tiles in turn: one per compute unit.
+// Two share its units without gaining on latency (and crowd the cell build that
+// runs beside a step's sweep): with 512 and 256, ms per step of the 2.6 million
+// slab 1.755 and 1.710, of the cylinder 0.975 and 0.934, of the droplet 0.425
+// and 0.418.
+constexpr int64_t kFsmTileBlocks = 256;
+constexpr int64_t kFsmListedTiles = 4096;
 
 // Sub-waves of a pass.  settle: until the tile has settled, at most
 // kSettleSubWaves.  Else the first kShortPasses passes take kShortSubWaves:
@@ -634,7 +645,7 @@ void launch_fsm_step(hipStream_t s, double *dA, double *dB, void *tiles, const i
     // small: first pass of 1,800 tiles (droplet) 36 -> 18 us, 2,197 (cylinder)
     // 36 -> 32; of 10,000 (slab) 35 -> 31, less than its cost.
     const int64_t tiles_n = fsm_tile_count(nv);
-    const bool listed = step == 1 && tiles_n > kFsmTileBlocks && tiles_n <= 8 * kFsmTileBlocks;
+    const bool listed = step == 1 && tiles_n > kFsmTileBlocks && tiles_n <= kFsmListedTiles;
     if (listed)
       hipLaunchKernelGGL(k_fsm_first, dim3((unsigned)ceil_div(tiles_n, 256)),
                          dim3(256), 0, s, w);

@@ -84,9 +84,10 @@ def test_sweep_along_a_cylinder(nv, hv):
             assert dcm.dcm_sync_status(ctx) == dcm.DCM_ERR_NOT_CONVERGED
 
 
-# tiles of the first pass searched by the workgroups (512, 4352) and listed
-# beforehand (576, 4096)
-@pytest.mark.parametrize("nv", [(128, 64, 64), (129, 64, 64), (256, 128, 128), (257, 128, 128)])
+# tiles of the first pass searched by the workgroups (256, 4352) and listed
+# beforehand (320, 512, 4096)
+@pytest.mark.parametrize("nv", [(64, 64, 64), (65, 64, 64), (128, 64, 64), (256, 128, 128),
+                                (257, 128, 128)])
 def test_first_pass_of_a_ball(nv):
     print(f"[gpu] ball sweep {nv}", flush=True)
     z, y, x = np.meshgrid(*(np.arange(k, dtype=np.float32) for k in nv[::-1]), indexing="ij")
