@@ -129,7 +129,7 @@ __device__ __forceinline__ void scan_by_block(const int32_t *in, int64_t n, int3
 // entries by (x key, caller index) so the layout (and every FP sum) is
 // reproducible and each cell's particles are in x order.  Cells of at most
 // kSmallCell entries are ranked one thread per particle (k_cell_rank);
-// larger cells go to a list that whole workgroups sort (k_cell_sort_big).
+// larger cells go to a list that whole workgroups sort (sort_big_cells).
 constexpr int kSmallCell = 32;
 constexpr int kSortChunk = 4096;  // entries a workgroup sorts at once in LDS
 constexpr int kBigSortBlocks = 256;

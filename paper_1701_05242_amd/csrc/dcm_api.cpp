@@ -1175,7 +1175,7 @@ dcm_status dcm_step(dcm_ctx *ctx, double *x, double *y, double *z, double *vx, d
     return check_launch(ctx, "dcm_step");
   };
   // sweep passes stop early once one changes nothing; the limit only bounds
-  // them (those past the first few dozen share one launch)
+  // them (those past the first dozen share one launch)
   const int32_t max_waves = 1024;
   double *scal = ptr<double>(ctx->scalars);
   const dcm_detect_opts dopts = {0.0, -1.0, 0};

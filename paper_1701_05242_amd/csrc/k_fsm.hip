@@ -272,9 +272,9 @@ __device__ __forceinline__ double godunov(double a0, double a1, double a2, const
 // active tiles evenly over the workgroups.
 // Sweep of a step, all passes, before (256 threads solving a 16 x 8 x 8 tile's
 // 1024 voxels in every sub-wave, the active tiles found by a look at all 26
-// neighbours of every tile) and after: 120^3 grid, droplet 326 -> 181 us;
-// 200 x 100 x 100, cylinder 419 -> 299 us; 160 x 160 x 400 settled (64 passes
-// launched, then 15) 354 -> 211 us.
+// neighbours of every tile) and after: 120^3 grid, droplet 326 -> 160 us;
+// 200 x 100 x 100, cylinder 419 -> 285 us; 160 x 160 x 400 settled (64 passes
+// launched, then 15) 354 -> 225 us.
 struct SweepTiles {
   int ntx, nty, ntz;
   const uint8_t *first, *live;
