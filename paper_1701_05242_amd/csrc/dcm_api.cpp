@@ -50,12 +50,32 @@ dcm_status ensure(dcm_ctx *ctx, DevBuf &b, size_t bytes) {
   return DCM_OK;
 }
 
-dcm_status ensure_zeroed(dcm_ctx *ctx, DevBuf &b, size_t bytes) {
+dcm_status ensure(dcm_ctx *ctx, CountBuf &b, size_t bytes) {
   const size_t before = b.cap;
-  const dcm_status st = ensure(ctx, b, bytes);
-  if (st == DCM_OK && b.cap != before)
-    launch_fill_u32(ctx->stream, static_cast<uint32_t *>(b.p), 0u, (int64_t)(b.cap / 4));
+  const dcm_status st = ensure(ctx, static_cast<DevBuf &>(b), bytes);
+  if (b.cap != before) b.zero = false;
   return st;
+}
+
+void counts_begin(dcm_ctx *ctx, CountBuf &b, bool capturing) {
+  if (capturing || !b.zero)
+    launch_fill_u32(ctx->stream, static_cast<uint32_t *>(b.p), 0u, (int64_t)(b.cap / 4));
+  if (!capturing) b.zero = false;
+}
+
+void counts_end(CountBuf &b, bool capturing) {
+  // (an error that an earlier call left also keeps the flag down: one more
+  // clearing launch, no harm)
+  if (!capturing) b.zero = hipPeekAtLastError() == hipSuccess;
+}
+
+bool stream_capturing(hipStream_t s) {
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &capture) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return capture != hipStreamCaptureStatusNone;
 }
 
 dcm_status check_launch(dcm_ctx *ctx, const char *what) {
@@ -631,7 +651,7 @@ dcm_status dcm_build_cells(dcm_ctx *ctx, const double *x, const double *y, const
     ncell *= nc[a];
   }
   if (ncell >= (int64_t(1) << 30)) return fail(ctx, DCM_ERR_RANGE, "too many cells");
-  DCM_TRY(ensure_zeroed(ctx, ctx->cell_count, ncell * sizeof(int32_t)));
+  DCM_TRY(ensure(ctx, ctx->cell_count, ncell * sizeof(int32_t)));
   DCM_TRY(ensure(ctx, ctx->cell_slot, std::max<int64_t>(n, 1) * sizeof(int32_t)));
   DCM_TRY(ensure(ctx, ctx->cell_start, (ncell + 1) * sizeof(int32_t)));
   DCM_TRY(ensure(ctx, ctx->scan_tmp, scan_tmp_elems(ncell) * sizeof(int32_t)));
@@ -673,12 +693,7 @@ dcm_status dcm_build_cells(dcm_ctx *ctx, const double *x, const double *y, const
   // between builds, else this build's own count, read back before the
   // images are written.  A stream being captured into a graph cannot wait:
   // it keeps the uniform-density estimate, the overflow is flagged.
-  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(ctx->stream, &capture) != hipSuccess) {
-    (void)hipGetLastError();
-    capture = hipStreamCaptureStatusNone;
-  }
-  const bool capturing = capture != hipStreamCaptureStatusNone;
+  const bool capturing = stream_capturing(ctx->stream);
   const int64_t key[7] = {nc[0], nc[1], nc[2], halo[0], halo[1], halo[2], n};
   const bool same_geom = std::equal(key, key + 7, ctx->ext_key);
   if (ctx->ext_copy_pending && !capturing) {
@@ -722,11 +737,13 @@ dcm_status dcm_build_cells(dcm_ctx *ctx, const double *x, const double *y, const
   hipEvent_t ev;
   timer_begin(ctx, "cells", &ev);
   const double *rc_in = no_rc ? nullptr : rc;
+  counts_begin(ctx, ctx->cell_count, capturing);
   launch_cell_count(s, x, y, z, rc_in, n, box.L, nc, sc, rc_cap, cof, ptr<int32_t>(ctx->cell_slot),
                     ptr<int32_t>(ctx->cell_count), ptr<unsigned long long>(ctx->rcmax_part),
                     ptr<uint32_t>(ctx->xkey), ctx->ctl, ctx->d_status, assign);
   launch_cell_scan(s, ptr<int32_t>(ctx->cell_count), ptr<int32_t>(ctx->cell_start), ncell,
                    qtab ? ptr<uint32_t>(ctx->qword) : nullptr, ptr<int32_t>(ctx->scan_tmp));
+  counts_end(ctx->cell_count, capturing);
   CellOrder o;
   o.n = n;
   for (int a = 0; a < 3; ++a) {

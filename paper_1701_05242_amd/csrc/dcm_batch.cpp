@@ -54,7 +54,8 @@ struct BatchState {
          table_bytes = 0;
   std::vector<unsigned char> table_host;
   // device memory
-  DevBuf tables, cell_of, cell_count, cell_slot, cell_start, perm, sorted, scan_tmp, row_count,
+  CountBuf cell_count;
+  DevBuf tables, cell_of, cell_slot, cell_start, perm, sorted, scan_tmp, row_count,
       row_start, row_lo, ext_start, ext_pos, ext_rel, partials, rcmax, rcmax_part, head,
       sort_tmp, sort_list, xkey, skey, qword, ext_sq;
   // recorded graph
@@ -274,8 +275,7 @@ dcm_status make_plan(dcm_ctx *ctx, BatchState &B, double edge, int queues, dcm_l
   if ((st = ensure(ctx, B.tables, B.table_bytes)) != DCM_OK) return st;
   if ((st = ensure(ctx, B.cell_of, sizeof(int32_t) * std::max<int64_t>(B.n_total, 1))) != DCM_OK)
     return st;
-  if ((st = ensure_zeroed(ctx, B.cell_count, sizeof(int32_t) * B.cells_total)) != DCM_OK)
-    return st;
+  if ((st = ensure(ctx, B.cell_count, sizeof(int32_t) * B.cells_total)) != DCM_OK) return st;
   if ((st = ensure(ctx, B.cell_slot, sizeof(int32_t) * std::max<int64_t>(B.n_total, 1))) != DCM_OK)
     return st;
   if ((st = ensure(ctx, B.cell_start, sizeof(int32_t) * (B.cells_total + 1))) != DCM_OK) return st;
@@ -326,7 +326,8 @@ dcm_status make_plan(dcm_ctx *ctx, BatchState &B, double edge, int queues, dcm_l
   return DCM_OK;
 }
 
-// Enqueue the whole batch on stream s (no allocation, no host sync).
+// Enqueue the whole batch on stream s (no allocation, no host sync), with the
+// cells' counters at zero (counts_begin).
 void enqueue(dcm_ctx *ctx, BatchState &B, hipStream_t s, dcm_lj lj, int rule, int prec,
              int ev_flags, bool timed) {
   const int32_t nsys = (int32_t)B.desc.size();
@@ -401,6 +402,15 @@ void enqueue(dcm_ctx *ctx, BatchState &B, hipStream_t s, dcm_lj lj, int rule, in
   if (timed) timer_end(ctx, "batch_pair", ev);
 }
 
+// The same as a call on the context's stream.
+void enqueue_call(dcm_ctx *ctx, BatchState &B, dcm_lj lj, int rule, int prec, int ev_flags,
+                  bool timed) {
+  const bool capturing = stream_capturing(ctx->stream);
+  counts_begin(ctx, B.cell_count, capturing);
+  enqueue(ctx, B, ctx->stream, lj, rule, prec, ev_flags, timed);
+  counts_end(B.cell_count, capturing);
+}
+
 // Time the batch at each candidate edge, work-queue layout (one queue in
 // cost order, or one per XCD) and, for the compact-record kernel, row-list
 // variant (second of two runs each) and keep the fastest.  Synchronises the
@@ -426,9 +436,9 @@ dcm_status tune(dcm_ctx *ctx, BatchState &B, dcm_lj lj, int rule, int prec, int 
     const int queues = ctx->batch_queues ? ctx->batch_queues : (iq ? kBatchQueues : 1);
     if (il == 0 && (st = make_plan(ctx, B, edge, queues, lj, rule, prec)) != DCM_OK) break;
     B.row_lists = ctx->batch_lists ? ctx->batch_lists - 1 : il;
-    enqueue(ctx, B, ctx->stream, lj, rule, prec, ev_flags, false);
+    enqueue_call(ctx, B, lj, rule, prec, ev_flags, false);
     const hipError_t r0 = hipEventRecord(e0, ctx->stream);
-    enqueue(ctx, B, ctx->stream, lj, rule, prec, ev_flags, false);
+    enqueue_call(ctx, B, lj, rule, prec, ev_flags, false);
     const hipError_t r1 = hipEventRecord(e1, ctx->stream);
     if ((st = check_launch(ctx, "dcm_forces_batched (tuning)")) != DCM_OK) break;
     float ms = 0.0f;
@@ -540,7 +550,7 @@ dcm_status dcm_forces_batched(dcm_ctx *ctx, int32_t nsys, const dcm_system *sys,
     }
   }
   if (!use_graph) {
-    enqueue(ctx, B, ctx->stream, lj, pair_rule, prec, ev_flags, ctx->profile);
+    enqueue_call(ctx, B, lj, pair_rule, prec, ev_flags, ctx->profile);
     return check_launch(ctx, "dcm_forces_batched");
   }
   std::vector<unsigned char> key = graph_key(B, lj, pair_rule, prec, ev_flags);
@@ -570,10 +580,13 @@ dcm_status dcm_forces_batched(dcm_ctx *ctx, int32_t nsys, const dcm_system *sys,
   }
   hipEvent_t ev = nullptr;
   timer_begin(ctx, "batch_graph", &ev);
+  const bool capturing = stream_capturing(ctx->stream);
+  counts_begin(ctx, B.cell_count, capturing);
   if (hipGraphLaunch(B.exec, ctx->stream) != hipSuccess) {
     (void)hipGetLastError();
     return fail(ctx, DCM_ERR_HIP, "dcm_forces_batched: graph launch failed");
   }
+  counts_end(B.cell_count, capturing);
   timer_end(ctx, "batch_graph", ev);
   return check_launch(ctx, "dcm_forces_batched");
 }

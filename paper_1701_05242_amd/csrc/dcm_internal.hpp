@@ -91,6 +91,14 @@ struct DevBuf {
   }
 };
 
+// Per-cell counters of a cell build.  The build's count needs them at zero and
+// its scan zeroes them again, so a build clears them itself only when it cannot
+// know that the last one got so far: `zero` is set between builds that were
+// enqueued whole.
+struct CountBuf : DevBuf {
+  bool zero = false;
+};
+
 struct Timer {
   double ms = 0.0;
   int64_t launches = 0;
@@ -151,7 +159,8 @@ struct dcm_ctx {
   dcm::DevBuf delta, rc, partials, ke, scalars;
   dcm::DevBuf tune_f;  // forces of the cell-edge tuner's trial passes (dcm_build_cells)
   // cells
-  dcm::DevBuf cell_of, cell_count, cell_start, cell_slot, perm, sorted, scan_tmp, rcmax_part;
+  dcm::CountBuf cell_count;
+  dcm::DevBuf cell_of, cell_start, cell_slot, perm, sorted, scan_tmp, rcmax_part;
   // x key of every particle (within-cell order), sub-cell word of every real
   // cell and (start, sub-cell word) of every extended cell (the pair walk's
   // x trimming)
@@ -249,8 +258,18 @@ dcm_status noalloc_scratch_setup(int device, std::string *err);
 // ---- context helpers (dcm_api.cpp)
 dcm_status fail(dcm_ctx *ctx, dcm_status code, const std::string &msg);
 dcm_status ensure(dcm_ctx *ctx, DevBuf &b, size_t bytes);
-// a buffer of counters that its users leave zeroed: cleared when it is new
-dcm_status ensure_zeroed(dcm_ctx *ctx, DevBuf &b, size_t bytes);
+// The same for a build's counters; they are not known to be zero in a new buffer.
+dcm_status ensure(dcm_ctx *ctx, CountBuf &b, size_t bytes);
+// Around the launches of a cell build on the context's stream (capturing: it
+// is being captured): counts_begin clears the counters unless they are known to
+// be zero, counts_end notes that they are again if every launch was accepted.
+// A captured build always clears them, in the graph: its replays then need no
+// state of the host's, and what is only captured says nothing about the
+// counters now.
+void counts_begin(dcm_ctx *ctx, CountBuf &b, bool capturing);
+void counts_end(CountBuf &b, bool capturing);
+// whether the stream is being captured into a graph
+bool stream_capturing(hipStream_t s);
 dcm_status check_launch(dcm_ctx *ctx, const char *what);
 void timer_begin(dcm_ctx *ctx, const char *family, hipEvent_t *ev);
 void timer_end(dcm_ctx *ctx, const char *family, hipEvent_t ev);
@@ -352,7 +371,7 @@ void launch_assign_cutoffs(hipStream_t s, const double *x, const double *y, cons
 // workgroups of the cell-count kernel: the size of its block_max scratch
 int64_t cell_count_blocks(int64_t n);
 // slot[i]: the particle's slot in its cell (arbitrary within it); cell_count
-// must be zero on entry, and ctl->big_cells is zeroed.  assign (sweep form;
+// must be zero on entry (counts_begin), and ctl->big_cells is zeroed.  assign (sweep form;
 // null: rc is read): the cutoffs are assigned in the same pass.
 void launch_cell_count(hipStream_t s, const double *x, const double *y, const double *z,
                        const double *rc, int64_t n, const double L[3], const int32_t nc[3],

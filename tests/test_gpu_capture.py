@@ -1,0 +1,183 @@
+"""Cell builds around stream capture: the cells' counters are right whatever a
+capture left behind.  A capture that is dropped, or fails, after it made the
+buffers grow leaves the next eager build a buffer nothing has cleared; a
+captured build is replayed between eager builds.  Forces and counts equal those
+of a fresh context bit for bit."""
+import ctypes
+
+import numpy as np
+import pytest
+import torch
+
+import paper_1701_05242_amd as dcm
+import workloads
+
+from gpu_util import DEV, F64, dev, host
+
+pytestmark = pytest.mark.gpu
+
+RELAXED = 2  # hipStreamCaptureModeRelaxed
+EDGE, BOUND = 1.5, 6.0
+
+
+def hip(name, *args):
+    # the runtime the library is linked with
+    return getattr(dcm.load_library(), name)(*args)
+
+
+def handle(stream):
+    return ctypes.c_void_p(stream.cuda_stream)
+
+
+def begin(stream):
+    assert hip("hipStreamBeginCapture", handle(stream), ctypes.c_int(RELAXED)) == 0
+
+
+def end(stream):
+    g = ctypes.c_void_p()
+    code = hip("hipStreamEndCapture", handle(stream), ctypes.byref(g))
+    hip("hipGetLastError")
+    return code, g
+
+
+def poison(nbytes):
+    """Device memory of every size up to nbytes that holds no zeros, given back."""
+    keep = []
+    while nbytes >= 4096:
+        keep.append(torch.full((nbytes // 4,), 0x01010101, dtype=torch.int32, device=DEV))
+        nbytes //= 2
+    torch.cuda.synchronize()
+    del keep
+    torch.cuda.empty_cache()
+
+
+def system(n, seed):
+    rng = np.random.default_rng(seed)
+    m, L = 24, 27.0
+    site = rng.permutation(m ** 3)[:n]
+    p = (np.stack(np.unravel_index(site, (m, m, m)), 1) + 0.5) * (L / m)
+    p += rng.uniform(-0.05, 0.05, p.shape)
+    rc = workloads.uniform_cutoffs(n, 2.5, BOUND, seed=seed)
+    return (L, L, L), [dev(p[:, a]) for a in range(3)] + [dev(rc)]
+
+
+def outputs(n):
+    return [torch.zeros(n, **F64) for _ in range(3)] + [torch.zeros(n, dtype=torch.int32,
+                                                                    device=DEV)]
+
+
+def single(ctx, box, a, out, prec):
+    dcm.dcm_build_cells(ctx, *a, box, EDGE, prec, rc_bound=BOUND)
+    dcm.dcm_forces(ctx, dcm.make_lj(), *out[:3], prec=prec, ev_flags=dcm.DCM_EV_COUNTS,
+                   nnbr=out[3])
+
+
+def fresh(box, a, prec):
+    out = outputs(a[0].numel())
+    ctx = dcm.dcm_create()
+    single(ctx, box, a, out, prec)
+    assert dcm.dcm_sync_status(ctx) == dcm.DCM_OK
+    dcm.dcm_destroy(ctx)
+    return [host(t) for t in out]
+
+
+def equal(out, ref):
+    for t, r in zip(out, ref):
+        np.testing.assert_array_equal(host(t), r)
+
+
+@pytest.mark.parametrize("prec", [dcm.DCM_FP64, dcm.DCM_FP32_MIXED])
+def test_eager_build_after_a_dropped_capture(prec):
+    print(f"[gpu] eager build after a dropped capture prec={prec}", flush=True)
+    box, a = system(9000, 1)
+    ref = fresh(box, a, prec)
+    out = outputs(9000)
+    stream = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    poison(64 << 20)
+    ctx = dcm.dcm_create(stream)
+    begin(stream)
+    dcm.dcm_build_cells(ctx, *a, box, EDGE, prec, rc_bound=BOUND)  # its buffers grow here
+    code, g = end(stream)
+    assert code == 0 and hip("hipGraphDestroy", g) == 0  # never run
+    for _ in range(2):
+        single(ctx, box, a, out, prec)
+        assert dcm.dcm_sync_status(ctx) == dcm.DCM_OK
+        equal(out, ref)
+    dcm.dcm_destroy(ctx)
+
+
+def test_batch_after_a_failed_capture():
+    """A batch met for the first time during a capture is refused (its tables
+    are uploaded and waited for); the eager call that follows is right."""
+    print("[gpu] batch after a failed capture", flush=True)
+    systems, refs = [], []
+    for n in (3000, 9000):
+        box, a = system(n, n)
+        refs.append(fresh(box, a, dcm.DCM_FP64))
+        out = outputs(n)
+        systems.append(dict(zip(("x", "y", "z", "rc"), a), box=box, cell_edge=EDGE,
+                            rc_bound=BOUND, **dict(zip(("fx", "fy", "fz", "nnbr"), out))))
+    stream = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    poison(64 << 20)
+    ctx = dcm.dcm_create(stream)
+    begin(stream)
+    with pytest.raises(dcm.DcmError):
+        dcm.dcm_forces_batched(ctx, systems, dcm.make_lj(), ev_flags=dcm.DCM_EV_COUNTS)
+    code, g = end(stream)
+    print(f"[gpu]   capture ended with {code}", flush=True)
+    if code == 0 and g:
+        assert hip("hipGraphDestroy", g) == 0
+    stream = torch.cuda.Stream()  # (the other one's capture may stay invalid)
+    dcm.dcm_set_stream(ctx, stream)
+    for graph in (False, True, True):
+        for d in systems:
+            d["fx"].zero_()
+        torch.cuda.synchronize()
+        dcm.dcm_forces_batched(ctx, systems, dcm.make_lj(), ev_flags=dcm.DCM_EV_COUNTS,
+                               use_graph=graph)
+        assert dcm.dcm_sync_status(ctx) == dcm.DCM_OK
+        for d, ref in zip(systems, refs):
+            equal([d[k] for k in ("fx", "fy", "fz", "nnbr")], ref)
+    dcm.dcm_destroy(ctx)
+
+
+@pytest.mark.parametrize("prec", [dcm.DCM_FP64, dcm.DCM_FP32_MIXED])
+def test_replays_between_eager_builds(prec):
+    print(f"[gpu] replayed builds between eager ones prec={prec}", flush=True)
+    n = 9000
+    box, a = system(n, 1)
+    _, other = system(n, 2)
+    ref, ref_other = fresh(box, a, prec), fresh(box, other, prec)
+    inputs = [t.clone() for t in a]
+    out, eager = outputs(n), outputs(n)
+    stream = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    ctx = dcm.dcm_create(stream)
+    # more particles first: a captured build sizes its ghost buffer by an estimate
+    single(ctx, box, system(13500, 3)[1], outputs(13500), prec)
+    assert dcm.dcm_sync_status(ctx) == dcm.DCM_OK
+    single(ctx, box, other, eager, prec)
+    assert dcm.dcm_sync_status(ctx) == dcm.DCM_OK
+    begin(stream)
+    single(ctx, box, inputs, out, prec)
+    code, g = end(stream)
+    assert code == 0
+    run = ctypes.c_void_p()
+    assert hip("hipGraphInstantiate", ctypes.byref(run), g, None, None, ctypes.c_size_t(0)) == 0
+    for k in range(4):
+        src, want = ((a, ref), (other, ref_other))[k % 2]
+        with torch.cuda.stream(stream):
+            for t, s in zip(inputs, src):
+                t.copy_(s)
+            for t in out:
+                t.zero_()
+        assert hip("hipGraphLaunch", run, handle(stream)) == 0
+        if k:
+            single(ctx, box, other, eager, prec)
+        assert dcm.dcm_sync_status(ctx) == dcm.DCM_OK
+        equal(out, want)
+        equal(eager, ref_other)
+    assert hip("hipGraphExecDestroy", run) == 0 and hip("hipGraphDestroy", g) == 0
+    dcm.dcm_destroy(ctx)
