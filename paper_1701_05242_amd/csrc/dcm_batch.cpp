@@ -37,21 +37,21 @@ struct BatchState {
   int row_lists = 0;    // the variant the next launches use
   bool needs_tuning = false;
   int plan_queues = 1;  // work-queue segments of the plan: 1 or kXcds
-  int plan_rule = 0;          // pair rule, and whether the force pass reads the compact
-  bool plan_compact = false;  // records, the plan's work items were made for
   // plan
   std::vector<SysGeom> geo;
   std::vector<int2> items;   // particle blocks of the build, system-major
-  std::vector<int2> pitems;  // pair work items in natural order: blocks of kItem >> split_log
   std::vector<int2> eblk;
   std::vector<int2> rblk;  // (system, first extended row) per group of 256 rows
-  std::vector<int32_t> queue;
-  std::vector<int32_t> qseg;  // segment starts in queue [plan_queues + 1]
+  // pair work items of each force pass (pair_form): (system, first particle,
+  // item in natural order, -) in the order they are handed out, and the segment
+  // starts in it [plan_queues + 1]
+  std::vector<int4> queue[kPairForms];
+  std::vector<int32_t> qseg[kPairForms];
   int64_t n_total = 0, cells_total = 0, ext_cells_total = 0, ext_rows_total = 0, ext_cap = 0;
   bool rel_ok = true;  // every system's halos fit the compact records
   double max_len = 0.0;  // widest cell edge of any system
-  size_t off_geo = 0, off_items = 0, off_eblk = 0, off_rblk = 0, off_queue = 0, off_qseg = 0,
-         table_bytes = 0;
+  size_t off_geo = 0, off_items = 0, off_eblk = 0, off_rblk = 0, off_queue[kPairForms] = {},
+         off_qseg[kPairForms] = {}, table_bytes = 0;
   std::vector<unsigned char> table_host;
   // device memory
   CountBuf cell_count;
@@ -104,15 +104,69 @@ bool compact_records(const BatchState &B, dcm_lj lj, int rule, int prec) {
          B.max_len <= kRelMaxEdgeSigma * lj.sigma;
 }
 
-// Cell geometry, concatenated layout, block tables and work queue for the
+// The work items of one force pass (pair_form), with the lanes per particle of
+// the single-system calls, in `queues` segments; cost_pp: estimated cost of a
+// particle of each system.
+void plan_items(BatchState &B, int form, int queues, const std::vector<double> &cost_pp) {
+  const int32_t nsys = (int32_t)B.desc.size();
+  const bool compact = form == pair_form(DCM_PAIR_OWN, true);
+  const int rule = form == pair_form(DCM_PAIR_MAX, false) ? DCM_PAIR_MAX : DCM_PAIR_OWN;
+  std::vector<int4> &queue = B.queue[form];
+  std::vector<int32_t> &qseg = B.qseg[form];
+  std::vector<int4> items;  // natural order
+  std::vector<double> cost;
+  for (int32_t b = 0; b < nsys; ++b) {
+    PairItems &w = B.geo[b].pair[form];
+    const int64_t n = B.geo[b].n;
+    w.split_log = pair_split_log(n, B.geo[b].rc_cap, rule, compact, false);
+    const int64_t per = kItem >> w.split_log;
+    w.item0 = (int64_t)items.size();
+    w.nitems = ceil_div(n, per);
+    for (int64_t k = 0; k < w.nitems; ++k) {
+      items.push_back(make_int4(b, (int)(k * per), (int)items.size(), 0));
+      cost.push_back(cost_pp[b] * (double)std::min(per, n - k * per));
+    }
+  }
+  const int64_t nitems = (int64_t)items.size();
+  queue.clear();
+  qseg.assign(queues + 1, 0);
+  if (queues == 1) {  // largest estimated cost first, ties in natural order
+    queue = items;
+    std::stable_sort(queue.begin(), queue.end(),
+                     [&](const int4 &a, const int4 &b) { return cost[a.z] > cost[b.z]; });
+    qseg[1] = (int32_t)nitems;
+    return;
+  }
+  // whole systems to segments, the costliest first onto the least loaded
+  // one; a segment lists its systems' items in natural order
+  std::vector<double> scost(nsys, 0.0);
+  for (int64_t k = 0; k < nitems; ++k) scost[items[k].x] += cost[k];
+  std::vector<int32_t> order(nsys);
+  std::iota(order.begin(), order.end(), 0);
+  std::stable_sort(order.begin(), order.end(),
+                   [&](int32_t a, int32_t b) { return scost[a] > scost[b]; });
+  std::vector<double> load(queues, 0.0);
+  std::vector<int32_t> seg_of(nsys, 0);
+  for (int32_t b : order) {
+    const int q = (int)(std::min_element(load.begin(), load.end()) - load.begin());
+    seg_of[b] = q;
+    load[q] += scost[b];
+  }
+  for (int q = 0; q < queues; ++q) {
+    qseg[q] = (int32_t)queue.size();
+    for (const int4 &it : items)
+      if (seg_of[it.x] == q) queue.push_back(it);
+  }
+  qseg[queues] = (int32_t)queue.size();
+}
+
+// Cell geometry, concatenated layout, block tables and work queues for the
 // batch, with `edge` for the systems that leave the cell edge to the tuner,
 // and `queues` work-queue segments (1 or kBatchQueues).
-dcm_status make_plan(dcm_ctx *ctx, BatchState &B, double edge, int queues, dcm_lj lj, int rule,
-                     int prec) {
+dcm_status make_plan(dcm_ctx *ctx, BatchState &B, double edge, int queues) {
   const int32_t nsys = (int32_t)B.desc.size();
   B.geo.assign(nsys, SysGeom{});
   B.items.clear();
-  B.pitems.clear();
   B.eblk.clear();
   B.rblk.clear();
   std::vector<double> cost_pp(nsys, 0.0);
@@ -196,79 +250,36 @@ dcm_status make_plan(dcm_ctx *ctx, BatchState &B, double edge, int queues, dcm_l
   // the most ghost copies any arrangement of the particles can need
   // (capped at what the pair kernel can address)
   B.ext_cap = std::max<int64_t>((int64_t)ext_bound, 1);
-  // pair work items, with the lanes per particle of the single-system calls
-  B.plan_rule = rule;
-  B.plan_compact = compact_records(B, lj, rule, prec);
-  for (int32_t b = 0; b < nsys; ++b) {
-    SysGeom &g = B.geo[b];
-    g.split_log = pair_split_log(g.n, g.rc_cap, rule, B.plan_compact, false);
-    const int64_t per = kItem >> g.split_log;
-    g.pitem0 = (int64_t)B.pitems.size();
-    g.npitems = ceil_div(g.n, per);
-    for (int64_t k = 0; k < g.npitems; ++k) B.pitems.push_back(make_int2(b, (int)(k * per)));
-  }
-  // work queue: largest estimated cost first, ties in natural order
-  const int64_t npitems = (int64_t)B.pitems.size();
-  std::vector<double> cost(npitems);
-  for (int64_t k = 0; k < npitems; ++k) {
-    const int b = B.pitems[k].x;
-    const int64_t cnt = std::min<int64_t>(kItem >> B.geo[b].split_log, B.desc[b].n - B.pitems[k].y);
-    cost[k] = cost_pp[b] * (double)cnt;
-  }
   B.plan_queues = queues;
-  B.queue.resize(npitems);
-  B.qseg.assign(queues + 1, 0);
-  if (queues == 1) {
-    std::iota(B.queue.begin(), B.queue.end(), 0);
-    std::stable_sort(B.queue.begin(), B.queue.end(),
-                     [&](int32_t a, int32_t b) { return cost[a] > cost[b]; });
-    B.qseg[1] = (int32_t)npitems;
-  } else {
-    // whole systems to segments, the costliest first onto the least loaded
-    // one; a segment lists its systems' items in natural order
-    std::vector<double> scost(nsys, 0.0);
-    for (int64_t k = 0; k < npitems; ++k) scost[B.pitems[k].x] += cost[k];
-    std::vector<int32_t> order(nsys);
-    std::iota(order.begin(), order.end(), 0);
-    std::stable_sort(order.begin(), order.end(),
-                     [&](int32_t a, int32_t b) { return scost[a] > scost[b]; });
-    std::vector<double> load(queues, 0.0);
-    std::vector<int32_t> seg_of(nsys, 0);
-    for (int32_t b : order) {
-      const int q = (int)(std::min_element(load.begin(), load.end()) - load.begin());
-      seg_of[b] = q;
-      load[q] += scost[b];
-    }
-    int64_t pos = 0;
-    for (int q = 0; q < queues; ++q) {
-      B.qseg[q] = (int32_t)pos;
-      for (int64_t k = 0; k < npitems; ++k)
-        if (seg_of[B.pitems[k].x] == q) B.queue[pos++] = (int32_t)k;
-    }
-    B.qseg[queues] = (int32_t)pos;
-  }
+  for (int f = 0; f < kPairForms; ++f) plan_items(B, f, queues, cost_pp);
   // device tables, uploaded once per plan
   B.off_geo = 0;
   const int64_t nitems = (int64_t)B.items.size();
   B.off_items = align256(sizeof(SysGeom) * nsys);
   B.off_eblk = B.off_items + align256(sizeof(int2) * std::max<int64_t>(nitems, 1));
   B.off_rblk = B.off_eblk + align256(sizeof(int2) * std::max<size_t>(B.eblk.size(), 1));
-  B.off_queue = B.off_rblk + align256(sizeof(int2) * std::max<size_t>(B.rblk.size(), 1));
-  B.off_qseg = B.off_queue + align256(sizeof(int4) * std::max<int64_t>(npitems, 1));
-  B.table_bytes = B.off_qseg + align256(sizeof(int32_t) * (queues + 1));
-  B.table_host.assign(B.table_bytes, 0);
-  std::memcpy(B.table_host.data() + B.off_geo, B.geo.data(), sizeof(SysGeom) * nsys);
-  if (nitems) {
-    std::memcpy(B.table_host.data() + B.off_items, B.items.data(), sizeof(int2) * nitems);
-    int4 *q = reinterpret_cast<int4 *>(B.table_host.data() + B.off_queue);
-    for (int64_t k = 0; k < npitems; ++k)
-      q[k] = make_int4(B.pitems[B.queue[k]].x, B.pitems[B.queue[k]].y, B.queue[k], 0);
+  size_t off = B.off_rblk + align256(sizeof(int2) * std::max<size_t>(B.rblk.size(), 1));
+  size_t npitems = 1;
+  for (int f = 0; f < kPairForms; ++f) {
+    B.off_queue[f] = off;
+    B.off_qseg[f] = off + align256(sizeof(int4) * std::max<size_t>(B.queue[f].size(), 1));
+    off = B.off_qseg[f] + align256(sizeof(int32_t) * (queues + 1));
+    npitems = std::max(npitems, B.queue[f].size());
   }
-  std::memcpy(B.table_host.data() + B.off_qseg, B.qseg.data(), sizeof(int32_t) * (queues + 1));
+  B.table_bytes = off;
+  B.table_host.assign(B.table_bytes, 0);
+  unsigned char *t = B.table_host.data();
+  std::memcpy(t + B.off_geo, B.geo.data(), sizeof(SysGeom) * nsys);
+  if (nitems) std::memcpy(t + B.off_items, B.items.data(), sizeof(int2) * nitems);
+  for (int f = 0; f < kPairForms; ++f) {
+    if (!B.queue[f].empty())
+      std::memcpy(t + B.off_queue[f], B.queue[f].data(), sizeof(int4) * B.queue[f].size());
+    std::memcpy(t + B.off_qseg[f], B.qseg[f].data(), sizeof(int32_t) * (queues + 1));
+  }
   if (!B.eblk.empty())
-    std::memcpy(B.table_host.data() + B.off_eblk, B.eblk.data(), sizeof(int2) * B.eblk.size());
+    std::memcpy(t + B.off_eblk, B.eblk.data(), sizeof(int2) * B.eblk.size());
   if (!B.rblk.empty())
-    std::memcpy(B.table_host.data() + B.off_rblk, B.rblk.data(), sizeof(int2) * B.rblk.size());
+    std::memcpy(t + B.off_rblk, B.rblk.data(), sizeof(int2) * B.rblk.size());
   // growing a buffer moves it: a recorded graph would hold stale addresses
   B.drop_graph();
   dcm_status st;
@@ -306,8 +317,7 @@ dcm_status make_plan(dcm_ctx *ctx, BatchState &B, double edge, int queues, dcm_l
   if ((st = ensure(ctx, B.ext_sq, sizeof(int2) * (B.ext_cells_total + 1))) != DCM_OK) return st;
   if ((st = ensure(ctx, B.ext_pos, sizeof(double4) * B.ext_cap)) != DCM_OK) return st;
   if (B.rel_ok && (st = ensure(ctx, B.ext_rel, sizeof(float4) * B.ext_cap)) != DCM_OK) return st;
-  if ((st = ensure(ctx, B.partials,
-                   sizeof(double) * kPartialSlots * std::max<int64_t>(npitems, 1))) != DCM_OK)
+  if ((st = ensure(ctx, B.partials, sizeof(double) * kPartialSlots * npitems)) != DCM_OK)
     return st;
   if ((st = ensure(ctx, B.rcmax, sizeof(unsigned long long) * nsys)) != DCM_OK) return st;
   if ((st = ensure(ctx, B.rcmax_part, sizeof(unsigned long long) * std::max<int64_t>(nitems, 1))) !=
@@ -377,10 +387,11 @@ void enqueue(dcm_ctx *ctx, BatchState &B, hipStream_t s, dcm_lj lj, int rule, in
   if (timed) timer_end(ctx, "batch_cells", ev);
   BatchPairArgs a;
   a.sys = geo;
-  a.queue = dptr<int4>(B.tables, B.off_queue);
-  a.qseg = dptr<int32_t>(B.tables, B.off_qseg);
+  const int form = pair_form(rule, rel != nullptr);
+  a.queue = dptr<int4>(B.tables, B.off_queue[form]);
+  a.qseg = dptr<int32_t>(B.tables, B.off_qseg[form]);
   a.nqueues = B.plan_queues;
-  a.nitems = (int32_t)B.pitems.size();
+  a.nitems = (int32_t)B.queue[form].size();
   a.head = dptr<uint32_t>(B.head);
   a.pos = dptr<double4>(B.sorted);
   a.cell_start = dptr<int32_t>(B.cell_start);
@@ -398,7 +409,7 @@ void enqueue(dcm_ctx *ctx, BatchState &B, hipStream_t s, dcm_lj lj, int rule, in
   a.status = ctx->d_status;
   if (timed) timer_begin(ctx, "batch_pair", &ev);
   launch_pair_batched(s, a, rule, prec, B.row_lists);
-  launch_batch_reduce(s, geo, nsys, dptr<double>(B.partials), ev_flags);
+  launch_batch_reduce(s, geo, nsys, dptr<double>(B.partials), form, ev_flags);
   if (timed) timer_end(ctx, "batch_pair", ev);
 }
 
@@ -434,7 +445,7 @@ dcm_status tune(dcm_ctx *ctx, BatchState &B, dcm_lj lj, int rule, int prec, int 
     const int il = trial % nlists, iq = (trial / nlists) % nlayouts;
     const double edge = kTuneEdges[trial / (nlists * nlayouts)];
     const int queues = ctx->batch_queues ? ctx->batch_queues : (iq ? kBatchQueues : 1);
-    if (il == 0 && (st = make_plan(ctx, B, edge, queues, lj, rule, prec)) != DCM_OK) break;
+    if (il == 0 && (st = make_plan(ctx, B, edge, queues)) != DCM_OK) break;
     B.row_lists = ctx->batch_lists ? ctx->batch_lists - 1 : il;
     enqueue_call(ctx, B, lj, rule, prec, ev_flags, false);
     const hipError_t r0 = hipEventRecord(e0, ctx->stream);
@@ -539,12 +550,8 @@ dcm_status dcm_forces_batched(dcm_ctx *ctx, int32_t nsys, const dcm_system *sys,
   const int queues =
       ctx->batch_queues ? ctx->batch_queues : (B.needs_tuning ? B.tuned_queues : 1);
   B.row_lists = ctx->batch_lists ? ctx->batch_lists - 1 : (B.needs_tuning ? B.tuned_lists : 0);
-  // (the lanes per particle, and so the pair work items, follow the rule and
-  // whether the compact records serve)
-  if (!B.have_plan || B.plan_edge != edge || B.plan_queues != queues ||
-      B.plan_rule != pair_rule ||
-      B.plan_compact != compact_records(B, lj, pair_rule, prec)) {
-    if ((st = make_plan(ctx, B, edge, queues, lj, pair_rule, prec)) != DCM_OK) {
+  if (!B.have_plan || B.plan_edge != edge || B.plan_queues != queues) {
+    if ((st = make_plan(ctx, B, edge, queues)) != DCM_OK) {
       B.have_plan = false;
       return st;
     }

@@ -105,6 +105,19 @@ struct Timer {
   std::vector<std::pair<hipEvent_t, hipEvent_t>> pending;
 };
 
+// Force passes that deal a particle's rows to different numbers of lanes
+// (pair_split_log), and so cut a batch into other work items: a batch's plan
+// holds the items of all of them, and serves calls of any rule and precision.
+constexpr int kPairForms = 3;
+__host__ __device__ constexpr int pair_form(int rule, bool compact) {
+  return rule == DCM_PAIR_MAX ? 2 : (compact ? 1 : 0);
+}
+struct PairItems {
+  int64_t item0;      // a system's first work item (blocks of 256 >> split_log particles)
+  int64_t nitems;
+  int32_t split_log;  // lanes sharing a particle (pair_split_log)
+};
+
 // One system of a batch as the device sees it: the caller's arrays, its
 // slices of the concatenated particle, cell and extended-cell orders, and
 // its cell geometry.
@@ -119,11 +132,9 @@ struct SysGeom {
   int64_t cell0;      // first real cell
   int64_t ext_cell0;  // first extended cell
   int64_t row0;       // first extended row (rows: ne[1] * ne[2] per system)
-  int64_t item0;      // first pair work item (blocks of 256 particles)
+  int64_t item0;      // first block of 256 particles of the build
   int64_t nitems;
-  int64_t pitem0;     // the same for the force pass (blocks of 256 >> split_log particles)
-  int64_t npitems;
-  int32_t split_log;  // lanes sharing a particle in the force pass (pair_split_log)
+  PairItems pair[kPairForms];  // work items of the force pass, by pair_form
   double rel_delta;   // error bound of the compact records (rel_record_delta)
   int32_t nc[3], h[3], ne[3];
   double len[3], sc[3], L[3];
@@ -616,7 +627,7 @@ struct BatchCells {
 };
 void launch_batch_cells(hipStream_t s, const BatchCells &c);
 void launch_batch_reduce(hipStream_t s, const SysGeom *sys, int32_t nsys,
-                         const double *partials, int ev_flags);
+                         const double *partials, int form, int ev_flags);
 void launch_fill_u64(hipStream_t s, unsigned long long *p, unsigned long long v, int64_t n);
 void launch_reduce_partials(hipStream_t s, const double *partials, int64_t blocks, double eps,
                             int ev_flags, double *energy, double *virial, uint64_t *npairs);

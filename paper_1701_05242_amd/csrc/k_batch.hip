@@ -299,11 +299,12 @@ __global__ __launch_bounds__(kBatchBlock) void kb_ext_fill(
 // are bit for bit those of dcm_forces on the same cells)
 __global__ __launch_bounds__(kReduceThreads) void kb_reduce(const SysGeom *__restrict__ sys,
                                                             const double *__restrict__ partials,
-                                                            int ev_flags) {
+                                                            int form, int ev_flags) {
   const SysGeom &g = sys[blockIdx.x];
+  const PairItems w = g.pair[form];
   __shared__ double red[kReduceThreads / 64][kPartialSlots];
   double t[kPartialSlots];
-  sum_rows<kReduceThreads, kPartialSlots>(partials + g.pitem0 * kPartialSlots, g.npitems, red, t);
+  sum_rows<kReduceThreads, kPartialSlots>(partials + w.item0 * kPartialSlots, w.nitems, red, t);
   if (threadIdx.x == 0) {
     if (g.energy && (ev_flags & DCM_EV_ENERGY)) *g.energy = t[0];
     if (g.virial && (ev_flags & DCM_EV_VIRIAL))
@@ -347,10 +348,10 @@ void launch_batch_cells(hipStream_t s, const BatchCells &c) {
 }
 
 void launch_batch_reduce(hipStream_t s, const SysGeom *sys, int32_t nsys,
-                         const double *partials, int ev_flags) {
+                         const double *partials, int form, int ev_flags) {
   if (nsys <= 0) return;
   hipLaunchKernelGGL(kb_reduce, dim3((unsigned)nsys), dim3(kReduceThreads), 0, s, sys, partials,
-                     ev_flags);
+                     form, ev_flags);
 }
 
 }  // namespace dcm

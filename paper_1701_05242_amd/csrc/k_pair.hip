@@ -1292,6 +1292,7 @@ __global__ __launch_bounds__(kPairBlock) void k_pair_batched(BatchPairArgs a) {
   __shared__ int32_t nearq[REL ? kNearCap + 1 : 1][kPairBlock];
   __shared__ double red[kPairBlock / 64][kPartialSlots];
   __shared__ int4 next_item;
+  constexpr int kForm = pair_form(RULE, REL);
   const double sig2 = a.sigma * a.sigma;
   const int home = a.nqueues > 1 ? (int)(blockIdx.x % (unsigned)a.nqueues) : 0;
   int tried = 0;  // segments found empty
@@ -1341,7 +1342,7 @@ __global__ __launch_bounds__(kPairBlock) void k_pair_batched(BatchPairArgs a) {
     }
     v.rc_bound = g.rc_cap;
     v.rc_all_bits = a.rc_max_bits + b;
-  v.split_log = g.split_log;
+    v.split_log = g.pair[kForm].split_log;
     v.fx = g.fx;
     v.fy = g.fy;
     v.fz = g.fz;
@@ -1349,14 +1350,13 @@ __global__ __launch_bounds__(kPairBlock) void k_pair_batched(BatchPairArgs a) {
     v.ext_src = nullptr;
     v.n3_f = nullptr;
     v.n3_cnt = nullptr;
-    int64_t local = first + ((int64_t)threadIdx.x >> g.split_log);
+    int64_t local = first + ((int64_t)threadIdx.x >> v.split_log);
     if constexpr (REL)
-      local = first + rc_lane_order(a.pos, g.p0 + first, g.n - first, g.split_log, g.rc_cap,
+      local = first + rc_lane_order(a.pos, g.p0 + first, g.n - first, v.split_log, g.rc_cap,
                                     &nearq[0][0]);
     pair_block<RULE, PREC, EVM, REL, CAP>(v, g.p0 + local, local < g.n, a.eps, sig2, segs, nearq,
-                                          red,
-                                     a.status,
-                                a.partials + (int64_t)item * kPartialSlots);
+                                          red, a.status,
+                                          a.partials + (int64_t)item * kPartialSlots);
   }
 }
 

@@ -1,8 +1,9 @@
 """Cell builds around stream capture: the cells' counters are right whatever a
 capture left behind.  A capture that is dropped, or fails, after it made the
 buffers grow leaves the next eager build a buffer nothing has cleared; a
-captured build is replayed between eager builds.  Forces and counts equal those
-of a fresh context bit for bit."""
+captured build is replayed between eager builds.  One plan serves a batch's
+calls of any rule and precision, so such a call can be captured after one of
+another kind.  Forces and counts equal those of a fresh context bit for bit."""
 import ctypes
 
 import numpy as np
@@ -180,4 +181,71 @@ def test_replays_between_eager_builds(prec):
         equal(out, want)
         equal(eager, ref_other)
     assert hip("hipGraphExecDestroy", run) == 0 and hip("hipGraphDestroy", g) == 0
+    dcm.dcm_destroy(ctx)
+
+
+KINDS = [(dcm.DCM_PAIR_OWN, dcm.DCM_FP64), (dcm.DCM_PAIR_OWN, dcm.DCM_FP32_MIXED),
+         (dcm.DCM_PAIR_MAX, dcm.DCM_FP64), (dcm.DCM_PAIR_MAX, dcm.DCM_FP32_MIXED)]
+
+
+@pytest.mark.parametrize("queues", [1, 8])
+def test_batch_of_every_rule_and_precision(queues):
+    """Calls of every kind in turn on one context, eager, then each captured
+    after a call of another kind and replayed between eager ones."""
+    print(f"[gpu] batch of every kind, {queues} queues", flush=True)
+    systems = []
+    for n in (0, 1, 2900, 8000, 13500):
+        box, a = system(n, 40 + n)
+        systems.append(dict(zip(("x", "y", "z", "rc"), a), box=box, cell_edge=EDGE,
+                            rc_bound=BOUND, energy=torch.zeros(1, **F64),
+                            **dict(zip(("fx", "fy", "fz", "nnbr"), outputs(n)))))
+    names = ("fx", "fy", "fz", "nnbr", "energy")
+    flags = dcm.DCM_EV_ENERGY | dcm.DCM_EV_COUNTS
+
+    def call(ctx, kind, graph=False):
+        dcm.dcm_forces_batched(ctx, systems, dcm.make_lj(), pair_rule=kind[0], prec=kind[1],
+                               ev_flags=flags, use_graph=graph)
+
+    def check(ctx, ref):
+        assert dcm.dcm_sync_status(ctx) == dcm.DCM_OK
+        for d, r in zip(systems, ref):
+            equal([d[k] for k in names], r)
+            for k in names:
+                d[k].zero_()
+        torch.cuda.synchronize()
+
+    def fresh_batch(kind):
+        ctx = dcm.dcm_create()
+        dcm.dcm_set_batched_queues(ctx, queues)
+        call(ctx, kind)
+        assert dcm.dcm_sync_status(ctx) == dcm.DCM_OK
+        dcm.dcm_destroy(ctx)
+        return [[host(d[k]).copy() for k in names] for d in systems]
+
+    refs = [fresh_batch(k) for k in KINDS]
+    stream = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    ctx = dcm.dcm_create(stream)
+    dcm.dcm_set_batched_queues(ctx, queues)
+    for graph in (False, True):
+        for kind, ref in list(zip(KINDS, refs)) * 2:
+            call(ctx, kind, graph)
+            check(ctx, ref)
+    for k, (kind, ref) in enumerate(zip(KINDS, refs)):
+        before, ref_before = KINDS[k - 1], refs[k - 1]
+        call(ctx, before)
+        check(ctx, ref_before)
+        begin(stream)
+        call(ctx, kind)
+        code, g = end(stream)
+        assert code == 0
+        run = ctypes.c_void_p()
+        assert hip("hipGraphInstantiate", ctypes.byref(run), g, None, None,
+                   ctypes.c_size_t(0)) == 0
+        for _ in range(3):
+            assert hip("hipGraphLaunch", run, handle(stream)) == 0
+            check(ctx, ref)
+            call(ctx, before)
+            check(ctx, ref_before)
+        assert hip("hipGraphExecDestroy", run) == 0 and hip("hipGraphDestroy", g) == 0
     dcm.dcm_destroy(ctx)
