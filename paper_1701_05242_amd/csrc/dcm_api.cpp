@@ -848,7 +848,7 @@ namespace {
 // current cell build
 dcm_status forces_impl(dcm_ctx *ctx, dcm_lj lj, int pair_rule, int prec, int ev_flags, double *fx,
                        double *fy, double *fz, double *energy, double *virial, int32_t *nnbr,
-                       uint64_t *npairs, bool use_list, bool alone = false,
+                       uint64_t *npairs, bool use_list, double step_rc_min = 0.0,
                        bool no_total = false) {
   if (!ctx) return DCM_ERR_INVALID;
   if (ctx->cell_n < 0) return fail(ctx, DCM_ERR_INVALID, "dcm_forces before dcm_build_cells");
@@ -885,7 +885,7 @@ dcm_status forces_impl(dcm_ctx *ctx, dcm_lj lj, int pair_rule, int prec, int ev_
   a.ext_rel = rel ? ptr<float4>(ctx->ext_rel) : nullptr;
   // a list keeps the split it was built with
   const int split_log =
-      use_list ? ctx->list_split : pair_split_log(n, ctx->rc_bound, pair_rule, rel, alone);
+      use_list ? ctx->list_split : pair_split_log(n, ctx->rc_bound, pair_rule, rel, step_rc_min);
   const int64_t blocks = pair_blocks(n, split_log);
   DCM_TRY(ensure(ctx, ctx->partials, blocks * kPartialSlots * sizeof(double)));
   double span = 0.0;  // largest coordinate magnitude in the extended grid
@@ -983,7 +983,8 @@ dcm_status dcm_build_list(dcm_ctx *ctx, double skin) {
     return fail(ctx, DCM_ERR_INVALID,
                 "dcm_build_list after dcm_update_list: build the cells again first");
   const int64_t n = ctx->cell_n;
-  const int split_log = pair_split_log(n, ctx->rc_bound, DCM_PAIR_OWN, false, false);  // as the cell walk's
+  // as the cell walk's
+  const int split_log = pair_split_log(n, ctx->rc_bound, DCM_PAIR_OWN, false, 0.0);
   const int64_t nw = list_waves(n, split_log);
   DCM_TRY(ensure(ctx, ctx->list_count, std::max<int64_t>(n << split_log, 1) * sizeof(int32_t)));
   DCM_TRY(ensure(ctx, ctx->list_wave_len, std::max<int64_t>(nw, 1) * sizeof(int32_t)));
@@ -1247,7 +1248,7 @@ dcm_status dcm_step(dcm_ctx *ctx, double *x, double *y, double *z, double *vx, d
   // them after its kick, with the kinetic energy
   auto step_forces = [&](int ev_flags) -> dcm_status {
     return forces_impl(ctx, lj, pair_rule, prec, ev_flags, W[WFX], W[WFY], W[WFZ], scal, nullptr,
-                       nullptr, nullptr, false, true, true);
+                       nullptr, nullptr, false, rule.rc_min, true);
   };
   auto forces = [&]() -> dcm_status {
     // cells built on the second stream: complete before their records

@@ -118,7 +118,7 @@ void plan_items(BatchState &B, int form, int queues, const std::vector<double> &
   for (int32_t b = 0; b < nsys; ++b) {
     PairItems &w = B.geo[b].pair[form];
     const int64_t n = B.geo[b].n;
-    w.split_log = pair_split_log(n, B.geo[b].rc_cap, rule, compact, false);
+    w.split_log = pair_split_log(n, B.geo[b].rc_cap, rule, compact, 0.0);
     const int64_t per = kItem >> w.split_log;
     w.item0 = (int64_t)items.size();
     w.nitems = ceil_div(n, per);

@@ -500,10 +500,15 @@ int64_t pair_blocks(int64_t n, int split_log);
 // follows m = n (6 / rc_max)^3.
 // compact: the force pass reads the compact records (cheaper candidates, so
 // the overhead weighs more).
-// alone: dcm_step's own passes.  The other calls share one rule, because a
-// batch returns what single-system calls do bit for bit, and in a batch the
-// other systems fill the chip: that rule stays where a 64-system batch of
-// 2,000 to 200,000 particles loses at most a few per cent of its time.
+// step_rc_min: 0, or the smallest cutoff for dcm_step's own passes (rule OWN).
+// The other calls share one rule, because a batch returns what single-system
+// calls do bit for bit, and in a batch the other systems fill the chip: that
+// rule stays where a 64-system batch of 2,000 to 200,000 particles loses at most
+// a few per cent of its time.  A step's forces so equal those of dcm_forces on
+// the same cells within rounding, not bit for bit.
+// Cutoffs that are nearly equal, or a caller's that are large for most of the
+// particles, leave no long walk to shorten, and many particles then pay for
+// every lane beyond the first; a step knows its smallest cutoff.
 // Measured, us per dcm_step without detection at 1, 2, 4, 8, 16 lanes (n in
 // thousands, rc_max):
 //   compact: 8, 6: 218 149 106 96 90; 40, 6: 223 160 121 114 121; 100, 4.5:
@@ -514,23 +519,37 @@ int64_t pair_blocks(int64_t n, int split_log);
 //     230 206 221 236; 341, 8 (cylinder): 1581 1421 1285 1191 1270; 400, 4.5:
 //     413 340 316 343 389
 //   FP64, 500,000 and more, us per call at 1, 2, 4 lanes: steps 600, 6 (five):
-//     2673 2255 2253; 1200, 8 (ten): 14500 10753 11107; cells and forces 1000,
-//     8: 923 764 768; 1000, 4.2: 527 511 571; 2600, 8: 1772 1727 1853; forces on
-//     a list 1000, 8: 1320 1013 875; 1000, 4.2: 620 560 545
+//     2673 2255 2253; 1200, 8 (ten): 14500 10753 11107; forces with cutoffs
+//     from the distance to a slab's faces 485, 8: 475 344 319; 1000, 4.2: 354
+//     353 429; 1000, 8: 595 525 586; 2600, 6: 970 937 1118; 2600, 8: 1207 1120
+//     1281; forces on a list 1000, 8: 1320 1013 875; 1000, 4.2: 620 560 545;
+//     forces with all cutoffs rc_max 536, 8: 2358 2433 2963; 1000, 8: 4183 4484
+//     5501; 2600, 6: 5050 5395 6784; gyroid, step 780, 8: 1825 1484 1360
+//   step, cutoffs from rc_min on (n, rc_min-rc_max), 1, 2, 4 lanes: compact 540,
+//     8-8: 1556 1575 1710; 2500, 8-8: 6680 7221 7881; 2500, 5.3-8: 2775 2918
+//     3267; 2500, 4-8: 1854 1878 2083; 300, 8-8: 972 936 994; FP64 540, 8-8: 3533
+//     3601 3802; 1000, 5.3-8: 2181 2159 2321; 1000, 4-8: 1341 1320 1436; 2500,
+//     6.4-8: 7854 8196 8731
+//   FP32-mixed on cells too wide for the compact records, likewise: 485, 8: 529
+//     399 385; 1000, 4.2: 458 452 512; 2600, 6: 1194 1219 1434; 2600, 8: 1457
+//     1421 1610
+//   symmetric rule, either precision (every particle walks with the largest
+//     cutoff, so no walk is longer than the rest): 60, 6: 209 190 196; 99, 6:
+//     305 265 294; 294, 4.2: 319 296 335; 294, 8: 1436 1390 1619; 392, 4.2: 371
+//     384 449; 392, 8: 1709 1841 2175; 2600, 6: 5016 5371 6783
 //   64-system batch, compact: 1440 1516 1743 2319; FP64: 2106 2073 2243 2665
-// From 500,000 particles on, FP64 passes use one number everywhere, so
-// dcm_step's forces there are those of dcm_forces on the same cells.
-inline int pair_split_log(int64_t n, double rc_max, int rule, bool compact, bool alone) {
+inline int pair_split_log(int64_t n, double rc_max, int rule, bool compact, double step_rc_min) {
   if (rule == DCM_PAIR_MAX_N3) return 0;  // bound by the reactions' atomics
   const double q = 6.0 / rc_max, m = (double)n * (q * q * q);
+  const bool alone = step_rc_min > 0.0 && rule == DCM_PAIR_OWN;
+  if (alone && n >= 500000 && step_rc_min > 0.6 * rc_max) return 0;
   if (compact) {
     if (alone) return m < 16e3 ? 4 : (m < 150e3 ? 3 : (m < 300e3 ? 2 : (m < 3e6 ? 1 : 0)));
     return n < 8000 ? 2 : (n < 32000 ? 1 : 0);
   }
-  if (n >= 500000) return m < 450e3 ? 2 : 1;
-  // (the symmetric rule walks every particle with the largest cutoff and
-  // gains least from many lanes)
-  if (alone && rule == DCM_PAIR_OWN) return m < 20e3 ? 4 : (m < 150e3 ? 3 : 2);
+  if (rule == DCM_PAIR_MAX && n >= 350000) return 0;
+  if (n >= 500000) return alone && m < 450e3 ? 2 : 1;
+  if (alone) return m < 20e3 ? 4 : (m < 150e3 ? 3 : 2);
   return n < 8000 ? 3 : (n < 100000 ? 2 : 1);
 }
 void launch_pair(hipStream_t s, const PairArgs &a, int rule, int prec);
