@@ -515,17 +515,21 @@ dcm_status sweep_enqueue(dcm_ctx *ctx, const uint8_t *seg, const uint8_t *iface,
   else
     launch_fsm_init(s, seg, iface, grid.n, tiled, ptr<double>(ctx->dA), ptr<double>(ctx->dB),
                     tiles, flags, max_waves);
-  // 14 passes serve the interfaces met in earnest with rc_grid of 8 voxels;
-  // those beyond share one launch, which one workgroup runs if the sweep has
-  // not ended by then (few tiles still change that late)
+  // 14 passes serve most interfaces met in earnest with rc_grid of 8 voxels
+  // (slabs 3 to 6, droplets and rough surfaces 8 to 13, a cylinder 15), and a
+  // pass carries a front at least a tile's 8 voxels further.  The passes beyond
+  // share one launch: a launch that finds nothing to do takes the host 4.6 us,
+  // and how many are needed is not known here.  (A pass in the shared launch
+  // costs more where many tiles are active: with six passes of their own a
+  // gyroid on 160 x 160 x 400 voxels takes 11.0 ms instead of 4.3.  One launch
+  // per voxel of rc_grid, 29 at a spacing of 0.25, cost a step 48 us of 332.)
   const double hmin = std::min(grid.h[0], std::min(grid.h[1], grid.h[2]));
-  const double enough = 6.0 + std::ceil(rc_grid / hmin);
-  // On a grid of at most 32 tiles one workgroup is soon as fast as launches
-  // that take the host 4.6 us each: six passes of their own, then its launch
-  // (twenty steps of 3,000 particles on 16 tiles, 14, 6, 4 and 3 passes: 3870,
-  // 3400, 3370, 3830 us; a droplet on 32 tiles 4100, 3440, 3980, 4670).  On 96
-  // tiles four passes cost ten steps of 20,000 particles, detected once, 74 us
-  // of 1012.
+  const double enough = 13.0 + std::ceil(rc_grid / (8.0 * hmin));
+  // On a grid of at most 32 tiles, six: the shared launch holds a pass's tiles
+  // at once, or nearly (us per step with 14 and six: slab, 16 tiles 164 and 135;
+  // droplet, 18 and 32 tiles 172 and 152, 173 and 150; gyroid, 220 and 214, 218
+  // and 191).  On 75 tiles a gyroid takes 291 and 323, a droplet 213 and 185; on
+  // 196 356 and 458, 255 and 244.
   const double many = fsm_tile_count(grid.n) <= 32 ? std::min(enough, 6.0) : enough;
   const int own = tiled && many < (double)max_waves ? (int)many : max_waves;
   auto passes = [&](int from, int to) {
@@ -1193,7 +1197,7 @@ dcm_status dcm_step(dcm_ctx *ctx, double *x, double *y, double *z, double *vx, d
     return check_launch(ctx, "dcm_step");
   };
   // sweep passes stop early once one changes nothing; the limit only bounds
-  // them (those past the first dozen share one launch)
+  // them (those past sweep_enqueue's first ones share one launch)
   const int32_t max_waves = 1024;
   double *scal = ptr<double>(ctx->scalars);
   const dcm_detect_opts dopts = {0.0, -1.0, 0};

@@ -342,7 +342,7 @@ void launch_fsm_init_bits(hipStream_t s, const uint32_t *const maps[2], const Ct
                           const int32_t nv[3], bool tiled, double *dA, double *dB, void *tiles,
                           uint32_t *flags, int max_steps);
 // passes step .. last of the sweep in one launch (last > step only with
-// tiled: one workgroup runs them in turn): temporally blocked tile passes, or
+// tiled and step > 1): temporally blocked tile passes, or
 // (tiled false, last = step) one synchronous wave.  settle: every pass runs
 // its tiles until they have settled (fewer, longer passes).  Tiles serve any
 // grid; dcm_sweep_distance, whose caller counts and bounds its waves, takes

@@ -255,11 +255,18 @@ __device__ __forceinline__ double godunov(double a0, double a1, double a2, const
 // ------------------------------------------------------------- tiled sweep
 // Launch L reads buf[(L-1)&1] and writes buf[L&1] for its active tiles.
 // Active in the first launch are the tiles with an interface voxel and their
-// face neighbours (found from the init's flags, or listed by k_fsm_first); a tile that changes in launch
-// L puts itself, and the face neighbours next to a voxel that changed, on
-// launch L + 1's list (stamp: the last launch a tile was listed for).  live: tiles with a voxel that is not a
-// source; the others never run.  With last > launch the workgroup (there must
-// be only one) goes on with the passes up to `last`.
+// face neighbours (found from the init's flags, or listed by k_fsm_first); a
+// tile that changes in launch L puts itself, and the face neighbours next to a
+// voxel that changed, on launch L + 1's list (stamp: the last launch a tile was
+// listed for).  live: tiles with a voxel that is not a source; the others never
+// run.
+//
+// With last > launch the launch goes on with the passes up to `last` (TAIL).
+// Its workgroups take the tiles of a pass from the list one by one, and wait at
+// the pass's end until as many are finished as were listed.  A workgroup waits
+// only when no tile is left to take, so each of those it waits for is in the
+// hands of one that is running: the wait ends whether or not the others have
+// started, and one that starts late finds nothing to take and catches up.
 //
 // A pass is bound by latency: one after the other, the sub-waves of the tiles
 // that the front crosses, each a solve (94 vector instructions, 70 of them
@@ -280,6 +287,7 @@ struct SweepTiles {
   const uint8_t *first, *live;
   uint32_t *stamp, *changed;  // last launch listed for; last launch that changed the tile
   uint32_t *count;            // [launch]: entries of the launch's list
+  uint32_t *taken, *done;     // [launch]: entries taken and finished (TAIL)
   int32_t *list[2];           // of even and odd launches
 };
 
@@ -320,7 +328,16 @@ __global__ __launch_bounds__(256) void k_fsm_first(SweepTiles w) {
   if (act) w.list[1][base + (uint32_t)__popcll(m & ((1ull << lane) - 1ull))] = t;
 }
 
-template <bool ISO>
+// Looks at a pass's count of finished tiles, some 0.5 us apart, before a waiting
+// workgroup gives up (seconds; a pass takes microseconds): the sweep is then
+// reported as not converged instead of hanging.
+constexpr unsigned kTailSpins = 1u << 23;
+
+__device__ __forceinline__ uint32_t agent_load(const uint32_t *p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+template <bool ISO, bool TAIL>
 __global__ __launch_bounds__(kTileThreads) void k_fsm_tiles(double *dA, double *dB, SweepTiles w,
                                                             SweepGeom g, int launch, int last,
                                                             bool listed, int max_sub,
@@ -330,7 +347,8 @@ __global__ __launch_bounds__(kTileThreads) void k_fsm_tiles(double *dA, double *
   __shared__ double A[2][QZ * PXY];
   __shared__ unsigned int map[3];  // blocks changed by sub-waves 0, 1, 2 mod 3
   __shared__ unsigned int faces;   // the tile's faces (as near_tile) with a changed voxel
-  __shared__ unsigned long long todo_s[kTileWaves];  // first launch: active tiles, 64 to a wavefront
+  __shared__ unsigned long long todo_s[kTileWaves];  // first launch: active tiles, 64 a wavefront
+  __shared__ int got, gave_up;  // TAIL: the entry taken; the wait was given up
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int ntiles = w.ntx * w.nty * w.ntz;
@@ -348,10 +366,9 @@ __global__ __launch_bounds__(kTileThreads) void k_fsm_tiles(double *dA, double *
     double *dst = (launch & 1) ? dB : dA;
     // a pass runs only while the previous one changed something
     int entries = 0;
-    const bool from_list = launch > 1 || listed;
+    const bool from_list = TAIL || launch > 1 || listed;
     if (from_list) {
-      entries = (int)__hip_atomic_load(&w.count[launch], __ATOMIC_RELAXED,
-                                       __HIP_MEMORY_SCOPE_AGENT);
+      entries = (int)agent_load(&w.count[launch]);
       if (entries == 0) return;
     }
     bool any_changed = false;
@@ -363,8 +380,14 @@ __global__ __launch_bounds__(kTileThreads) void k_fsm_tiles(double *dA, double *
     while (true) {
       int t;
       if (from_list) {
+        if constexpr (TAIL) {
+          if (tid == 0) got = (int)atomicAdd(&w.taken[launch], 1u);
+          __syncthreads();
+          at_entry = __builtin_amdgcn_readfirstlane(got);
+        }
         if (at_entry >= entries) break;
-        t = __builtin_amdgcn_readfirstlane(w.list[launch & 1][at_entry]);
+        t = __builtin_amdgcn_readfirstlane(
+            (int)agent_load((const uint32_t *)&w.list[launch & 1][at_entry]));
         at_entry += gridDim.x;
       } else {
         while (todo == 0ull && group + 1 < groups) todo = uniform_u64(todo_s[++group]);
@@ -397,7 +420,7 @@ __global__ __launch_bounds__(kTileThreads) void k_fsm_tiles(double *dA, double *
       const int tx = t % w.ntx, tr = t / w.ntx, ty = tr % w.nty, tz = tr / w.nty;
       const int x0 = tx * TX, y0 = ty * TY, z0 = tz * TZ;
       const bool owned = x0 + lx < g.nx && y0 + ly < g.ny && z0 + lz < g.nz;
-      const bool prev = launch > 1 && w.changed[t] == (uint32_t)(launch - 1);
+      const bool prev = launch > 1 && agent_load(&w.changed[t]) == (uint32_t)(launch - 1);
       // stage the tile and its halo (periodic; on a grid thinner than the
       // tile a halo voxel copies one of the tile, frozen as any halo voxel)
       for (int e = tid; e < QZ * QY * QX; e += NT) {
@@ -470,16 +493,30 @@ __global__ __launch_bounds__(kTileThreads) void k_fsm_tiles(double *dA, double *
           const int n = near_tile(w, tx, ty, tz, tid);
           const uint32_t next = (uint32_t)launch + 1u;
           if (w.live[n] && atomicMax(&w.stamp[n], next) != next)
-            w.list[next & 1][atomicAdd(&w.count[next], 1u)] = n;
+            __hip_atomic_store(&w.list[next & 1][atomicAdd(&w.count[next], 1u)], n,
+                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
       }
+      if constexpr (TAIL) __threadfence();  // the tile's stores, before it counts as finished
       __syncthreads();  // the last map has been read before the next tile clears it
+      if constexpr (TAIL)
+        if (tid == 0) atomicAdd(&w.done[launch], 1u);
     }
     if (tid == 0 && any_changed)
       __hip_atomic_store(&flags[launch], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (launch < last) {  // the only workgroup: its stores are seen by its next pass
-      __threadfence();
+    if constexpr (TAIL) {
+      if (tid == 0) {
+        unsigned spins = 0;
+        while (agent_load(&w.done[launch]) < (uint32_t)entries && ++spins < kTailSpins)
+          __builtin_amdgcn_s_sleep(8);
+        gave_up = spins == kTailSpins;
+        if (gave_up)
+          __hip_atomic_store(&flags[last], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
       __syncthreads();
+      if (gave_up) return;
+      __threadfence();  // the others' stores of this pass are read from here on
+      __syncthreads();  // gave_up has been read
     }
   }
 }
@@ -563,10 +600,10 @@ static SweepGeom geom(const int32_t nv[3], const double h[3], double rc_grid) {
 }
 
 // The tiles' scratch: stamp, changed, the two lists (4 bytes a tile each),
-// first and live (1 byte each).  The flags' scratch: max_steps + 2 pass flags,
-// then max_steps + 2 list counts.
+// first and live (1 byte each).  The flags' scratch, max_steps + 2 words each:
+// pass flags, list counts, entries taken, entries finished.
 int64_t fsm_tile_bytes(const int32_t nv[3]) { return 18 * fsm_tile_count(nv); }
-int64_t fsm_flag_words(int max_steps) { return 2 * ((int64_t)max_steps + 2); }
+int64_t fsm_flag_words(int max_steps) { return 4 * ((int64_t)max_steps + 2); }
 
 static SweepTiles sweep_tiles(const int32_t nv[3], void *tiles, uint32_t *flags, int max_steps) {
   SweepTiles w;
@@ -581,6 +618,8 @@ static SweepTiles sweep_tiles(const int32_t nv[3], void *tiles, uint32_t *flags,
   w.first = reinterpret_cast<const uint8_t *>(w.list[1] + n);
   w.live = w.first + n;
   w.count = flags + max_steps + 2;
+  w.taken = w.count + max_steps + 2;
+  w.done = w.taken + max_steps + 2;
   return w;
 }
 
@@ -616,6 +655,15 @@ void launch_fsm_init_bits(hipStream_t s, const uint32_t *const maps[2], const Ct
 // slab 1.755 and 1.710, of the cylinder 0.975 and 0.934, of the droplet 0.425
 // and 0.418.
 constexpr int64_t kFsmTileBlocks = 256;
+// and of the launch that goes on with several passes, few tiles each by then:
+// more only wait (31 passes along a cylinder of 480 x 36 x 36 voxels, the last 17
+// in that launch: one workgroup 3245 us, 32 1142, 128 and 256, with eight passes
+// of their own, 1785 and 2836 against 1415)
+constexpr int64_t kFsmTailBlocks = 32;
+// From some thousands of tiles on what the list saves of a first pass comes near
+// its launch (sweep without and with it: droplet, 2048 tiles 253 and 211 us, 4000
+// 322 and 300, 5324 342 and 315, 10976 535 and 514; slab, 4000 125 and 129, 10000
+// 567 and 576 with detection; gyroid, 4000 1313 and 1305, 6912 1635 and 1695).
 constexpr int64_t kFsmListedTiles = 4096;
 
 // Sub-waves of a pass.  settle: until the tile has settled, at most
@@ -638,8 +686,8 @@ void launch_fsm_step(hipStream_t s, double *dA, double *dB, void *tiles, const i
   if (tiled) {
     const SweepTiles w = sweep_tiles(nv, tiles, flags, max_steps);
     int64_t blocks = fsm_tile_count(nv);
-    if (blocks > kFsmTileBlocks) blocks = kFsmTileBlocks;
-    if (last > step) blocks = 1;
+    const bool tail = last > step;
+    blocks = std::min(blocks, tail ? kFsmTailBlocks : kFsmTileBlocks);
     const int subs = settle || step > kShortPasses ? kSettleSubWaves : kShortSubWaves;
     // The list pays its launch (5 us) while a workgroup's share of the tiles is
     // small: first pass of 1,800 tiles (droplet) 36 -> 18 us, 2,197 (cylinder)
@@ -649,12 +697,11 @@ void launch_fsm_step(hipStream_t s, double *dA, double *dB, void *tiles, const i
     if (listed)
       hipLaunchKernelGGL(k_fsm_first, dim3((unsigned)ceil_div(tiles_n, 256)),
                          dim3(256), 0, s, w);
-    if (h[0] == h[1] && h[1] == h[2])
-      hipLaunchKernelGGL(k_fsm_tiles<true>, dim3((unsigned)blocks), dim3(kTileThreads), 0, s, dA,
-                         dB, w, g, step, last, listed, subs, flags);
-    else
-      hipLaunchKernelGGL(k_fsm_tiles<false>, dim3((unsigned)blocks), dim3(kTileThreads), 0, s, dA,
-                         dB, w, g, step, last, listed, subs, flags);
+    const bool iso = h[0] == h[1] && h[1] == h[2];
+    const auto kernel = iso ? (tail ? k_fsm_tiles<true, true> : k_fsm_tiles<true, false>)
+                            : (tail ? k_fsm_tiles<false, true> : k_fsm_tiles<false, false>);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kTileThreads), 0, s, dA, dB, w, g, step,
+                       last, listed, subs, flags);
   } else {
     int zb = nv[2] < 64 ? nv[2] : 64;
     hipLaunchKernelGGL(k_fsm_wave,
