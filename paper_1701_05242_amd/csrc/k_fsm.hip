@@ -172,9 +172,7 @@ __global__ __launch_bounds__(256) void k_fsm_init_bits(const uint32_t *b0, const
 // (SweepGeom) indexed by the axis of the largest a.  A quotient x / A is then
 // q = x r with r = 1/A correctly rounded, corrected once by its exact
 // remainder, which gives the correctly rounded quotient (P. Markstein, IBM J.
-// Res. Dev. 34, 1990); the square root is the Goldschmidt iteration on the
-// hardware's reciprocal square root with two exact-remainder corrections,
-// without the range scaling that the library's needs for tiny arguments.
+// Res. Dev. 34, 1990).
 struct SweepGeom {
   int nx, ny, nz;
   double h[3], w[3];
@@ -190,18 +188,6 @@ __device__ __forceinline__ double by_axis(const double v[3], int k) {
 __device__ __forceinline__ double div_by(double x, double A, double r) {
   const double q = x * r;
   return fma(fma(-q, A, x), r, q);
-}
-
-// square root of v >= 0, v zero or far from the denormal range
-__device__ __forceinline__ double sqrt_normal(double v) {
-  const double y = __builtin_amdgcn_rsq(v);
-  double g = v * y, h = 0.5 * y;
-  const double r = fma(-h, g, 0.5);
-  g = fma(g, r, g);
-  h = fma(h, r, h);
-  g = fma(fma(-g, g, v), h, g);
-  g = fma(fma(-g, g, v), h, g);
-  return v == 0.0 ? 0.0 : g;
 }
 
 // ISO: equal spacings on every axis, so only the a's need ordering
@@ -238,14 +224,14 @@ __device__ __forceinline__ double godunov(double a0, double a1, double a2, const
     const double p1 = w1 * b1, p2 = w2 * b2;
     double disc2 = p1 * p1 - A2 * (p1 * b1 - 1.0);
     disc2 = disc2 < 0.0 ? 0.0 : disc2;
-    const double d2 = a0 + div_by(p1 + sqrt_normal(disc2), A2, R2);
+    const double d2 = a0 + div_by(p1 + sqrt(disc2), A2, R2);
     d = more ? d2 : d;
     more = more && !(d2 <= a2);
     if (__ballot(more) != 0ull) {
       const double B3 = p1 + p2;
       double disc3 = B3 * B3 - A3 * ((p1 * b1 + p2 * b2) - 1.0);
       disc3 = disc3 < 0.0 ? 0.0 : disc3;
-      const double d3 = a0 + div_by(B3 + sqrt_normal(disc3), A3, R3);
+      const double d3 = a0 + div_by(B3 + sqrt(disc3), A3, R3);
       d = more ? d3 : d;
     }
   }
