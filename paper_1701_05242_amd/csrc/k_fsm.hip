@@ -39,26 +39,27 @@ int64_t fsm_tile_count(const int32_t nv[3]) {
 
 // Initial distances and the first pass's tile flags, a workgroup to a region
 // of kInitX x TY x TZ voxels (kInitX / TX tiles): sources (low-density phase
-// and interface) start at 0, the rest at +inf.  A tile holding an interface
-// voxel is flagged as changed before the first pass: only next to an
-// interface can a pass change anything at first (a liquid voxel with a source
-// face neighbour is itself an interface voxel).  Also clears the pass flags
-// and the tiles' stamps, which took a launch of their own before.  Bound by the
-// two fields it writes (39 us on the 160 x 160 x 400 grid, 4.2 TB/s; 50 to
-// 60 us beside the cell build).
+// and interface) start at 0, the rest at +inf.  A tile holding a source is
+// flagged as changed before the first pass: only next to a source can a pass
+// change anything at first.  (Where the interface is that of the phase map, a
+// tile with a voxel that is not a source then runs at first if it or a face
+// neighbour holds an interface voxel; a caller's maps may be others.)  Also
+// clears the pass flags and the tiles' stamps, which took a launch of their own
+// before.  Bound by the two fields it writes (39 us on the 160 x 160 x 400 grid,
+// 4.2 TB/s; 50 to 60 us beside the cell build).
 constexpr int kInitX = 64;
 struct FsmInit {
   int nx, ny, nz, ntx, nty;
   double *dA, *dB;
-  uint8_t *first;   // tiles holding an interface voxel; null: no tiles
+  uint8_t *first;   // tiles holding a source; null: no tiles
   uint8_t *live;    // tiles with a voxel that is not a source
   uint32_t *stamp, *changed;  // cleared
   uint32_t *flags;  // pass flags and list counts, cleared
   int nflags;
 };
 
-// source(x, y, z, interface): whether the voxel is a source; interface set if
-// it is an interface voxel.  prepare: called by the whole workgroup first.
+// source(x, y, z): whether the voxel is a source.  prepare: called by the whole
+// workgroup first.
 template <typename P, typename F>
 __device__ __forceinline__ void fsm_init_region(const FsmInit &p, P &&prepare, F &&source) {
   __shared__ int has[kInitX / TX], lives[kInitX / TX];
@@ -77,12 +78,11 @@ __device__ __forceinline__ void fsm_init_region(const FsmInit &p, P &&prepare, F
     for (int r = row; r < TY * TZ; r += 256 / kInitX) {
       const int y = y0 + r % TY, z = z0 + r / TY;
       if (y >= p.ny || z >= p.nz) continue;
-      bool fc = false;
-      const double d = source(x, y, z, fc) ? 0.0 : __builtin_huge_val();
+      const double d = source(x, y, z) ? 0.0 : __builtin_huge_val();
       const int64_t v = ((int64_t)z * p.ny + y) * p.nx + x;
       p.dA[v] = d;
       p.dB[v] = d;
-      any |= fc;
+      any |= d == 0.0;
       inf |= d != 0.0;
     }
   if (any) has[lx / TX] = 1;
@@ -99,10 +99,9 @@ __device__ __forceinline__ void fsm_init_region(const FsmInit &p, P &&prepare, F
 
 __global__ __launch_bounds__(256) void k_fsm_init(const uint8_t *__restrict__ seg,
                                                   const uint8_t *__restrict__ iface, FsmInit p) {
-  fsm_init_region(p, [] {}, [&](int x, int y, int z, bool &fc) {
+  fsm_init_region(p, [] {}, [&](int x, int y, int z) {
     const int64_t v = ((int64_t)z * p.ny + y) * p.nx + x;
-    fc = iface[v] != 0;
-    return seg[v] == 0 || fc;
+    return seg[v] == 0 || iface[v] != 0;
   });
 }
 
@@ -110,12 +109,12 @@ __global__ __launch_bounds__(256) void k_fsm_init(const uint8_t *__restrict__ se
 // (final_phase_map), without the byte maps: a voxel starts at +inf iff it
 // and its six face neighbours (periodic) are all high density -- otherwise
 // it is low density or an interface voxel, a source.  Four threads per row of
-// the region form both masks of its 64 voxels, from whole words, in LDS: a look
+// the region form the mask of its 64 voxels, from whole words, in LDS: a look
 // at seven bits per voxel was a chain of loads per row, and the workgroups of a
 // small grid took 13 us for it.
 __global__ __launch_bounds__(256) void k_fsm_init_bits(const uint32_t *b0, const uint32_t *b1,
                                                        const Ctl *ctl, FsmInit p) {
-  __shared__ unsigned long long high[TY * TZ], inner[TY * TZ], parts[4][TY * TZ];
+  __shared__ unsigned long long inner[TY * TZ], parts[4][TY * TZ];
   static_assert(kInitX == 64 && TY * TZ == 64, "two words a row, 64 rows, 4 threads a row");
   const int nx = p.nx, ny = p.ny, nz = p.nz, W = (nx + 31) >> 5;
   fsm_init_region(
@@ -142,7 +141,6 @@ __global__ __launch_bounds__(256) void k_fsm_init_bits(const uint32_t *b0, const
             const int last = nx - 1 - k * 32;  // place of the row's last voxel
             if (last < 64) after |= (unsigned long long)(own[0] & 1u) << last;
             else after |= (unsigned long long)(own[k + 2] & 1u) << 63;
-            high[r] = m;
             a = m & (m << 1 | before) & after;
           } else if (part == 1) {
             a = row(y == 0 ? ny - 1 : y - 1, z) & row(y + 1 == ny ? 0 : y + 1, z);
@@ -154,11 +152,8 @@ __global__ __launch_bounds__(256) void k_fsm_init_bits(const uint32_t *b0, const
         __syncthreads();
         if (part == 0) inner[r] = parts[0][r] & parts[1][r] & parts[2][r] & parts[3][r];
       },
-      [&](int x, int y, int z, bool &fc) {
-        const int r = (z % TZ) * TY + y % TY, b = x & (kInitX - 1);
-        const bool in = inner[r] >> b & 1ull;
-        fc = !in && (high[r] >> b & 1ull);
-        return !in;
+      [&](int x, int y, int z) {
+        return !(inner[(z % TZ) * TY + y % TY] >> (x & (kInitX - 1)) & 1ull);
       });
 }
 
@@ -240,8 +235,8 @@ __device__ __forceinline__ double godunov(double a0, double a1, double a2, const
 
 // ------------------------------------------------------------- tiled sweep
 // Launch L reads buf[(L-1)&1] and writes buf[L&1] for its active tiles.
-// Active in the first launch are the tiles with an interface voxel and their
-// face neighbours (found from the init's flags, or listed by k_fsm_first); a
+// Active in the first launch are the tiles with a source and their face
+// neighbours (found from the init's flags, or listed by k_fsm_first); a
 // tile that changes in launch L puts itself, and the face neighbours next to a
 // voxel that changed, on launch L + 1's list (stamp: the last launch a tile was
 // listed for).  live: tiles with a voxel that is not a source; the others never
