@@ -50,6 +50,7 @@ int64_t fsm_tile_count(const int32_t nv[3]) {
 constexpr int kInitX = 64;
 struct FsmInit {
   int nx, ny, nz, ntx, nty;
+  int nbx;  // regions along x (nty along y)
   double *dA, *dB;
   uint8_t *first;   // tiles holding a source; null: no tiles
   uint8_t *live;    // tiles with a voxel that is not a source
@@ -58,17 +59,27 @@ struct FsmInit {
   int nflags;
 };
 
+// A workgroup's region.  The grid is one-dimensional: its other dimensions end at
+// 65,535 workgroups, which a long thin grid of voxels passes.
+struct InitRegion {
+  int x, y, z;
+};
+__device__ __forceinline__ InitRegion init_region(const FsmInit &p) {
+  const int b = (int)blockIdx.x, r = b / p.nbx;
+  return {b - r * p.nbx, r % p.nty, r / p.nty};
+}
+
 // source(x, y, z): whether the voxel is a source.  prepare: called by the whole
 // workgroup first.
 template <typename P, typename F>
 __device__ __forceinline__ void fsm_init_region(const FsmInit &p, P &&prepare, F &&source) {
   __shared__ int has[kInitX / TX], lives[kInitX / TX];
   const int lx = threadIdx.x & (kInitX - 1), row = threadIdx.x / kInitX;
-  const int x = blockIdx.x * kInitX + lx, y0 = blockIdx.y * TY, z0 = blockIdx.z * TZ;
+  const InitRegion at = init_region(p);
+  const int x = at.x * kInitX + lx, y0 = at.y * TY, z0 = at.z * TZ;
   if (threadIdx.x < kInitX / TX) has[threadIdx.x] = lives[threadIdx.x] = 0;
-  const int64_t block = ((int64_t)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
-  for (int64_t f = block * 256 + threadIdx.x; f < p.nflags;
-       f += 256 * (int64_t)gridDim.x * gridDim.y * gridDim.z)
+  for (int64_t f = (int64_t)blockIdx.x * 256 + threadIdx.x; f < p.nflags;
+       f += 256 * (int64_t)gridDim.x)
     p.flags[f] = 0u;
   prepare();
   __syncthreads();
@@ -88,9 +99,9 @@ __device__ __forceinline__ void fsm_init_region(const FsmInit &p, P &&prepare, F
   if (any) has[lx / TX] = 1;
   if (inf) lives[lx / TX] = 1;
   __syncthreads();
-  const int tx = blockIdx.x * (kInitX / TX) + threadIdx.x;
+  const int tx = at.x * (kInitX / TX) + threadIdx.x;
   if (p.first && threadIdx.x < kInitX / TX && tx < p.ntx) {
-    const int64_t t = ((int64_t)blockIdx.z * p.nty + blockIdx.y) * p.ntx + tx;
+    const int64_t t = ((int64_t)at.z * p.nty + at.y) * p.ntx + tx;
     p.first[t] = (uint8_t)has[threadIdx.x];
     p.live[t] = (uint8_t)lives[threadIdx.x];
     p.stamp[t] = p.changed[t] = 0u;
@@ -121,11 +132,12 @@ __global__ __launch_bounds__(256) void k_fsm_init_bits(const uint32_t *b0, const
       p,
       [&] {
         const int r = threadIdx.x & 63, part = threadIdx.x >> 6;
-        const int y = blockIdx.y * TY + r % TY, z = blockIdx.z * TZ + r / TY;
+        const InitRegion at = init_region(p);
+        const int y = at.y * TY + r % TY, z = at.z * TZ + r / TY;
         if (y < ny && z < nz) {
           const uint32_t *__restrict__ s =
               final_phase_map(ctl->maj_chg1, ctl->maj_chg2, kMajorityMaxPasses, b0, b1);
-          const int k = blockIdx.x * 2;
+          const int k = at.x * 2;
           auto row = [&](int yy, int zz) {
             const uint32_t *q = s + ((int64_t)zz * ny + yy) * W + k;
             return (unsigned long long)q[0] | (k + 1 < W ? (unsigned long long)q[1] << 32 : 0ull);
@@ -606,10 +618,10 @@ static SweepTiles sweep_tiles(const int32_t nv[3], void *tiles, uint32_t *flags,
 
 static FsmInit init_args(const int32_t nv[3], bool tiled, double *dA, double *dB, void *tiles,
                          uint32_t *flags, int max_steps, dim3 *grid) {
-  *grid = dim3((unsigned)ceil_div(nv[0], kInitX), (unsigned)ceil_div(nv[1], TY),
-               (unsigned)ceil_div(nv[2], TZ));
+  const int64_t nbx = ceil_div(nv[0], kInitX);
+  *grid = dim3((unsigned)(nbx * ceil_div(nv[1], TY) * ceil_div(nv[2], TZ)));
   const SweepTiles w = sweep_tiles(nv, tiles, flags, max_steps);
-  return FsmInit{nv[0], nv[1], nv[2], w.ntx, w.nty, dA, dB,
+  return FsmInit{nv[0], nv[1], nv[2], w.ntx, w.nty, (int)nbx, dA, dB,
                  tiled ? const_cast<uint8_t *>(w.first) : nullptr, const_cast<uint8_t *>(w.live),
                  w.stamp, w.changed, flags, (int)fsm_flag_words(max_steps)};
 }

@@ -1,7 +1,8 @@
 """dcm_sweep_distance on maps whose interface is not that of the phase map: every
 low-density voxel and every marked voxel is a source, wherever the marks are.
-Grids of one tile and of many.  Against the oracle's distances: 1e-12 of rc_grid,
-the bar of the other sweep tests."""
+Grids of one tile and of many.  And long thin grids, of more than 65,535 layers of
+tiles.  Against the oracle's distances: 1e-12 of rc_grid, the bar of the other
+sweep tests."""
 import numpy as np
 import pytest
 import torch
@@ -55,3 +56,21 @@ def test_any_marks(kind, nv):
                                500, dist)
         assert dcm.dcm_sync_status(ctx) == dcm.DCM_OK
     assert np.max(np.abs(host(dist) - D)) <= 1e-12 * rcg
+
+
+@pytest.mark.parametrize("nv", [(2, 3, 600000), (3, 1, 530000)])
+def test_long_thin_grid(nv):
+    print(f"[gpu] sweep of a long thin grid {nv}", flush=True)
+    rng = np.random.default_rng(3)
+    n = int(np.prod(nv))
+    seg = (rng.uniform(0, 1, n) > 0.02).astype(np.uint8)
+    marked = oracle.interface(nv, seg)
+    D, passes = oracle.fsm(nv, (1.0, 1.0, 1.0), seg, marked, 8.0)
+    assert passes > 0
+    grid = dcm.make_grid(tuple(float(k) for k in nv), 1.0)
+    dist = torch.zeros(n, **F64)
+    with Ctx() as ctx:
+        dcm.dcm_sweep_distance(ctx, dev(seg, torch.uint8), dev(marked, torch.uint8), grid, 8.0,
+                               500, dist)
+        assert dcm.dcm_sync_status(ctx) == dcm.DCM_OK
+    assert np.max(np.abs(host(dist) - D)) <= 8e-12
