@@ -504,7 +504,9 @@ dcm_status sweep_enqueue(dcm_ctx *ctx, const uint8_t *seg, const uint8_t *iface,
   DCM_TRY(ensure(ctx, ctx->dB, nvox * sizeof(double)));
   DCM_TRY(ensure(ctx, ctx->fsm_chg, fsm_tile_bytes(grid.n)));
   void *tiles = ctx->fsm_chg.p;
-  DCM_TRY(ensure(ctx, ctx->fsm_flags, fsm_flag_words(max_waves) * sizeof(uint32_t)));
+  // (for 1024 passes at least, as dcm_step's: sweeps of other limits need no other)
+  DCM_TRY(ensure(ctx, ctx->fsm_flags,
+                 fsm_flag_words(std::max(max_waves, 1024)) * sizeof(uint32_t)));
   uint32_t *flags = ptr<uint32_t>(ctx->fsm_flags);
   hipStream_t s = ctx->stream;
   hipEvent_t ev;
@@ -891,7 +893,8 @@ dcm_status forces_impl(dcm_ctx *ctx, dcm_lj lj, int pair_rule, int prec, int ev_
   const int split_log =
       use_list ? ctx->list_split : pair_split_log(n, ctx->rc_bound, pair_rule, rel, step_rc_min);
   const int64_t blocks = pair_blocks(n, split_log);
-  DCM_TRY(ensure(ctx, ctx->partials, blocks * kPartialSlots * sizeof(double)));
+  DCM_TRY(ensure(ctx, ctx->partials, pair_blocks(n, pair_max_split_log(n, ctx->rc_bound)) *
+                                         kPartialSlots * sizeof(double)));
   double span = 0.0;  // largest coordinate magnitude in the extended grid
   for (int k = 0; k < 3; ++k)
     span = std::max(span, ctx->cell_box.L[k] + 2.0 * ctx->halo[k] * ctx->cell_len[k]);

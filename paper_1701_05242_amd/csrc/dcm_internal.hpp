@@ -552,6 +552,15 @@ inline int pair_split_log(int64_t n, double rc_max, int rule, bool compact, doub
   if (alone) return m < 20e3 ? 4 : (m < 150e3 ? 3 : 2);
   return n < 8000 ? 3 : (n < 100000 ? 2 : 1);
 }
+// The most lanes that any call takes over these n particles: scratch is sized for
+// it, so a call in one form can be captured after one in another.
+inline int pair_max_split_log(int64_t n, double rc_max) {
+  int most = pair_split_log(n, rc_max, DCM_PAIR_MAX, false, 0.0);
+  for (const bool compact : {false, true})
+    for (const double step_rc_min : {0.0, 0.5 * rc_max, rc_max})
+      most = std::max(most, pair_split_log(n, rc_max, DCM_PAIR_OWN, compact, step_rc_min));
+  return most;
+}
 void launch_pair(hipStream_t s, const PairArgs &a, int rule, int prec);
 // rule DCM_PAIR_MAX_N3: sorted-order sums to caller order (24 eps applied)
 void launch_n3_out(hipStream_t s, const double4 *f, const int32_t *cnt, const int32_t *perm,

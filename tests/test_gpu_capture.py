@@ -1,9 +1,10 @@
-"""Cell builds around stream capture: the cells' counters are right whatever a
-capture left behind.  A capture that is dropped, or fails, after it made the
-buffers grow leaves the next eager build a buffer nothing has cleared; a
-captured build is replayed between eager builds.  One plan serves a batch's
-calls of any rule and precision, so such a call can be captured after one of
-another kind.  Forces and counts equal those of a fresh context bit for bit."""
+"""Library calls around stream capture.  The cells' counters are right whatever a
+capture left behind: a capture that is dropped, or fails, after it made the
+buffers grow leaves the next eager build a buffer nothing has cleared; a captured
+build is replayed between eager builds.  One plan serves a batch's calls of any
+rule and precision, and scratch is sized for all of them, so a call can be
+captured after one of another kind.  Forces and counts equal those of a fresh
+context bit for bit."""
 import ctypes
 
 import numpy as np
@@ -248,4 +249,57 @@ def test_batch_of_every_rule_and_precision(queues):
             call(ctx, before)
             check(ctx, ref_before)
         assert hip("hipGraphExecDestroy", run) == 0 and hip("hipGraphDestroy", g) == 0
+    dcm.dcm_destroy(ctx)
+
+
+# lanes per particle of the two forms: 4 and 8; 1 and 2
+@pytest.mark.parametrize("n,warm,then", [
+    (5000, (dcm.DCM_PAIR_OWN, dcm.DCM_FP32_MIXED), (dcm.DCM_PAIR_OWN, dcm.DCM_FP64)),
+    (360000, (dcm.DCM_PAIR_MAX, dcm.DCM_FP64), (dcm.DCM_PAIR_OWN, dcm.DCM_FP64)),
+])
+def test_forces_of_another_form(n, warm, then):
+    """Forces captured after a first call of another rule or precision."""
+    print(f"[gpu] forces captured after another form n={n}", flush=True)
+    rng = np.random.default_rng(n)
+    m = int(np.ceil(n ** (1.0 / 3.0)))
+    L = 1.1 * m
+    site = rng.permutation(m ** 3)[:n]
+    p = (np.stack(np.unravel_index(site, (m, m, m)), 1) + 0.5) * 1.1
+    x = [dev(p[:, a]) for a in range(3)]
+    rc = dev(workloads.uniform_cutoffs(n, 2.5, 4.0, seed=1))
+    out = outputs(n)
+
+    def forces(ctx, form, o):
+        dcm.dcm_forces(ctx, dcm.make_lj(), *o[:3], pair_rule=form[0], prec=form[1],
+                       ev_flags=dcm.DCM_EV_COUNTS, nnbr=o[3])
+
+    stream = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    refs = []
+    for form in (warm, then):
+        ctx = dcm.dcm_create(stream)
+        dcm.dcm_build_cells(ctx, *x, rc, (L, L, L), EDGE, dcm.DCM_FP32_MIXED, rc_bound=4.0)
+        forces(ctx, form, out)
+        assert dcm.dcm_sync_status(ctx) == dcm.DCM_OK
+        refs.append([host(t).copy() for t in out])
+        dcm.dcm_destroy(ctx)
+    ctx = dcm.dcm_create(stream)
+    dcm.dcm_build_cells(ctx, *x, rc, (L, L, L), EDGE, dcm.DCM_FP32_MIXED, rc_bound=4.0)
+    forces(ctx, warm, out)
+    assert dcm.dcm_sync_status(ctx) == dcm.DCM_OK
+    equal(out, refs[0])
+    begin(stream)
+    forces(ctx, then, out)
+    code, g = end(stream)
+    assert code == 0
+    run = ctypes.c_void_p()
+    assert hip("hipGraphInstantiate", ctypes.byref(run), g, None, None, ctypes.c_size_t(0)) == 0
+    for _ in range(3):
+        assert hip("hipGraphLaunch", run, handle(stream)) == 0
+        assert dcm.dcm_sync_status(ctx) == dcm.DCM_OK
+        equal(out, refs[1])
+        forces(ctx, warm, out)
+        assert dcm.dcm_sync_status(ctx) == dcm.DCM_OK
+        equal(out, refs[0])
+    assert hip("hipGraphExecDestroy", run) == 0 and hip("hipGraphDestroy", g) == 0
     dcm.dcm_destroy(ctx)
