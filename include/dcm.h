@@ -359,7 +359,11 @@ dcm_status dcm_forces_list(dcm_ctx *ctx, dcm_lj lj, int prec, int ev_flags, doub
  * (non-blocking, default priority) beside the distance sweep, and the
  * context's stream waits for it before the cutoffs are assigned; every
  * launch of the call is complete once the context's stream is.  A stream
- * being captured into a graph keeps the build on the context's stream. */
+ * being captured into a graph keeps the build on the context's stream.
+ * A step's forces are those of the separate calls on the same cells within
+ * rounding, and not bit for bit: how many lanes share a particle's sums depends
+ * on its own passes' sizes, and dcm_forces, dcm_forces_list and
+ * dcm_forces_batched have a rule of their own. */
 dcm_status dcm_step(dcm_ctx *ctx, double *x, double *y, double *z, double *vx, double *vy,
                     double *vz, double *fx, double *fy, double *fz, int64_t n, double mass,
                     dcm_box box, dcm_lj lj, dcm_rule rule, dcm_grid grid, double rc_grid,
@@ -388,10 +392,12 @@ typedef struct {
  * those of dcm_build_cells(x, y, z, rc, n, box, cell_edge, rc_bound) followed
  * by dcm_forces(lj, pair_rule, prec, ev_flags) -- bit for bit when the cell
  * edge is the same -- but all systems share one launch of each build kernel
- * and one persistent pair kernel that takes blocks of 256 particles from a
- * work queue ordered by estimated cost (largest first), or from one such
- * queue per XCD (dcm_set_batched_queues), so systems of very different size
- * and cutoff balance across the GPU (the dynamic scheduling of Section 2.4).
+ * and one persistent pair kernel that takes work items of up to 256 particles
+ * (fewer where several lanes share a particle) from a work queue ordered by
+ * estimated cost (largest first), or from one such queue per XCD
+ * (dcm_set_batched_queues), so systems of very different size and cutoff
+ * balance across the GPU (the dynamic scheduling of Section 2.4).  Calls of any
+ * rule, precision and outputs on the same descriptors share one plan.
  * sys: host array of nsys descriptors (nsys = 0 is a no-op).  Systems whose
  * cell_edge is <= 0 share one edge chosen, together with the work-queue
  * layout and the pair kernel's row-list size, by timing a few candidates the

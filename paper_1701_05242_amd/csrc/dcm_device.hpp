@@ -114,22 +114,6 @@ struct ExtGeom {
   double L[3];
 };
 
-// Real cell rc behind extended cell e, and the periods p[a] crossed.
-__device__ __forceinline__ void ext_to_real(const ExtGeom &g, int64_t e, int &rc, int p[3]) {
-  const int ex = (int)(e % g.ne[0]);
-  const int64_t t = e / g.ne[0];
-  const int ey = (int)(t % g.ne[1]);
-  const int ez = (int)(t / g.ne[1]);
-  const int u[3] = {ex - g.h[0], ey - g.h[1], ez - g.h[2]};
-  int r[3];
-#pragma unroll
-  for (int a = 0; a < 3; ++a) {
-    r[a] = wrap_index(u[a], g.nc[a]);
-    p[a] = (u[a] - r[a]) / g.nc[a];  // periods crossed: exact division
-  }
-  rc = (r[2] * g.nc[1] + r[1]) * g.nc[0] + r[0];
-}
-
 // floor(a / b) for b > 0
 __device__ __forceinline__ int floor_div(int a, int b) {
   const int q = a / b;
@@ -233,20 +217,6 @@ __device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long v)
   return v;
 }
 
-// Add 1 to hist[key] for every valid lane with one atomic per distinct key in
-// the wavefront.  Must be reached by all lanes of the wavefront together.
-template <typename Counter>
-__device__ __forceinline__ void wave_aggregated_add(Counter *hist, uint32_t key, bool valid) {
-  unsigned long long pending = __ballot(valid);
-  while (pending) {
-    const int leader = __ffsll((long long)pending) - 1;
-    const uint32_t k = __shfl(key, leader, 64);
-    const unsigned long long same = __ballot(valid && key == k);
-    if ((int)(threadIdx.x & 63) == leader) atomicAdd(&hist[k], (Counter)__popcll(same));
-    pending &= ~same;
-  }
-}
-
 // Run-aggregated counters for key-ordered input (cell-sorted particles): the
 // lanes of a wavefront are cut into runs of consecutive valid lanes with equal
 // keys, and the first lane of every run issues one atomic for its run -- all
@@ -291,26 +261,6 @@ __device__ __forceinline__ int wave_run_slot(int32_t *fill, uint32_t key, bool v
   const unsigned long long upto = heads & (lane == 63 ? ~0ull : ((2ull << lane) - 1ull));
   const int hl = upto ? 63 - __clzll((long long)upto) : lane;
   return __shfl(base, hl, 64) + (lane - hl);
-}
-
-// Reserve one slot per valid lane in fill[key] (lanes with equal keys share
-// one atomic and take consecutive slots in lane order); returns the slot.
-__device__ __forceinline__ int wave_aggregated_slot(int32_t *fill, uint32_t key, bool valid) {
-  const int lane = (int)(threadIdx.x & 63);
-  unsigned long long pending = __ballot(valid);
-  int slot = 0;
-  while (pending) {
-    const int leader = __ffsll((long long)pending) - 1;
-    const uint32_t k = __shfl(key, leader, 64);
-    const unsigned long long same = __ballot(valid && key == k);
-    int base = 0;
-    if (lane == leader) base = atomicAdd(&fill[k], (int32_t)__popcll(same));
-    base = __shfl(base, leader, 64);
-    if (valid && key == k)
-      slot = base + (int)__popcll(same & ((1ull << lane) - 1ull));
-    pending &= ~same;
-  }
-  return slot;
 }
 
 }  // namespace dcm

@@ -262,7 +262,7 @@ __device__ __forceinline__ double godunov(double a0, double a1, double a2, const
 // started, and one that starts late finds nothing to take and catches up.
 //
 // A pass is bound by latency: one after the other, the sub-waves of the tiles
-// that the front crosses, each a solve (94 vector instructions, 70 of them
+// that the front crosses, each a solve (107 vector instructions, 75 of them
 // FP64, where all three axes count) and a barrier long.  So one thread owns
 // one voxel, in a register; a wavefront owns a 4 x 4 x 4 block, so that a
 // front of any direction touches few blocks; one bit per block says that a
@@ -274,7 +274,8 @@ __device__ __forceinline__ double godunov(double a0, double a1, double a2, const
 // 1024 voxels in every sub-wave, the active tiles found by a look at all 26
 // neighbours of every tile) and after: 120^3 grid, droplet 326 -> 160 us;
 // 200 x 100 x 100, cylinder 419 -> 285 us; 160 x 160 x 400 settled (64 passes
-// launched, then 15) 354 -> 225 us.
+// launched, then 15) 354 -> 225 us; whole steps 1% more since with the library's
+// square root.
 struct SweepTiles {
   int ntx, nty, ntz;
   const uint8_t *first, *live;

@@ -41,11 +41,12 @@ constexpr int kPairBlock = 256;
 // Row ranges per lane per chunk (LDS: 8 B each), for the kernels reading FP64
 // records and for those reading compact records.  A smaller list allows more
 // resident workgroups but cuts a lane's rows into more chunks.  The FP64
-// kernels share a particle among two to sixteen lanes (pair_split_log), whose
-// rows fit a list of 18: four workgroups on a compute unit instead of three
-// with 24 (1.2 M-particle step: 1.231 / 1.206 / 1.213 ms with 24 / 18 / 12).  The compact-record kernels also hold their
-// close-pair queue (kNearCap + 1 entries of 4 B); with 14 row entries both
-// fit in the 40 KB of LDS that keeps four workgroups on a compute unit.
+// kernels mostly share a particle among two to sixteen lanes (pair_split_log),
+// whose rows fit a list of 18: four workgroups on a compute unit instead of three
+// with 24 (1.2 M-particle step: 1.231 / 1.206 / 1.213 ms with 24 / 18 / 12).  The
+// compact-record kernels also hold their close-pair queue (kNearCap + 1 entries of
+// 4 B); with 14 row entries both fit in the 40 KB of LDS that keeps four
+// workgroups on a compute unit.
 #ifndef DCM_PAIR_SEGCAP
 #define DCM_PAIR_SEGCAP 18
 #endif
@@ -389,7 +390,7 @@ struct LaneGeo {
   double sig2;
   int zlo, zhi, cx, cy, cz, self;
   int slot;  // sorted slot of the lane's particle
-  // the lane's share of its particle's rows (row_part): part `part` of `parts`
+  // the lane's share of its particle's rows (row_skew): part `part` of `parts`
   int part, parts, skew;
 };
 
