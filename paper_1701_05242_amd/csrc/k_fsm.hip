@@ -179,7 +179,7 @@ __global__ __launch_bounds__(256) void k_fsm_init_bits(const uint32_t *b0, const
 // (SweepGeom) indexed by the axis of the largest a.  A quotient x / A is then
 // q = x r with r = 1/A correctly rounded, corrected once by its exact
 // remainder, which gives the correctly rounded quotient (P. Markstein, IBM J.
-// Res. Dev. 34, 1990).
+// Res. Dev. 34, 1990).  For the square root see root_of.
 struct SweepGeom {
   int nx, ny, nz;
   double h[3], w[3];
@@ -195,6 +195,25 @@ __device__ __forceinline__ double by_axis(const double v[3], int k) {
 __device__ __forceinline__ double div_by(double x, double A, double r) {
   const double q = x * r;
   return fma(fma(-q, A, x), r, q);
+}
+
+// Square root of v, 0 or of the size that spacings between 1e-130 and 1e130 give
+// (w rounded off at its last place, to ten w).  With y near 1 / sqrt(v) from the
+// hardware and e = 1 - v y^2, the binomial series of (1 - e)^(-1/2) gives
+// 1 / sqrt(v) = y (1 + e / 2 + 3 e^2 / 8 + ...): one step of third order (A. S.
+// Householder, The Numerical Treatment of a Single Nonlinear Equation, 1970),
+// which leaves 5 e^3 / 16, below a rounding for e under 2^-18.  g = v y1 is then
+// within three units of its last place of the root, and g + r y1 / 2, r its
+// remainder v - g^2 (Markstein, as above), within a few 2^-52 of a unit before
+// its one rounding.  (3 to 5% of a sweep against the library's, which must serve
+// every argument: 10 million voxels, interface everywhere, 4478 and 4308 us.)
+__device__ __forceinline__ double root_of(double v) {
+  const double y = __builtin_amdgcn_rsq(v);
+  const double e = fma(-(v * y), y, 1.0);
+  const double y1 = fma(y * e, fma(0.375, e, 0.5), y);
+  const double g = v * y1;
+  const double s = fma(fma(-g, g, v), 0.5 * y1, g);
+  return v == 0.0 ? 0.0 : s;
 }
 
 // ISO: equal spacings on every axis, so only the a's need ordering
@@ -231,14 +250,14 @@ __device__ __forceinline__ double godunov(double a0, double a1, double a2, const
     const double p1 = w1 * b1, p2 = w2 * b2;
     double disc2 = p1 * p1 - A2 * (p1 * b1 - 1.0);
     disc2 = disc2 < 0.0 ? 0.0 : disc2;
-    const double d2 = a0 + div_by(p1 + sqrt(disc2), A2, R2);
+    const double d2 = a0 + div_by(p1 + root_of(disc2), A2, R2);
     d = more ? d2 : d;
     more = more && !(d2 <= a2);
     if (__ballot(more) != 0ull) {
       const double B3 = p1 + p2;
       double disc3 = B3 * B3 - A3 * ((p1 * b1 + p2 * b2) - 1.0);
       disc3 = disc3 < 0.0 ? 0.0 : disc3;
-      const double d3 = a0 + div_by(B3 + sqrt(disc3), A3, R3);
+      const double d3 = a0 + div_by(B3 + root_of(disc3), A3, R3);
       d = more ? d3 : d;
     }
   }
@@ -262,7 +281,7 @@ __device__ __forceinline__ double godunov(double a0, double a1, double a2, const
 // started, and one that starts late finds nothing to take and catches up.
 //
 // A pass is bound by latency: one after the other, the sub-waves of the tiles
-// that the front crosses, each a solve (107 vector instructions, 75 of them
+// that the front crosses, each a solve (97 vector instructions, 69 of them
 // FP64, where all three axes count) and a barrier long.  So one thread owns
 // one voxel, in a register; a wavefront owns a 4 x 4 x 4 block, so that a
 // front of any direction touches few blocks; one bit per block says that a
@@ -274,8 +293,7 @@ __device__ __forceinline__ double godunov(double a0, double a1, double a2, const
 // 1024 voxels in every sub-wave, the active tiles found by a look at all 26
 // neighbours of every tile) and after: 120^3 grid, droplet 326 -> 160 us;
 // 200 x 100 x 100, cylinder 419 -> 285 us; 160 x 160 x 400 settled (64 passes
-// launched, then 15) 354 -> 225 us; whole steps 1% more since with the library's
-// square root.
+// launched, then 15) 354 -> 225 us.
 struct SweepTiles {
   int ntx, nty, ntz;
   const uint8_t *first, *live;
