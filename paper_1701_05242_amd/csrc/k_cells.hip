@@ -119,9 +119,10 @@ template <bool ASSIGN>
 __global__ __launch_bounds__(256) void k_cell_count(
     CutoffArgs cut, const double *__restrict__ x, const double *__restrict__ y,
     const double *__restrict__ z, const double *__restrict__ rc, int64_t n, double Lx, double Ly,
-    double Lz, int nx, int ny, int nz, double sx, double sy, double sz, double rc_cap, int32_t *__restrict__ cell_of,
-    int32_t *__restrict__ slot, int32_t *count, unsigned long long *__restrict__ block_max,
-    uint32_t *__restrict__ xq, Ctl *ctl, uint32_t *status) {
+    double Lz, int nx, int ny, int nz, double sx, double sy, double sz, double rc_cap,
+    int32_t *__restrict__ cell_of, int32_t *__restrict__ slot, int32_t *count,
+    unsigned long long *__restrict__ block_max, uint32_t *__restrict__ xq, Ctl *ctl,
+    uint32_t *status) {
   const CutoffField<ASSIGN> field(cut);
   unsigned long long rmax = 0;
   if (blockIdx.x == 0 && threadIdx.x == 0) ctl->big_cells = 0u;  // for the cell sort that follows
